@@ -215,8 +215,9 @@ ecc_status ecc_compute_streamed(ecc_ctx* ctx, const ecc_image* img, int32_t nbin
 ecc_status ecc_smooth13(ecc_ctx* ctx, const float* in, float* out, int64_t n1, int64_t n2, const float* taps,
                         void* hip_stream);
 
-/* Launch shape of the single-image kernel: waves per workgroup (a workgroup
- * covers waves * 63 consecutive position columns), rows (2D) or planes (3D) per
+/* Launch shape of the single-image kernel: waves per workgroup (2D: a workgroup
+ * covers waves * 63 consecutive position columns; 3D: each wave takes 126
+ * neighbouring columns of a strip of rows), rows (2D) or planes (3D) per
  * workgroup brick, resident workgroups per CU aimed for, `window`, the bins
  * one pass counts in LDS (Sec. 4.3's block-shared histogram; fewer than nbins
  * makes several passes over the image, each with less LDS; 0: all of nbins up to

@@ -308,20 +308,77 @@ struct Sizes {
 };
 
 // Launch shape of the main kernel for one image:
-//  - waves: a workgroup's waves cover a contiguous x-chunk of 63 * waves position
+//  - 3D: shape_3d;
+//  - 2D: a workgroup's waves cover a contiguous x-chunk of 63 * waves position
 //    columns, the whole row when it has at most 9 * 63 positions, else chunks of
-//    8 * 63;
-//  - depth: planes (3D) or rows (2D) per workgroup brick, chosen so that there are
-//    about two bricks per CU;
-//  - grid: at most two resident workgroups per CU (more concurrent bricks cost
-//    DRAM locality), at least enough that no workgroup histogram can reach 2^31
-//    (every voxel position adds at most 8 in absolute value: four type counts of
-//    at most 1, and at a brick's last plane four more).
+//    8 * 63; `depth` rows per workgroup brick, chosen so that there are about two
+//    bricks per CU;
+//  - grid: at least enough that no workgroup histogram can reach 2^31 (every
+//    voxel position adds at most 8 in absolute value: four type counts of at
+//    most 1, and at a brick's last plane four more).
 using TuneKey = std::tuple<int, int, int, int, int64_t, int64_t, int64_t>;
+
+// Constants of shape_3d's model: planes' worth of work a brick starts with (its
+// places, first plane and last counts), microseconds of a plane step per wave on a
+// SIMD (about 290 vector instructions at 4 cycles), and of a workgroup row's bin
+// through the merge (8 bytes written and read).
+constexpr double kStartPlanes = 2.5, kPlaneUs = 0.5, kRowUs = 2e-6;
 
 TuneKey tune_key(const ecc_ctx* ctx, const Job& j, int32_t nbins)
 {
     return TuneKey{j.ndim, j.dtype, ctx->construction, nbins > ecc::kMaxLdsBins ? 1 : 0, j.g.n0, j.g.n1, j.g.n2};
+}
+
+// Launch shape of a 3D image (or of the npass hyperplanes of a 4D part that run
+// as one launch): waves per workgroup, workgroups, and planes per brick, from a
+// model of its time.  Every resident wave walks the same number of bricks but
+// for the last round, so what a shape loses is that round's idle workgroups, the
+// planes a brick starts up with, and the issue slots that few waves per SIMD
+// leave empty; more workgroups cost more rows to merge.  For each wave and
+// workgroup count the candidates are the depths whose bricks fill one, two or
+// three rounds exactly.  Measured on the 512^3 float32 field: 66 bricks of 8 waves
+// in 16 plane blocks over 512 workgroups (2.06 rounds) 148 us, a depth that fills
+// the rounds 127 us.  Fields that `tuned` sets are kept.
+template <class Resident>
+void shape_3d(const ecc_ctx* ctx, const Job& j, const ecc_launch_shape* tuned, Sizes& s, Resident&& resident)
+{
+    const double tasks = (double)ecc::strips_3d(j.g, ctx->construction).tasks, n0 = (double)j.g.n0;
+    const double npass = (double)j.npass, cus = (double)ctx->cu_count;
+    // share of the vector issue slots used by 1, 2, .. 8 waves per SIMD
+    static const double eff[9] = {0.2, 0.40, 0.66, 0.80, 0.87, 0.91, 0.94, 0.96, 0.97};
+    const int forced_w = tuned && tuned->waves > 0 ? (int)std::min<double>(std::min<int>(tuned->waves, ecc::kMaxWaves), tasks) : 0;
+    double best = HUGE_VAL;
+    s.waves = 0;
+    for (int w : {8, 4, 2, 1}) {
+        if (forced_w) w = forced_w;
+        else if (w > tasks || (w < 4 && s.waves > 0)) continue;
+        const double per_z = std::ceil(tasks / w);   // bricks of a plane block
+        const int rmax = resident(w);
+        int r0 = 1, r1 = std::min(rmax, 6);
+        if (tuned && tuned->wgs_per_cu > 0) r0 = r1 = std::min(tuned->wgs_per_cu, rmax);
+        for (int r = r0; r <= r1; ++r) {
+            const double gx = std::max(1.0, std::floor(cus * r / npass));   // workgroups per pass
+            for (int k = 1; k <= 3; ++k) {
+                double d;
+                if (tuned && tuned->depth > 0) d = (double)std::min<int64_t>(tuned->depth, 256);
+                else d = std::min(std::max(std::ceil(n0 / std::max(1.0, std::floor(gx * k / per_z))), 2.0), 256.0);
+                const double bricks = per_z * std::ceil(n0 / d);
+                const double g = std::min(gx, bricks), rounds = std::ceil(bricks / g);
+                const double busy = std::ceil(g * npass / cus) * w / 4.0;   // waves per SIMD
+                const int n = (int)std::min(8.0, std::ceil(busy));
+                const double us = rounds * (d + kStartPlanes) * busy / eff[n] * kPlaneUs +
+                                  g * npass * (double)s.window * kRowUs;
+                if (us < best) {
+                    best = us;
+                    s.waves = w;
+                    s.depth = (int64_t)d;
+                    s.grid = (int)std::min(gx * npass, cus * r);
+                }
+                if (tuned && tuned->depth > 0) break;
+            }
+        }
+        if (forced_w) break;
+    }
 }
 
 // The default launch shape of an image (waves 0 / depth 0 / wgs 0 in a forced
@@ -337,27 +394,6 @@ Sizes plan_sizes(const ecc_ctx* ctx, const Job& j, int32_t nbins, const ecc_laun
     const int cons = ctx->construction;
     const int64_t xpos = ecc::axis_positions(j.g.n2, cons);
     const int64_t cols = (xpos + ecc::kLaneCols - 1) / ecc::kLaneCols;
-    const int64_t max_waves = j.ndim == 3 ? ECC_MAX_WAVES_3D : ecc::kMaxWaves;
-    s.waves = (int)(cols <= max_waves ? cols : std::min<int64_t>(8, max_waves));
-    // 3D: when the last wave of a row would own only a few columns, one wave
-    // fewer and a packed tail (ecc::layout_3d) keep more lanes busy
-    if (j.ndim == 3 && cols > 1 && cols <= max_waves && ecc::layout_3d(j.g, cons, (int)cols - 1).spw > 0)
-        s.waves = (int)cols - 1;
-    if (tuned && tuned->waves > 0) s.waves = (int)std::min<int64_t>(std::min<int64_t>(tuned->waves, ecc::kMaxWaves), cols);
-    const int64_t chunk = ecc::kLaneCols * (int64_t)s.waves;
-    const int64_t nxc = (xpos + chunk - 1) / chunk;
-    const int64_t target = 2 * (int64_t)ctx->cu_count;
-    if (j.ndim == 3) {
-        int64_t d = (j.g.n0 * ecc::layout_3d(j.g, cons, s.waves).per_z + target - 1) / target;
-        s.depth = std::min<int64_t>(std::max<int64_t>(d, 4), 32);
-        if (tuned && tuned->depth > 0) s.depth = std::min<int64_t>(tuned->depth, 256);
-    } else {
-        int64_t d = (j.g.n1 * nxc + target - 1) / target;
-        d = std::min<int64_t>(std::max<int64_t>(d, ecc::kChunk2), 512);
-        if (tuned && tuned->depth > 0) d = std::min<int64_t>(tuned->depth, 4096);
-        s.depth = (d + ecc::kChunk2 - 1) / ecc::kChunk2 * ecc::kChunk2;
-    }
-    const int64_t bricks = ecc::wg_bricks(j.ndim, cons, j.g, s.waves, s.depth);
     // bins per LDS pass: all of them up to kMaxLdsBins, or fewer when tuned so
     s.window = std::min<int32_t>(nbins, ecc::kMaxLdsBins);
     if (tuned && tuned->window > 0) s.window = std::min<int32_t>(s.window, tuned->window);
@@ -366,12 +402,29 @@ Sizes plan_sizes(const ecc_ctx* ctx, const Job& j, int32_t nbins, const ecc_laun
     s.hist_copies = ecc::hist_copies(s.window);
     if (tuned && tuned->copies > 0) s.hist_copies = (uint32_t)tuned->copies;
     s.sentinel = ecc::lds_sentinel(nbins);
-    s.lds_bytes = 4u * ecc::lds_words(s.window, windowed, s.sentinel, s.hist_copies);
-    int want_per_cu = j.ndim == 3 ? ECC_MAX_WGS_PER_CU_3D : ECC_MAX_WGS_PER_CU_2D;
-    if (tuned && tuned->wgs_per_cu > 0) want_per_cu = tuned->wgs_per_cu;
-    const int per_cu = std::min(want_per_cu, ecc::resident_wgs_per_cu(j.ndim, j.dtype, ctx->construction, windowed,
-                                                                      s.waves, s.lds_bytes));
-    int64_t grid = std::min<int64_t>(bricks, (int64_t)ctx->cu_count * per_cu);
+    s.lds_bytes = 4u * (j.ndim == 3 ? s.hist_copies * s.hist_stride
+                                    : ecc::lds_words(s.window, windowed, s.sentinel, s.hist_copies));
+    auto resident = [&](int waves) {
+        return ecc::resident_wgs_per_cu(j.ndim, j.dtype, cons, windowed, waves, s.lds_bytes);
+    };
+    if (j.ndim == 3) {
+        shape_3d(ctx, j, tuned, s, resident);
+    } else {
+        s.waves = (int)(cols <= ecc::kMaxWaves ? cols : 8);
+        if (tuned && tuned->waves > 0) s.waves = (int)std::min<int64_t>(std::min<int64_t>(tuned->waves, ecc::kMaxWaves), cols);
+        const int64_t target = 2 * (int64_t)ctx->cu_count;
+        const int64_t chunk = ecc::kLaneCols * (int64_t)s.waves;
+        const int64_t nxc = (xpos + chunk - 1) / chunk;
+        int64_t d = (j.g.n1 * nxc + target - 1) / target;
+        d = std::min<int64_t>(std::max<int64_t>(d, ecc::kChunk2), 512);
+        if (tuned && tuned->depth > 0) d = std::min<int64_t>(tuned->depth, 4096);
+        s.depth = (d + ecc::kChunk2 - 1) / ecc::kChunk2 * ecc::kChunk2;
+        int want = ECC_MAX_WGS_PER_CU_2D;
+        if (tuned && tuned->wgs_per_cu > 0) want = tuned->wgs_per_cu;
+        s.grid = ctx->cu_count * std::min(want, resident(s.waves));
+    }
+    const int64_t bricks = ecc::wg_bricks(j.ndim, cons, j.g, s.waves, s.depth) * j.npass;
+    int64_t grid = std::min<int64_t>(bricks, s.grid);
     grid = std::max<int64_t>(grid, std::min<int64_t>(bricks, (j.nvox >> 27) + 1));
     s.grid = (int)std::max<int64_t>(grid, 1);
     s.off_counters = 0;   // fixed place, shared with the batch layout (never overwritten)
@@ -642,10 +695,10 @@ ecc_status enqueue_4d_part(ecc_ctx* ctx, char* base, const Sizes& sz, Job h, con
     };
     // With one LDS window every launch adds into the same workgroup rows and one
     // merge follows, when the int32 rows cannot overflow: a row's workgroup sees
-    // at most ceil(bricks / gx) bricks of chunk x rows x depth voxels per
-    // launch, and a voxel adds at most 8 in absolute value.
+    // at most ceil(bricks / gx) bricks of waves x 2 x 63 slots x rows x depth
+    // voxels per launch, and a voxel adds at most 8 in absolute value.
     const int64_t bricks = ecc::wg_bricks(3, ctx->construction, h.g, sz.waves, sz.depth);
-    const int64_t brick_vox = ecc::kLaneCols * sz.waves * ecc::kRows3 * sz.depth;
+    const int64_t brick_vox = 2 * ecc::kLaneCols * sz.waves * ecc::kStripRows * sz.depth;
     int64_t nlaunch = 0, per_row = 0;
     for_launches([&](int64_t, int64_t, int, bool, int64_t gx) {
         ++nlaunch;
@@ -693,7 +746,9 @@ ecc_status enqueue_nd(ecc_ctx* ctx, const Job& j, int32_t nbins, hipStream_t str
         auto it = ctx->tuned.find(tune_key(ctx, j, nbins));
         if (it != ctx->tuned.end()) force = &it->second;
     }
+    h.npass = (int32_t)std::min<int64_t>(j.nw, 1 << 20);   // the largest group of passes (enqueue_4d_part)
     Sizes sz = plan_sizes(ctx, h, nbins, force);
+    h.npass = 1;
     // one buffer per reduced axis a < d-4, a hyperplane of it, after the rest
     size_t mat_off[ECC_MAX_NDIM] = {};
     int64_t plane_vox[ECC_MAX_NDIM] = {};
@@ -1120,11 +1175,13 @@ ecc_status enqueue_streamed(ecc_ctx* ctx, const Job& vol, int32_t nbins, int64_t
         first.ndim = 3;
         first.nw = 1;
         first.nvox = plane_vox;
+        first.npass = (int32_t)std::min<int64_t>(S, 1 << 20);
     } else {
         first.g.n0 = std::min<int64_t>(S + 1, N);
         first.nvox = first.g.n0 * vol.g.n1 * vol.g.n2;
     }
     const Sizes sz = plan_sizes(ctx, first, nbins);
+    first.npass = 1;
     if ((st = ensure_ws(ctx, sz.total)) != ECC_OK) return st;
     hipError_t e;
     // the slab buffers are free once work already on `stream` is done
@@ -1647,12 +1704,16 @@ ecc_status ecc_autotune(ecc_ctx* ctx, const ecc_image* img, int32_t nbins, int32
         shape_job.ndim = 3;
         shape_job.nw = 1;
         shape_job.nvox = j.g.n0 * j.g.n1 * j.g.n2;
+        shape_job.npass = (int32_t)std::min<int64_t>(j.nw, 1 << 20);
     }
     const Sizes def = plan_sizes(ctx, shape_job, nbins);
     auto run = [&](const ecc_launch_shape* c) {
         return j.ndim >= 4 ? enqueue_nd(ctx, j, nbins, stream, false, c) : enqueue_one(ctx, j, nbins, stream, c);
     };
-    const int64_t cols = (ecc::axis_positions(j.g.n2, ctx->construction) + ecc::kLaneCols - 1) / ecc::kLaneCols;
+    // waves a workgroup can use: 3D: the wave tasks of a plane block; 2D: a row's
+    const int64_t cols = shape_job.ndim == 3
+                             ? ecc::strips_3d(shape_job.g, ctx->construction).tasks
+                             : (ecc::axis_positions(j.g.n2, ctx->construction) + ecc::kLaneCols - 1) / ecc::kLaneCols;
     std::vector<ecc_launch_shape> cand;
     auto add = [&](int waves, int64_t depth, int wgs, int32_t window = 0, int32_t copies = 0) {
         ecc_launch_shape c = {};
@@ -1667,24 +1728,20 @@ ecc_status ecc_autotune(ecc_ctx* ctx, const ecc_image* img, int32_t nbins, int32
                 return;
         cand.push_back(c);
     };
-    const int def_wgs = j.ndim == 2 ? ECC_MAX_WGS_PER_CU_2D : ECC_MAX_WGS_PER_CU_3D;
+    const int def_wgs = j.ndim == 2 ? ECC_MAX_WGS_PER_CU_2D
+                                    : std::max(1, (def.grid + ctx->cu_count - 1) / ctx->cu_count);
     add(def.waves, def.depth, def_wgs);
     for (int wgs : {1, 2, 3, 4})
         for (int64_t dm : {1, 2, 4}) {
             add(def.waves, def.depth * dm / 2, wgs);
             if (def.waves > 4) add((def.waves + 1) / 2, def.depth * dm / 2, wgs);
         }
-    // a 3D row whose default packs its narrow tail (one wave fewer than the
-    // row's chunks, ecc::layout_3d): also one chunk with the tail in its last wave
-    if (shape_job.ndim == 3 && def.waves + 1 == cols && cols <= ECC_MAX_WAVES_3D)
-        for (int wgs : {2, 3, 4})
-            for (int64_t dm : {1, 2}) add((int)cols, def.depth * dm, wgs);
     // 3D: for each workgroup count, the plane depth (between half and twice the
     // default) whose bricks split most evenly over the workgroups: the slowest
     // workgroup walks ceil(bricks / grid) bricks of depth planes plus about one
     // and a half planes of start-up each
     if (shape_job.ndim == 3) {
-        const int64_t per_z = ecc::layout_3d(shape_job.g, ctx->construction, def.waves).per_z;
+        const int64_t per_z = (cols + def.waves - 1) / def.waves * shape_job.npass;
         const int resident = ecc::resident_wgs_per_cu(3, j.dtype, ctx->construction, def.window < nbins, def.waves,
                                                       def.lds_bytes);
         for (int wgs : {2, 3, 4}) {

@@ -71,12 +71,9 @@ template <> struct ValT<DT_U8> { using T = uint8_t; };
 template <> struct ValT<DT_U16> { using T = uint16_t; };
 template <> struct ValT<DT_F32> { using T = float; };
 
-// Key (bin << kKeyShift, its LDS byte address) of one value, OR-ed with `oob`:
-// 0, or the sentinel for lanes outside the image, which makes the key the
-// sentinel.
-// IDENT: integer data with nbins == hi - lo + 1, where the bin is the level.
-template <int DT, bool IDENT>
-__device__ __forceinline__ uint32_t key_of(typename ValT<DT>::T v, const BinParams& p, uint32_t oob)
+// Bin of one value.
+template <int DT>
+__device__ __forceinline__ uint32_t bin_of(typename ValT<DT>::T v, const BinParams& p)
 {
     if constexpr (DT == DT_F32) {
         // clamp(floor(((double)x - lo) * scale), 0, nbins-1) without branches:
@@ -89,18 +86,28 @@ __device__ __forceinline__ uint32_t key_of(typename ValT<DT>::T v, const BinPara
         // the conversion saturates: negative values and -inf give 0
         uint32_t b;
         asm("v_cvt_u32_f64 %0, %1" : "=v"(b) : "v"(t));
-        return (b << kKeyShift) | oob;
+        return b;
     } else {
-        uint32_t a = (uint32_t)v;
-        a = min(max(a, p.ilo), p.ihi) - p.ilo;
-        if constexpr (IDENT) return (a << kKeyShift) | oob;
+        const uint32_t a = min(max((uint32_t)v, p.ilo), p.ihi) - p.ilo;
         // floor(a * nbins / D): a * nbins < 2^32 is exact in double, and rcp is
         // 1/D rounded up, so the product never falls below an integer it should
         // reach and stays below the next one (a < D <= 65536).
         const uint32_t n = __umul24(a, (uint32_t)p.nbins);
-        const uint32_t b = (uint32_t)__dmul_rn((double)n, p.rcp);
-        return (b << kKeyShift) | oob;
+        return (uint32_t)__dmul_rn((double)n, p.rcp);
     }
+}
+
+// Key (bin << kKeyShift, its LDS byte address) of one value, OR-ed with `oob`:
+// 0, or the sentinel for lanes outside the image, which makes the key the
+// sentinel.
+// IDENT: integer data with nbins == hi - lo + 1, where the bin is the level.
+template <int DT, bool IDENT>
+__device__ __forceinline__ uint32_t key_of(typename ValT<DT>::T v, const BinParams& p, uint32_t oob)
+{
+    if constexpr (DT != DT_F32 && IDENT)
+        return ((min(max((uint32_t)v, p.ilo), p.ihi) - p.ilo) << kKeyShift) | oob;
+    else
+        return (bin_of<DT>(v, p) << kKeyShift) | oob;
 }
 
 // Binning parameters from the min/max keys of an image (AUTO range).  Keys are
@@ -273,13 +280,14 @@ struct HistRef {
     uint32_t stride;   // words from one copy to the next
     uint32_t sm;       // the sentinel key of a one-window launch
     uint32_t copies;   // copies (a power of two; lane l adds to copy l mod copies)
+    uint32_t first;    // word of the window's first counter in a copy (0, or 1 after a spare word)
 };
 
 __device__ __forceinline__ HistRef hist_ref(int32_t* hist, int32_t bin_lo, int32_t width, uint32_t stride,
                                             uint32_t sm, uint32_t copies)
 {
     return HistRef{hist, (uint32_t)bin_lo << kKeyShift, (uint32_t)width << kKeyShift,
-                   (__lane_id() & (copies - 1u)) * stride * 4u, stride, sm, copies};
+                   (__lane_id() & (copies - 1u)) * stride * 4u, stride, sm, copies, 0u};
 }
 
 // Adds v to the counter of `key` in this lane's copy.  One window: the key is the
@@ -394,14 +402,16 @@ __device__ __forceinline__ void fused_merge_scan(int32_t* hist, const int32_t* p
 
 __device__ __forceinline__ void zero_hist(const HistRef& H, int width)
 {
+    const int words = width + (int)H.first;
     for (uint32_t c = 0; c < H.copies; ++c)
-        for (int j = threadIdx.x; j < width; j += blockDim.x) H.hist[c * H.stride + j] = 0;
+        for (int j = threadIdx.x; j < words; j += blockDim.x) H.hist[c * H.stride + j] = 0;
     __syncthreads();
 }
 
 // The workgroup's count of bin j of the window: the sum of its copies.
 __device__ __forceinline__ int32_t hist_value(const HistRef& H, int j)
 {
+    j += (int)H.first;
     int32_t t = H.hist[j];
     for (uint32_t c = 1; c < H.copies; ++c) t += H.hist[c * H.stride + j];
     return t;

@@ -46,6 +46,9 @@ constexpr int kMaxLdsBins = 4096;
 #ifndef ECC_ROWS3
 #define ECC_ROWS3 3
 #endif
+#ifndef ECC_STRIP_ROWS
+#define ECC_STRIP_ROWS 6   // 7/6 rows loaded and binned per row, 86 vector registers (5 waves per SIMD)
+#endif
 #ifndef ECC_CHUNK2
 #define ECC_CHUNK2 16
 #endif
@@ -57,12 +60,6 @@ constexpr int kMaxLdsBins = 4096;
 #endif
 #ifndef ECC_WAVES_PER_EU_2D
 #define ECC_WAVES_PER_EU_2D 5   // resident waves per SIMD the 2D kernels are compiled for
-#endif
-#ifndef ECC_MAX_WAVES_3D
-#define ECC_MAX_WAVES_3D 9   // waves per workgroup of a single 3D image (a whole row up to 567 positions)
-#endif
-#ifndef ECC_MAX_WGS_PER_CU_3D
-#define ECC_MAX_WGS_PER_CU_3D 2   // resident workgroups per CU a single 3D image launches
 #endif
 #ifndef ECC_MAX_WGS_PER_CU_2D
 #define ECC_MAX_WGS_PER_CU_2D 3   // resident workgroups per CU a single 2D image launches
@@ -116,21 +113,20 @@ inline __host__ __device__ int64_t axis_positions(int64_t n, int construction)
 {
     return n + (construction == CONS_TOP ? 1 : 0);
 }
-constexpr int kRows3 = ECC_ROWS3;      // rows per 3D brick
+constexpr int kRows3 = ECC_ROWS3;      // rows per 3D brick of a batch
+constexpr int kStripRows = ECC_STRIP_ROWS;   // rows per strip of a single 3D image
 constexpr int kChunk2 = ECC_CHUNK2;    // rows loaded together in the 2D kernel
 // Waves per workgroup of the main kernels (x-chunk = waves * 63 position columns).
 constexpr int kMaxWaves = 9;
 
-// Workgroup bricks of a single 3D image (k_ecc_3d).  Ordinary bricks are an
+// Bricks of a 3D volume of a batch (k_ecc_batch).  Ordinary bricks are an
 // x-chunk of 63 * waves position columns x kRows3 rows (a strip) x `depth`
 // planes, each wave on 63 columns of the chunk.  When the positions of a row
 // leave a narrow tail after the full chunks (t < 32 columns), a wave on the
 // tail would own t of its 63 lanes; instead the tail is packed: t + 1 lanes per
 // strip (t owning, one supplying the right neighbour), floor(64 / (t + 1))
 // strips per wave, for the strips whose rows (and the row after them) all lie
-// in the image; the few other strips' tails run as ordinary bricks.  A 512-wide
-// row then takes 8 waves of 63 columns and a packed tail of 8 instead of a
-// ninth wave with 8 columns.
+// in the image; the few other strips' tails run as ordinary bricks.
 struct Layout3 {
     int64_t nxc;        // x-chunks of the ordinary bricks of each strip (full ones)
     int64_t nyb;        // strips
@@ -169,6 +165,41 @@ inline __host__ __device__ Layout3 layout_3d(const Geom& g, int construction, in
         y.sa = y.sb = 0;
         y.per_z = y.nxc * y.nyb;
     }
+    return y;
+}
+
+// Wave tasks of a plane block of a single 3D image (k_ecc_3d).  A strip is
+// kStripRows rows; its slots are its position columns and one more (the column
+// past the last one, which only supplies the sentinel to its left neighbour).
+// The slots of the strips whose rows (and the row after them) all lie in the
+// image are numbered through, strip after strip, and cut into units of 63 (half
+// a wave: 64 lanes, the last one only supplying its left neighbour's right one),
+// so a unit may run from one strip's end into the next strip and no lane idles on
+// row tails or narrow rows: a 512-wide row takes 8.14 units of 63.  A wave task is
+// two consecutive units.  The strips that reach over the image's first or last
+// rows are cut each for itself.
+struct Strips {
+    int64_t slots;        // per strip
+    int64_t sa, sb;       // strips [sa, sb) are whole
+    int64_t pairs_full;   // wave tasks over the whole strips
+    int64_t pairs_edge;   // wave tasks of each other strip
+    int64_t tasks;        // wave tasks per plane block
+};
+inline __host__ __device__ Strips strips_3d(const Geom& g, int construction)
+{
+    Strips y = {};
+    const int64_t org = construction == CONS_TOP ? -1 : 0;
+    const int64_t nyb = (axis_positions(g.n1, construction) + kStripRows - 1) / kStripRows;
+    y.slots = axis_positions(g.n2, construction) + 1;
+    // strip s reads rows org + R s .. org + R s + R (the last one completes pairs)
+    y.sa = org < 0 ? 1 : 0;
+    y.sb = g.n1 - kStripRows - 1 - org >= 0 ? (g.n1 - kStripRows - 1 - org) / kStripRows + 1 : 0;
+    if (y.sb > nyb) y.sb = nyb;
+    if (y.sb <= y.sa) y.sa = y.sb = 0;
+    const int64_t per = 2 * kLaneCols;
+    y.pairs_full = ((y.sb - y.sa) * y.slots + per - 1) / per;
+    y.pairs_edge = (y.slots + per - 1) / per;
+    y.tasks = y.pairs_full + (nyb - (y.sb - y.sa)) * y.pairs_edge;
     return y;
 }
 
@@ -322,7 +353,7 @@ hipError_t launch_merge(const int32_t* partials, int rows, int32_t width, int32_
 // Folds `blocks` min/max key pairs into the running pair acc (first: start it).
 hipError_t launch_mm_fold(const uint32_t* mm, int blocks, uint32_t* acc, bool first, hipStream_t s);
 
-// Workgroup bricks of an image for a launch shape.
+// Workgroup bricks of an image (a 3D one: of one volume) for a launch shape.
 int64_t wg_bricks(int ndim, int construction, const Geom& g, int waves, int64_t depth);
 // Workgroups of the main kernel variant (of `waves` waves, lds_bytes of dynamic
 // LDS) that fit on one CU.

@@ -8,7 +8,7 @@
 
 #include <hip/hip_ext.h>
 
-#include "ecc_device.h"
+#include "ecc_march.h"
 
 namespace ecc {
 
@@ -16,38 +16,26 @@ namespace {
 
 using namespace dev;
 
-// 3D images.  A workgroup brick is a contiguous x-chunk (the workgroup's waves
-// side by side, each 64 lanes wide with 63 owned) x kRows3 rows x L.depth planes.
-// All waves of a workgroup read the same rows at about the same time, so every
-// plane step of a workgroup reads whole row segments of memory.
+// 3D images.  A workgroup brick is as many consecutive wave tasks (Strips: 2 x 63
+// slots of kStripRows rows each) as it has waves x L.depth planes.  Its waves read
+// neighbouring parts of the same rows at about the same time.
 template <int DT, int CONS, bool WIN, bool PAIR>
 __global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(ECC_WAVES_PER_EU_3D))) void k_ecc_3d(EccLaunch L)
 {
     extern __shared__ __align__(16) int32_t hist[];
     const BinParams P = load_params<DT>(L);
-    const HistRef H = hist_ref(hist, L.bin_lo, L.width, L.hist_stride, L.sentinel, L.hist_copies);
+    const HistRef H = march_hist<WIN>(hist, L.width, L.hist_stride, L.hist_copies);
     zero_hist(H, L.width);
-    const int waves = (int)(blockDim.x >> 6);
-    const int64_t chunk = (int64_t)waves * kLaneCols;
-    // per plane block: the ordinary bricks (x-chunk fastest), then the packed
-    // tail bricks, then the tails of the strips not packed (Layout3)
-    const Layout3 Y = layout_3d(L.g, CONS, waves);
-    const uint32_t nxc = (uint32_t)Y.nxc, nyb = (uint32_t)Y.nyb, per_z = (uint32_t)Y.per_z;
-    const uint32_t main = nxc * nyb, npk = (uint32_t)Y.npk, sa = (uint32_t)Y.sa, sb = (uint32_t)Y.sb;
-    const uint32_t nzb = (uint32_t)((L.z_own + L.depth - 1) / L.depth);
-    const uint32_t nbricks = per_z * nzb;
+    const uint32_t waves = blockDim.x >> 6;
+    const Strips Y = strips_3d(L.g, CONS);
+    const uint32_t per_z = ((uint32_t)Y.tasks + waves - 1u) / waves;
+    const uint32_t nbricks = per_z * (uint32_t)((L.z_own + L.depth - 1) / L.depth);
     for (uint32_t brick = blockIdx.x; brick < nbricks; brick += gridDim.x) {
-        const uint32_t zb = brick / per_z, r = brick - zb * per_z;
-        Brick3 B;
-        if (r < main) {
-            B = chunk_brick_3d<DT, CONS, WIN>(L, H, chunk, r % nxc, r / nxc, zb, wave_id());
-        } else if (r - main < npk) {
-            B = tail_brick_3d<DT, CONS, WIN>(L, H, Y, waves, r - main, zb, wave_id());
-        } else {
-            const uint32_t e = r - main - npk;   // the strips before sa, then those from sb on
-            B = chunk_brick_3d<DT, CONS, WIN>(L, H, chunk, nxc, e < sa ? e : sb + (e - sa), zb, wave_id());
-        }
-        run_brick3<DT, CONS, WIN, PAIR>(L, P, H, B);
+        const uint32_t zb = uniform_u32(brick / per_z), r = uniform_u32(brick - zb * per_z);
+        const uint32_t z0 = zb * (uint32_t)L.depth;
+        const uint32_t ze = (int64_t)z0 + L.depth < L.z_own ? z0 + (uint32_t)L.depth : (uint32_t)L.z_own;
+        const Task3 K = strip_task<DT, CONS, kStripRows>(L, Y, H.sm, r * waves + (uint32_t)wave_id());
+        run_march_3d<DT, CONS, kStripRows, WIN, PAIR>(L, P, H, K, z0, ze);
     }
     flush_hist(H, L.partials + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * (size_t)L.width, L.width, L.flush_add != 0, L.flush_sign);
     if (L.fused) fused_merge_scan(hist, L.partials, L.width, L.out, L.counter + 1);
@@ -81,7 +69,7 @@ int64_t wg_bricks(int ndim, int construction, const Geom& g, int waves, int64_t 
     const int64_t chunk = (int64_t)waves * kLaneCols;
     const int64_t nxc = (axis_positions(g.n2, construction) + chunk - 1) / chunk;
     if (ndim == 2) return nxc * ((g.n1 + depth - 1) / depth);
-    return layout_3d(g, construction, waves).per_z * ((g.n0 + depth - 1) / depth);
+    return (strips_3d(g, construction).tasks + waves - 1) / waves * ((g.n0 + depth - 1) / depth);
 }
 
 template <class K>

@@ -1,0 +1,66 @@
+"""GPU parity of the packed marching kernels at the sizes where their layout can
+go wrong, against the oracle, bit for bit.
+
+A wave takes two units of 63 position columns; the columns of consecutive strips
+(6 rows each) are numbered through, so a unit may end inside a row and go on in
+the next strip.  The sizes put the end of a row, of a strip and of a unit on and
+next to each other, with images smaller than a unit or a strip, every dtype,
+values that tie, and histograms of one bin, one window and several windows.
+"""
+import sys
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def say(*args):
+    print(*args, flush=True, file=sys.stderr)
+
+
+def to_dev(a):
+    if a.dtype == np.uint16:
+        return torch.from_numpy(np.ascontiguousarray(a).view(np.int16)).cuda()
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda()
+
+
+def draw_image(rng, shape, kind):
+    if kind == "u8":
+        return rng.integers(0, 7, size=shape).astype(np.uint8), 7, (0, 6)
+    if kind == "u16":
+        return rng.integers(0, 65536, size=shape).astype(np.uint16), 4096, "auto"
+    if kind == "u16wide":   # more bins than one window
+        return rng.integers(0, 65536, size=shape).astype(np.uint16), 20000, (0, 65535)
+    img = rng.standard_normal(shape).astype(np.float32)
+    img[rng.random(shape) < 0.02] = np.nan
+    img[rng.random(shape) < 0.02] = np.inf
+    img[rng.random(shape) < 0.02] = -np.inf
+    return img, (1 if kind == "f32one" else 333), (-1.5, 1.25)
+
+
+SHAPES_3D = [(1, 1, 1), (2, 6, 62), (3, 7, 63), (2, 5, 64), (4, 12, 125), (3, 13, 126), (2, 14, 127), (5, 31, 3),
+             (3, 40, 1), (2, 25, 41), (9, 8, 189)]
+
+
+@pytest.mark.parametrize("cons", ["vertex", "top"])
+@pytest.mark.parametrize("kind", ["u8", "u16", "u16wide", "f32", "f32one"])
+def test_strips_and_units_3d(oracle_mod, cons, kind):
+    from paper_2203_09087_amd import ecc
+    rng = np.random.default_rng(4100)
+    ctx = ecc.Context(0, cons)
+    try:
+        for shape in SHAPES_3D:
+            img, nbins, r = draw_image(rng, shape, kind)
+            say(f"case: {cons} {kind} {shape} nbins={nbins}")
+            dev = to_dev(img)
+            want = oracle_mod.ecc(img, nbins, cons, value_range=r, threads=8)
+            for depth in (0, 1, 2, 3):
+                ctx.set_launch_shape(dev, nbins, depth=depth)
+                got = ctx.compute(dev, nbins, value_range=r)
+                torch.cuda.synchronize()
+                assert np.array_equal(got.cpu().numpy(), want), (cons, kind, shape, depth)
+    finally:
+        ctx.close()
