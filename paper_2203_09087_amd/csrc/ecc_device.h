@@ -166,6 +166,43 @@ __device__ __forceinline__ void mm_take(typename ValT<DT>::T v, uint32_t& lo, ui
     }
 }
 
+// Folds elements [b, e) of img into running min/max keys, thread tid of nthreads:
+// 16-byte loads, U in flight, the unaligned head and the tail element by element.
+template <int DT, int U>
+__device__ __forceinline__ void mm_range(const typename ValT<DT>::T* __restrict__ img, int64_t b, int64_t e,
+                                         int64_t tid, int64_t nthreads, uint32_t& lo, uint32_t& hi)
+{
+    using T = typename ValT<DT>::T;
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    constexpr int PER = 16 / (int)sizeof(T);
+    const int64_t n = e - b;
+    img += b;
+    int64_t head = (int64_t)(((16 - ((uintptr_t)img & 15)) & 15) / sizeof(T));
+    if (head > n) head = n;
+    for (int64_t i = tid; i < head; i += nthreads) mm_take<DT>(img[i], lo, hi);
+    const int64_t nvec = (n - head) / PER;
+    const u32x4* __restrict__ vec = (const u32x4*)(img + head);
+    int64_t i = tid;
+    for (; U > 1 && i + (U - 1) * nthreads < nvec; i += U * nthreads) {
+        u32x4 w[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) w[u] = __builtin_nontemporal_load(vec + i + u * nthreads);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const T* x = (const T*)&w[u];
+#pragma unroll
+            for (int k = 0; k < PER; ++k) mm_take<DT>(x[k], lo, hi);
+        }
+    }
+    for (; i < nvec; i += nthreads) {
+        const u32x4 w = __builtin_nontemporal_load(vec + i);
+        const T* x = (const T*)&w;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) mm_take<DT>(x[k], lo, hi);
+    }
+    for (int64_t j = head + nvec * PER + tid; j < n; j += nthreads) mm_take<DT>(img[j], lo, hi);
+}
+
 // Block-wide min/max of (lo, hi); the result is valid in thread 0.
 __device__ __forceinline__ void block_minmax(uint32_t& lo, uint32_t& hi)
 {
