@@ -303,78 +303,90 @@ struct Sizes {
     int waves;
     int64_t depth;
     int32_t window;
-    uint32_t hist_stride, hist_copies, sentinel, lds_bytes;   // LDS layout of the histogram kernel
+    uint32_t hist_stride, hist_copies, lds_bytes;   // LDS layout of the histogram kernel
     size_t off_params, off_counters, off_mm, off_level2, off_partials, total;
 };
 
 // Launch shape of the main kernel for one image:
-//  - 3D: shape_3d;
-//  - 2D: a workgroup's waves cover a contiguous x-chunk of 63 * waves position
-//    columns, the whole row when it has at most 9 * 63 positions, else chunks of
-//    8 * 63; `depth` rows per workgroup brick, chosen so that there are about two
-//    bricks per CU;
+//  - waves, depth and workgroups: pick_shape;
 //  - grid: at least enough that no workgroup histogram can reach 2^31 (every
 //    voxel position adds at most 8 in absolute value: four type counts of at
 //    most 1, and at a brick's last plane four more).
 using TuneKey = std::tuple<int, int, int, int, int64_t, int64_t, int64_t>;
 
-// Constants of shape_3d's model: planes' worth of work a brick starts with (its
-// places, first plane and last counts), microseconds of a plane step per wave on a
-// SIMD (about 290 vector instructions at 4 cycles), and of a workgroup row's bin
-// through the merge (8 bytes written and read).
-constexpr double kStartPlanes = 2.5, kPlaneUs = 0.5, kRowUs = 2e-6;
+// Constants of pick_shape's model: planes' (rows') worth of work a brick starts
+// with (its places, first plane and last counts), microseconds of a plane (row)
+// step per wave on a SIMD (about 290 and 30 vector instructions at 4 cycles), and
+// of a workgroup row's bin through the merge (8 bytes written and read).
+constexpr double kStartPlanes = 2.5, kPlaneUs = 0.5, kStartRows = 12, kRowUs = 0.05, kBinUs = 2e-6;
 
 TuneKey tune_key(const ecc_ctx* ctx, const Job& j, int32_t nbins)
 {
     return TuneKey{j.ndim, j.dtype, ctx->construction, nbins > ecc::kMaxLdsBins ? 1 : 0, j.g.n0, j.g.n1, j.g.n2};
 }
 
-// Launch shape of a 3D image (or of the npass hyperplanes of a 4D part that run
-// as one launch): waves per workgroup, workgroups, and planes per brick, from a
-// model of its time.  Every resident wave walks the same number of bricks but
-// for the last round, so what a shape loses is that round's idle workgroups, the
-// planes a brick starts up with, and the issue slots that few waves per SIMD
+// Launch shape of an image (or of the npass hyperplanes of a 4D part that run as
+// one launch): waves per workgroup, workgroups, and planes (2D: rows) per brick,
+// from a model of its time.  Every resident wave walks the same number of bricks
+// but for the last round, so what a shape loses is that round's idle workgroups,
+// the planes a brick starts up with, and the issue slots that few waves per SIMD
 // leave empty; more workgroups cost more rows to merge.  For each wave and
 // workgroup count the candidates are the depths whose bricks fill one, two or
 // three rounds exactly.  Measured on the 512^3 float32 field: 66 bricks of 8 waves
 // in 16 plane blocks over 512 workgroups (2.06 rounds) 148 us, a depth that fills
 // the rounds 127 us.  Fields that `tuned` sets are kept.
 template <class Resident>
-void shape_3d(const ecc_ctx* ctx, const Job& j, const ecc_launch_shape* tuned, Sizes& s, Resident&& resident)
+void pick_shape(const ecc_ctx* ctx, const Job& j, const ecc_launch_shape* tuned, Sizes& s, Resident&& resident)
 {
-    const double tasks = (double)ecc::strips_3d(j.g, ctx->construction).tasks, n0 = (double)j.g.n0;
+    const bool flat = j.ndim == 2;   // 2D: rows are the marching axis, one block of rows like a plane block
+    // the last depths: 2D blocks are whole groups of kChunk2 rows
+    const double step = flat ? ecc::kChunk2 : 1, dmin = flat ? ecc::kChunk2 : 2, dmax = flat ? 512 : 256;
+    const double start = flat ? kStartRows : kStartPlanes, unit_us = flat ? kRowUs : kPlaneUs;
+    const double length = flat ? (double)j.g.n1 : (double)j.g.n0;
+    // wave tasks per block (2D: units of 63 columns, not yet rounded to pairs)
+    const double tasks = flat ? (double)(ecc::axis_positions(j.g.n2, ctx->construction) + 1) / (2.0 * ecc::kLaneCols)
+                              : (double)ecc::units_3d(j.g, ctx->construction).tasks;
     const double npass = (double)j.npass, cus = (double)ctx->cu_count;
-    // share of the vector issue slots used by 1, 2, .. 8 waves per SIMD
+    // share of the vector issue slots used by 0, 1, .. 8 waves per SIMD
     static const double eff[9] = {0.2, 0.40, 0.66, 0.80, 0.87, 0.91, 0.94, 0.96, 0.97};
-    const int forced_w = tuned && tuned->waves > 0 ? (int)std::min<double>(std::min<int>(tuned->waves, ecc::kMaxWaves), tasks) : 0;
+    const double most = flat ? std::ceil(tasks * std::ceil(length / dmin)) : tasks;   // waves with work
+    const int forced_w =
+        tuned && tuned->waves > 0 ? (int)std::min<double>(std::min<int>(tuned->waves, ecc::kMaxWaves), most) : 0;
+    double forced_d = 0.0;
+    if (tuned && tuned->depth > 0)
+        forced_d = flat ? (double)((std::min<int64_t>(tuned->depth, 4096) + ecc::kChunk2 - 1) / ecc::kChunk2 * ecc::kChunk2)
+                        : (double)std::min<int64_t>(tuned->depth, 256);
     double best = HUGE_VAL;
     s.waves = 0;
     for (int w : {8, 4, 2, 1}) {
         if (forced_w) w = forced_w;
-        else if (w > tasks || (w < 4 && s.waves > 0)) continue;
-        const double per_z = std::ceil(tasks / w);   // bricks of a plane block
+        else if (w > most || (w < 4 && s.waves > 0)) continue;
+        // bricks of a block of rows (2D, fractional: blocks share bricks) or planes
+        const double per_block = flat ? tasks / w : std::ceil(tasks / w);
         const int rmax = resident(w);
         int r0 = 1, r1 = std::min(rmax, 6);
         if (tuned && tuned->wgs_per_cu > 0) r0 = r1 = std::min(tuned->wgs_per_cu, rmax);
         for (int r = r0; r <= r1; ++r) {
             const double gx = std::max(1.0, std::floor(cus * r / npass));   // workgroups per pass
             for (int k = 1; k <= 3; ++k) {
-                double d;
-                if (tuned && tuned->depth > 0) d = (double)std::min<int64_t>(tuned->depth, 256);
-                else d = std::min(std::max(std::ceil(n0 / std::max(1.0, std::floor(gx * k / per_z))), 2.0), 256.0);
-                const double bricks = per_z * std::ceil(n0 / d);
+                double d = forced_d;
+                if (d == 0.0) {
+                    d = std::ceil(length / std::max(1.0, std::floor(gx * k / per_block)) / step) * step;
+                    d = std::min(std::max(d, dmin), dmax);
+                }
+                const double bricks = std::ceil(per_block * std::ceil(length / d));
                 const double g = std::min(gx, bricks), rounds = std::ceil(bricks / g);
                 const double busy = std::ceil(g * npass / cus) * w / 4.0;   // waves per SIMD
                 const int n = (int)std::min(8.0, std::ceil(busy));
-                const double us = rounds * (d + kStartPlanes) * busy / eff[n] * kPlaneUs +
-                                  g * npass * (double)s.window * kRowUs;
+                const double us = rounds * (std::min(d, length) + start) * busy / eff[n] * unit_us +
+                                  g * npass * (double)s.window * kBinUs;
                 if (us < best) {
                     best = us;
                     s.waves = w;
                     s.depth = (int64_t)d;
                     s.grid = (int)std::min(gx * npass, cus * r);
                 }
-                if (tuned && tuned->depth > 0) break;
+                if (forced_d > 0.0) break;
             }
         }
         if (forced_w) break;
@@ -392,8 +404,6 @@ Sizes plan_sizes(const ecc_ctx* ctx, const Job& j, int32_t nbins, const ecc_laun
         if (it != ctx->tuned.end()) tuned = &it->second;
     }
     const int cons = ctx->construction;
-    const int64_t xpos = ecc::axis_positions(j.g.n2, cons);
-    const int64_t cols = (xpos + ecc::kLaneCols - 1) / ecc::kLaneCols;
     // bins per LDS pass: all of them up to kMaxLdsBins, or fewer when tuned so
     s.window = std::min<int32_t>(nbins, ecc::kMaxLdsBins);
     if (tuned && tuned->window > 0) s.window = std::min<int32_t>(s.window, tuned->window);
@@ -401,28 +411,11 @@ Sizes plan_sizes(const ecc_ctx* ctx, const Job& j, int32_t nbins, const ecc_laun
     s.hist_stride = ecc::lds_stride(s.window);
     s.hist_copies = ecc::hist_copies(s.window);
     if (tuned && tuned->copies > 0) s.hist_copies = (uint32_t)tuned->copies;
-    s.sentinel = ecc::lds_sentinel(nbins);
-    s.lds_bytes = 4u * (j.ndim == 3 ? s.hist_copies * s.hist_stride
-                                    : ecc::lds_words(s.window, windowed, s.sentinel, s.hist_copies));
+    s.lds_bytes = 4u * s.hist_copies * s.hist_stride;
     auto resident = [&](int waves) {
         return ecc::resident_wgs_per_cu(j.ndim, j.dtype, cons, windowed, waves, s.lds_bytes);
     };
-    if (j.ndim == 3) {
-        shape_3d(ctx, j, tuned, s, resident);
-    } else {
-        s.waves = (int)(cols <= ecc::kMaxWaves ? cols : 8);
-        if (tuned && tuned->waves > 0) s.waves = (int)std::min<int64_t>(std::min<int64_t>(tuned->waves, ecc::kMaxWaves), cols);
-        const int64_t target = 2 * (int64_t)ctx->cu_count;
-        const int64_t chunk = ecc::kLaneCols * (int64_t)s.waves;
-        const int64_t nxc = (xpos + chunk - 1) / chunk;
-        int64_t d = (j.g.n1 * nxc + target - 1) / target;
-        d = std::min<int64_t>(std::max<int64_t>(d, ecc::kChunk2), 512);
-        if (tuned && tuned->depth > 0) d = std::min<int64_t>(tuned->depth, 4096);
-        s.depth = (d + ecc::kChunk2 - 1) / ecc::kChunk2 * ecc::kChunk2;
-        int want = ECC_MAX_WGS_PER_CU_2D;
-        if (tuned && tuned->wgs_per_cu > 0) want = tuned->wgs_per_cu;
-        s.grid = ctx->cu_count * std::min(want, resident(s.waves));
-    }
+    pick_shape(ctx, j, tuned, s, resident);
     const int64_t bricks = ecc::wg_bricks(j.ndim, cons, j.g, s.waves, s.depth) * j.npass;
     int64_t grid = std::min<int64_t>(bricks, s.grid);
     grid = std::max<int64_t>(grid, std::min<int64_t>(bricks, (j.nvox >> 27) + 1));
@@ -546,6 +539,7 @@ ecc_status enqueue_hist(ecc_ctx* ctx, char* base, const Job& j, int32_t nbins, h
     L.grid = sz.grid;
     L.waves = sz.waves;
     L.depth = sz.depth;
+    L.units = j.ndim == 2 ? ecc::units_2d(j.g, ctx->construction, sz.depth) : ecc::units_3d(j.g, ctx->construction);
     L.z_own = z_own;
     L.z_base = z_base;
     L.n0_global = n0_global;
@@ -559,7 +553,6 @@ ecc_status enqueue_hist(ecc_ctx* ctx, char* base, const Job& j, int32_t nbins, h
     L.fused = 0;
     L.hist_stride = sz.hist_stride;
     L.hist_copies = sz.hist_copies;
-    L.sentinel = sz.sentinel;
     L.lds_bytes = sz.lds_bytes;
     auto launch_l = [&](hipEvent_t t0, hipEvent_t t1) { return ecc::launch_ecc(L, stream, t0, t1); };
     hipError_t e;
@@ -1710,10 +1703,10 @@ ecc_status ecc_autotune(ecc_ctx* ctx, const ecc_image* img, int32_t nbins, int32
     auto run = [&](const ecc_launch_shape* c) {
         return j.ndim >= 4 ? enqueue_nd(ctx, j, nbins, stream, false, c) : enqueue_one(ctx, j, nbins, stream, c);
     };
-    // waves a workgroup can use: 3D: the wave tasks of a plane block; 2D: a row's
+    // waves a workgroup can use: 3D: the wave tasks of a plane block; 2D: the image's
     const int64_t cols = shape_job.ndim == 3
-                             ? ecc::strips_3d(shape_job.g, ctx->construction).tasks
-                             : (ecc::axis_positions(j.g.n2, ctx->construction) + ecc::kLaneCols - 1) / ecc::kLaneCols;
+                             ? (int64_t)ecc::units_3d(shape_job.g, ctx->construction).tasks
+                             : (int64_t)ecc::units_2d(j.g, ctx->construction, ecc::kChunk2).tasks;
     std::vector<ecc_launch_shape> cand;
     auto add = [&](int waves, int64_t depth, int wgs, int32_t window = 0, int32_t copies = 0) {
         ecc_launch_shape c = {};
@@ -1728,8 +1721,7 @@ ecc_status ecc_autotune(ecc_ctx* ctx, const ecc_image* img, int32_t nbins, int32
                 return;
         cand.push_back(c);
     };
-    const int def_wgs = j.ndim == 2 ? ECC_MAX_WGS_PER_CU_2D
-                                    : std::max(1, (def.grid + ctx->cu_count - 1) / ctx->cu_count);
+    const int def_wgs = std::max(1, (def.grid + ctx->cu_count - 1) / ctx->cu_count);
     add(def.waves, def.depth, def_wgs);
     for (int wgs : {1, 2, 3, 4})
         for (int64_t dm : {1, 2, 4}) {

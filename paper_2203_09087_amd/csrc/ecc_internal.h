@@ -61,9 +61,6 @@ constexpr int kMaxLdsBins = 4096;
 #ifndef ECC_WAVES_PER_EU_2D
 #define ECC_WAVES_PER_EU_2D 5   // resident waves per SIMD the 2D kernels are compiled for
 #endif
-#ifndef ECC_MAX_WGS_PER_CU_2D
-#define ECC_MAX_WGS_PER_CU_2D 3   // resident workgroups per CU a single 2D image launches
-#endif
 // A key is 4 * bin: the LDS byte address of its counter.
 constexpr int kKeyShift = 2;
 // A workgroup histogram is kept in several copies, lane l of every wave adding to
@@ -168,39 +165,54 @@ inline __host__ __device__ Layout3 layout_3d(const Geom& g, int construction, in
     return y;
 }
 
-// Wave tasks of a plane block of a single 3D image (k_ecc_3d).  A strip is
-// kStripRows rows; its slots are its position columns and one more (the column
-// past the last one, which only supplies the sentinel to its left neighbour).
-// The slots of the strips whose rows (and the row after them) all lie in the
-// image are numbered through, strip after strip, and cut into units of 63 (half
-// a wave: 64 lanes, the last one only supplying its left neighbour's right one),
-// so a unit may run from one strip's end into the next strip and no lane idles on
-// row tails or narrow rows: a 512-wide row takes 8.14 units of 63.  A wave task is
-// two consecutive units.  The strips that reach over the image's first or last
-// rows are cut each for itself.
-struct Strips {
-    int64_t slots;        // per strip
-    int64_t sa, sb;       // strips [sa, sb) are whole
-    int64_t pairs_full;   // wave tasks over the whole strips
-    int64_t pairs_edge;   // wave tasks of each other strip
-    int64_t tasks;        // wave tasks per plane block
+// How the waves divide an image (computed on the host: the 64-bit divisions cost a
+// small image more than its counting).
+//
+// 3D, per plane block: a strip is kStripRows rows; its slots are its position
+// columns and one more (the column past the last one, which only supplies the
+// sentinel to its left neighbour).  The slots of the strips whose rows (and the
+// row after them) all lie in the image are numbered through, strip after strip,
+// and cut into units of 63 (half a wave: 64 lanes, the last one only supplying
+// its left neighbour's right one), so a unit may run from one strip's end into the
+// next strip and no lane idles on row tails or narrow rows: a 512-wide row takes
+// 8.14 units of 63.  A wave task is two consecutive units.  The strips that reach
+// over the image's first or last rows are cut each for itself.
+//
+// 2D: the same with blocks of `depth` rows (a multiple of 8) in place of strips;
+// a last block of fewer rows is cut for itself.  Rows too long for 32-bit offsets
+// from one block into the next ones: every block for itself.
+struct Units {
+    uint32_t slots;        // per strip (block)
+    uint32_t sa, sb;       // strips (blocks) [sa, sb) are numbered through
+    uint32_t pairs_full;   // wave tasks over them
+    uint32_t pairs_edge;   // wave tasks of each other strip (block)
+    uint32_t tasks;        // wave tasks per plane block (2D: of the image)
 };
-inline __host__ __device__ Strips strips_3d(const Geom& g, int construction)
+inline Units units_3d(const Geom& g, int construction)
 {
-    Strips y = {};
     const int64_t org = construction == CONS_TOP ? -1 : 0;
     const int64_t nyb = (axis_positions(g.n1, construction) + kStripRows - 1) / kStripRows;
-    y.slots = axis_positions(g.n2, construction) + 1;
+    const int64_t slots = axis_positions(g.n2, construction) + 1, per = 2 * kLaneCols;
     // strip s reads rows org + R s .. org + R s + R (the last one completes pairs)
-    y.sa = org < 0 ? 1 : 0;
-    y.sb = g.n1 - kStripRows - 1 - org >= 0 ? (g.n1 - kStripRows - 1 - org) / kStripRows + 1 : 0;
-    if (y.sb > nyb) y.sb = nyb;
-    if (y.sb <= y.sa) y.sa = y.sb = 0;
-    const int64_t per = 2 * kLaneCols;
-    y.pairs_full = ((y.sb - y.sa) * y.slots + per - 1) / per;
-    y.pairs_edge = (y.slots + per - 1) / per;
-    y.tasks = y.pairs_full + (nyb - (y.sb - y.sa)) * y.pairs_edge;
-    return y;
+    int64_t sa = org < 0 ? 1 : 0;
+    int64_t sb = g.n1 - kStripRows - 1 - org >= 0 ? (g.n1 - kStripRows - 1 - org) / kStripRows + 1 : 0;
+    if (sb > nyb) sb = nyb;
+    if (sb <= sa) sa = sb = 0;
+    const int64_t full = ((sb - sa) * slots + per - 1) / per, edge = (slots + per - 1) / per;
+    return Units{(uint32_t)slots, (uint32_t)sa, (uint32_t)sb, (uint32_t)full, (uint32_t)edge,
+                 (uint32_t)(full + (nyb - (sb - sa)) * edge)};
+}
+inline Units units_2d(const Geom& g, int construction, int64_t depth)
+{
+    const int64_t nyb = (g.n1 + depth - 1) / depth;
+    const int64_t slots = axis_positions(g.n2, construction) + 1, per = 2 * kLaneCols;
+    // a lane's rows reach up to `span` blocks past the wave's first row
+    const int64_t span = (slots + per) / slots + 2;
+    const bool flat = depth % 8 == 0 && (double)span * (double)depth * (double)(g.n2 * 4) < 2147483648.0;
+    const int64_t whole = flat ? g.n1 / depth : 0;
+    const int64_t full = (whole * slots + per - 1) / per, edge = (slots + per - 1) / per;
+    return Units{(uint32_t)slots, 0u, (uint32_t)whole, (uint32_t)full, (uint32_t)edge,
+                 (uint32_t)(full + (nyb - whole) * edge)};
 }
 
 struct EccLaunch {
@@ -208,6 +220,7 @@ struct EccLaunch {
     const void* data2;             // non-null (3D): count the elementwise max (min) of data and data2
     int ndim, dtype, construction;
     Geom g;
+    Units units;                   // units_3d or units_2d of g
     const BinParams* params_dev;   // non-null: read the parameters from device memory
     BinParams params;              // used when params_dev is null
     int32_t bin_lo, width;
@@ -233,8 +246,7 @@ struct EccLaunch {
     int32_t fused;                 // one window, few rows: the last workgroup merges and scans into out
     uint32_t hist_stride;          // LDS words between the histogram copies (lds_stride(width))
     uint32_t hist_copies;          // copies of the histogram (a power of two up to kMaxHistCopies)
-    uint32_t sentinel;             // one-window sentinel key (lds_sentinel(nbins))
-    uint32_t lds_bytes;            // dynamic LDS of the launch (lds_words * 4)
+    uint32_t lds_bytes;            // dynamic LDS of the launch
 };
 // Partial-row words (grid x window) up to which the histogram kernel merges its
 // own rows (fused_merge_scan) instead of launching the two merge kernels.

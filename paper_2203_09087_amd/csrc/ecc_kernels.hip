@@ -16,7 +16,7 @@ namespace {
 
 using namespace dev;
 
-// 3D images.  A workgroup brick is as many consecutive wave tasks (Strips: 2 x 63
+// 3D images.  A workgroup brick is as many consecutive wave tasks (Units: 2 x 63
 // slots of kStripRows rows each) as it has waves x L.depth planes.  Its waves read
 // neighbouring parts of the same rows at about the same time.
 template <int DT, int CONS, bool WIN, bool PAIR>
@@ -27,34 +27,33 @@ __global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(
     const HistRef H = march_hist<WIN>(hist, L.width, L.hist_stride, L.hist_copies);
     zero_hist(H, L.width);
     const uint32_t waves = blockDim.x >> 6;
-    const Strips Y = strips_3d(L.g, CONS);
-    const uint32_t per_z = ((uint32_t)Y.tasks + waves - 1u) / waves;
+    const uint32_t per_z = (L.units.tasks + waves - 1u) / waves;
     const uint32_t nbricks = per_z * (uint32_t)((L.z_own + L.depth - 1) / L.depth);
     for (uint32_t brick = blockIdx.x; brick < nbricks; brick += gridDim.x) {
         const uint32_t zb = uniform_u32(brick / per_z), r = uniform_u32(brick - zb * per_z);
         const uint32_t z0 = zb * (uint32_t)L.depth;
         const uint32_t ze = (int64_t)z0 + L.depth < L.z_own ? z0 + (uint32_t)L.depth : (uint32_t)L.z_own;
-        const Task3 K = strip_task<DT, CONS, kStripRows>(L, Y, H.sm, r * waves + (uint32_t)wave_id());
+        const Task3 K = strip_task<DT, CONS, kStripRows>(L.g, L.units, H.sm, r * waves + (uint32_t)wave_id());
         run_march_3d<DT, CONS, kStripRows, WIN, PAIR>(L, P, H, K, z0, ze);
     }
     flush_hist(H, L.partials + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * (size_t)L.width, L.width, L.flush_add != 0, L.flush_sign);
     if (L.fused) fused_merge_scan(hist, L.partials, L.width, L.out, L.counter + 1);
 }
 
-// 2D images.  A workgroup brick is a contiguous x-chunk x L.depth rows.
+// 2D images.  A workgroup brick is as many consecutive wave tasks (Units: 2 x 63
+// slots x L.depth rows each) as it has waves.
 template <int DT, int CONS, bool WIN>
 __global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(ECC_WAVES_PER_EU_2D))) void k_ecc_2d(EccLaunch L)
 {
     extern __shared__ __align__(16) int32_t hist[];
-    const BinParams P = L.params_dev ? *L.params_dev : L.params;
-    const HistRef H = hist_ref(hist, L.bin_lo, L.width, L.hist_stride, L.sentinel, L.hist_copies);
+    const BinParams P = load_params<DT>(L);
+    const HistRef H = march_hist<WIN>(hist, L.width, L.hist_stride, L.hist_copies);
     zero_hist(H, L.width);
-    const int64_t chunk = (int64_t)(blockDim.x >> 6) * kLaneCols;
-    const uint32_t nxc = (uint32_t)((axis_positions(L.g.n2, CONS) + chunk - 1) / chunk);
-    const uint32_t nyb = (uint32_t)((L.g.n1 + L.depth - 1) / L.depth);
-    const uint32_t nbricks = nxc * nyb;
-    for (uint32_t brick = blockIdx.x; brick < nbricks; brick += gridDim.x)
-        run_brick_2d<DT, CONS, WIN>(L, P, H, chunk, brick % nxc, brick / nxc, wave_id());
+    const uint32_t waves = blockDim.x >> 6;
+    const WinKeys W = win_keys<WIN>(L);
+    for (uint32_t task = blockIdx.x * waves + (uint32_t)wave_id(); task < L.units.tasks; task += gridDim.x * waves)
+        run_march_2d<DT, CONS, WIN>(L.data, L.g, L.depth, P, W, H,
+                                    block_task<DT, CONS>(L.g, L.units, L.depth, H.sm, task));
     flush_hist(H, L.partials + (size_t)blockIdx.x * (size_t)L.width, L.width, L.flush_add != 0, L.flush_sign);
     if (L.fused) fused_merge_scan(hist, L.partials, L.width, L.out, L.counter + 1);
 }
@@ -66,10 +65,8 @@ __global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(
 
 int64_t wg_bricks(int ndim, int construction, const Geom& g, int waves, int64_t depth)
 {
-    const int64_t chunk = (int64_t)waves * kLaneCols;
-    const int64_t nxc = (axis_positions(g.n2, construction) + chunk - 1) / chunk;
-    if (ndim == 2) return nxc * ((g.n1 + depth - 1) / depth);
-    return (strips_3d(g, construction).tasks + waves - 1) / waves * ((g.n0 + depth - 1) / depth);
+    if (ndim == 2) return ((int64_t)units_2d(g, construction, depth).tasks + waves - 1) / waves;
+    return ((int64_t)units_3d(g, construction).tasks + waves - 1) / waves * ((g.n0 + depth - 1) / depth);
 }
 
 template <class K>

@@ -160,11 +160,18 @@ __device__ __forceinline__ uint32_t pair_key(typename ValT<DT>::T a, typename Va
                                              const WinKeys& w, uint32_t oob)
 {
     uint32_t k;
-    if constexpr (DT != DT_F32 && IDENT) {
+    if constexpr (DT == DT_F32) {
+        k = bin_of<DT>(a, p) | (bin_of<DT>(b, p) << 16);
+    } else {
         k = (uint32_t)a | ((uint32_t)b << 16);
         k = pk_min(pk_subsat(k, halves(p.ilo)), halves(p.ihi - p.ilo));
-    } else {
-        k = bin_of<DT>(a, p) | (bin_of<DT>(b, p) << 16);
+        if constexpr (!IDENT) {
+            // bin_of on both halves; v_mad_u32_u16 takes a half and multiplies it
+            uint32_t na, nb;
+            asm("v_mad_u32_u16 %0, %1, %2, 0" : "=v"(na) : "v"(k), "s"(p.nbins));
+            asm("v_mad_u32_u16 %0, %1, %2, 0 op_sel:[1,0,0,0]" : "=v"(nb) : "v"(k), "s"(p.nbins));
+            k = (uint32_t)__dmul_rn((double)na, p.rcp) | ((uint32_t)__dmul_rn((double)nb, p.rcp) << 16);
+        }
     }
     if constexpr (WIN) k = pk_min(pk_sub(pk_max(k, w.floor), w.sub), w.top);
     return pk_max(k, oob);
@@ -417,33 +424,54 @@ struct Task3 {
     int r_lo, r_hi;
 };
 
-// Wave task `task` of a plane block (Strips): units 2 task and 2 task + 1 of the
-// slots of the whole strips, or two units of one of the other strips.
+// The slots of wave task `task`: the strip (block) of its first one, that one's
+// place in it, and the slots from there to the end of the numbering.
+struct Place {
+    bool whole;
+    int64_t strip, left;
+    uint32_t c0;
+};
+__device__ __forceinline__ Place task_place(const Units& Y, uint32_t task)
+{
+    const uint32_t P = Y.slots;
+    Place p;
+    p.whole = task < Y.pairs_full;
+    if (p.whole) {
+        const uint64_t g = (uint64_t)task * (2u * kLaneCols), total = (uint64_t)(Y.sb - Y.sa) * P;
+        const uint64_t s = (total >> 32) == 0 ? (uint64_t)((uint32_t)g / P) : g / P;
+        p.strip = (int64_t)Y.sa + uniform_i64((int64_t)s);
+        p.c0 = uniform_u32((uint32_t)(g - s * P));
+        p.left = uniform_i64((int64_t)(total - g));
+    } else {
+        const uint32_t e = task - Y.pairs_full;
+        const uint32_t i = uniform_u32(e / Y.pairs_edge);
+        p.c0 = (e - i * Y.pairs_edge) * (2u * kLaneCols);
+        p.strip = i < Y.sa ? (int64_t)i : (int64_t)Y.sb + (int64_t)(i - Y.sa);
+        p.left = (int64_t)P - (int64_t)p.c0;
+    }
+    return p;
+}
+// Strips (blocks) passed by place c < P + 2 * 64: c / P, for narrow ones through a
+// 16-bit reciprocal m = 65536 / P + 1 (exact for c < 256, P < 128).
+__device__ __forceinline__ uint32_t strips_passed(uint32_t c, uint32_t P, uint32_t m)
+{
+    return P < 128u ? (c * m) >> 16 : (c >= P ? 1u : 0u);
+}
+
+// Wave task `task` of a plane block.
 template <int DT, int CONS, int R>
-__device__ __forceinline__ Task3 strip_task(const EccLaunch& L, const Strips& Y, uint32_t sm, uint32_t task)
+__device__ __forceinline__ Task3 strip_task(const Geom& G, const Units& Y, uint32_t sm, uint32_t task)
 {
     using T = typename ValT<DT>::T;
     constexpr int org = CONS == CONS_TOP ? -1 : 0;
-    const int64_t n1 = L.g.n1, n2 = L.g.n2;
+    const int64_t n1 = G.n1, n2 = G.n2;
     const uint32_t row_bytes = (uint32_t)(n2 * (int64_t)sizeof(T));
-    const uint32_t P = (uint32_t)Y.slots;
+    const uint32_t P = Y.slots;
     Task3 K;
-    K.active = task < (uint32_t)Y.tasks;
-    int64_t strip, left;   // first strip; slots from the task's first one to the end of the numbering
-    uint32_t c0;           // the first slot's place in its strip
-    if (task < (uint32_t)Y.pairs_full) {
-        const uint64_t g = (uint64_t)task * (2u * kLaneCols), total = (uint64_t)(Y.sb - Y.sa) * P;
-        const uint64_t s = (total >> 32) == 0 ? (uint64_t)((uint32_t)g / P) : g / P;
-        strip = Y.sa + uniform_i64((int64_t)s);
-        c0 = uniform_u32((uint32_t)(g - s * P));
-        left = uniform_i64((int64_t)(total - g));
-    } else {
-        const uint32_t e = task - (uint32_t)Y.pairs_full;
-        const uint32_t i = uniform_u32(e / (uint32_t)Y.pairs_edge);
-        c0 = (e - i * (uint32_t)Y.pairs_edge) * (2u * kLaneCols);
-        strip = i < (uint32_t)Y.sa ? (int64_t)i : Y.sb + (int64_t)(i - (uint32_t)Y.sa);
-        left = (int64_t)P - (int64_t)c0;
-    }
+    K.active = task < Y.tasks;
+    const Place at0 = task_place(Y, task);
+    const int64_t strip = at0.strip, left = at0.left;
+    const uint32_t c0 = at0.c0;
     K.ys = org + strip * R;
     K.r_lo = K.ys < 0 ? (int)(-K.ys) : 0;
     K.r_hi = (int)((n1 - K.ys) < R + 1 ? (n1 - K.ys) : R + 1);
@@ -452,8 +480,6 @@ __device__ __forceinline__ Task3 strip_task(const EccLaunch& L, const Strips& Y,
     // they would hold registers through every brick's body
     uint32_t lane = lane_id();
     asm volatile("" : "+v"(lane));
-    // strips passed by place c < P + 2 * 64: c / P, for narrow strips through a
-    // 16-bit reciprocal (exact for c < 256, P < 128)
     const uint32_t m = 65536u / P + 1u;
     uint32_t x[2], oob = 0, own = 0;
 #pragma unroll
@@ -461,7 +487,7 @@ __device__ __forceinline__ Task3 strip_task(const EccLaunch& L, const Strips& Y,
         const uint32_t at = (uint32_t)(h * kLaneCols) + lane;
         const bool in = (int64_t)at < left;
         const uint32_t c = in ? c0 + at : 0u;
-        const uint32_t q = P < 128u ? (c * m) >> 16 : (c >= P ? 1u : 0u);
+        const uint32_t q = strips_passed(c, P, m);
         const int32_t col = org + (int32_t)(c - q * P);
         const bool ok = in && col >= 0 && col < (int32_t)n2;
         const uint32_t cx = ok ? (uint32_t)col : (col < 0 ? 0u : (uint32_t)n2 - 1u);
@@ -486,6 +512,170 @@ __device__ __forceinline__ void run_march_3d(const EccLaunch& L, const BinParams
     } else {
         if (full) march_3d<DT, CONS, R, WIN, true, false, PAIR>(L, P, H, K.lanes, K.ys, z0, ze, K.r_lo, K.r_hi);
         else march_3d<DT, CONS, R, WIN, false, false, PAIR>(L, P, H, K.lanes, K.ys, z0, ze, K.r_lo, K.r_hi);
+    }
+}
+
+// ------------------------------------------------------------------------- 2D
+
+// A wave's place in a 2D image: its lanes and the rows of its block.
+struct Task2 {
+    bool active, whole;   // whole: a block of the numbered slots (every block `depth` rows)
+    Lanes lanes;
+    uint32_t xl[2];       // the lane's columns in the row after the block (the last row inside the image)
+    uint32_t oob_last;    // the sentinel where that row lies outside the image, or N.oob
+    uint32_t first;       // 0xFF in the bytes of the positions in the image's first block
+    int64_t y0;           // first row of the lanes' (first) block
+};
+
+// Rows of a 2D block for one wave: rows are the marching axis, types T0 = the row
+// and T1 = op2(T0, right), with signs +, - (vertex) or -, + (top).  The counts of
+// T1 go to the left or the right voxel and each voxel's sum is added once (see
+// above: bytes 0-1 hold T0's fields, 2-3 T1's).  EDGE: one block for the whole
+// wave, `rows` of it counted, `avail` rows readable from its first one.  Otherwise
+// (whole blocks, `rows` a multiple of 8) the lanes may sit in different blocks.
+// Bound by vector issue: 20 instructions a row of two positions beside the
+// binning, every one 4 cycles; loads run 8 rows ahead.
+template <int DT, int CONS, bool WIN, bool IDENT, bool EDGE>
+__device__ __forceinline__ void march_2d(const void* base, uint32_t row_bytes, const BinParams& P, const WinKeys& W,
+                                         const HistRef& H, const Task2& K, uint32_t rows, uint32_t avail)
+{
+    using T = typename ValT<DT>::T;
+    constexpr int G = 8;   // rows loaded ahead
+    constexpr uint32_t M = CONS == CONS_VERTEX ? 0xFFFF0000u : 0x0000FFFFu;
+    const Lanes& N = K.lanes;
+    const uint32_t S = halves(H.sm);
+    const __amdgpu_buffer_rsrc_t rs = rsrc_at(base);
+    T raw[G][2];
+    uint32_t soff = 0;   // byte offset of the next row to load
+    // loads row r (relative to the block): EDGE stays on the last readable row;
+    // otherwise the row after the block takes the lanes' own places
+    auto load = [&](int k, uint32_t r, bool last) {
+        if (EDGE) {
+            raw[k][0] = buffer_load<T>(rs, N.xa, soff);
+            raw[k][1] = buffer_load<T>(rs, N.xb, soff);
+            soff = advance(soff, r + 1 < avail ? row_bytes : 0u);
+        } else {
+            raw[k][0] = buffer_load<T>(rs, last ? K.xl[0] : N.xa, last ? 0u : soff);
+            raw[k][1] = buffer_load<T>(rs, last ? K.xl[1] : N.xb, last ? 0u : soff);
+            soff = advance(soff, row_bytes);
+        }
+    };
+    uint32_t t0, t1, q;
+    auto count = [&](uint32_t d) {
+        const uint32_t f = (d ^ M) & N.own, c = q - f;
+        q = f | kFieldBias;
+        const uint32_t nx = signs_low(CONS == CONS_VERTEX ? pk_sub(t0, t1) : pk_sub(t1, t0));
+        const uint32_t h = c >> 16, right = h & nx;
+        uint32_t x = c + from_left(right);
+        asm("" : "+v"(x));
+        add_pair<WIN>(H, t0, x + (h - right));
+    };
+    load(0, 0, false);
+    t0 = pair_key<DT, IDENT, WIN>(raw[0][0], raw[0][1], P, W, N.oob);
+    t1 = pk_op<CONS>(t0, from_right(t0));
+    // the image's first row wins the interval before it (D = 1), except types
+    // whose cells do not exist (the sentinel)
+    q = (((signs(pk_sub(t1, S), pk_sub(t0, S)) & K.first) ^ M) & N.own) | kFieldBias;
+#pragma unroll
+    for (int k = 0; k < G; ++k) load(k, 1u + (uint32_t)k, !EDGE && k == G - 1 && rows == (uint32_t)G);
+    // counts row r - 1 against the loaded row r
+    auto row = [&](int k, uint32_t oob) {
+        const uint32_t n0 = pair_key<DT, IDENT, WIN>(raw[k][0], raw[k][1], P, W, oob);
+        const uint32_t n1 = pk_op<CONS>(n0, from_right(n0));
+        count(signs(pk_sub(n1, t1), pk_sub(n0, t0)));
+        t0 = n0;
+        t1 = n1;
+    };
+    // groups of G rows that need no check, then the rest
+    const uint32_t plain = EDGE ? (rows < avail ? rows : rows - 1u) / G * G : rows - G;
+    uint32_t y = 0;
+    for (; y < plain; y += G) {
+#pragma unroll
+        for (int k = 0; k < G; ++k) {
+            // the row's registers take the next group's row as soon as its key is made
+            const uint32_t n0 = pair_key<DT, IDENT, WIN>(raw[k][0], raw[k][1], P, W, N.oob);
+            load(k, y + 1u + (uint32_t)(k + G), k == G - 1 && y + 2 * G >= rows);
+            const uint32_t n1 = pk_op<CONS>(n0, from_right(n0));
+            count(signs(pk_sub(n1, t1), pk_sub(n0, t0)));
+            t0 = n0;
+            t1 = n1;
+        }
+    }
+    if (EDGE) {
+#pragma unroll
+        for (int k = 0; k < G; ++k)
+            if (y + (uint32_t)k < rows) row(k, y + 1u + (uint32_t)k < avail ? N.oob : S);
+    } else {
+#pragma unroll
+        for (int k = 0; k < G; ++k) row(k, k == G - 1 ? K.oob_last : N.oob);
+    }
+    // the part of the next block's first row that this block's last row decides
+    // (at the image's last row the keys are the sentinel and the counts 0)
+    if (!EDGE || rows < avail) count(0u);
+}
+
+// Wave task `task` of a 2D image.
+template <int DT, int CONS>
+__device__ __forceinline__ Task2 block_task(const Geom& G, const Units& Y, int64_t depth, uint32_t sm, uint32_t task)
+{
+    using T = typename ValT<DT>::T;
+    constexpr int org = CONS == CONS_TOP ? -1 : 0;
+    const uint32_t row_bytes = (uint32_t)(G.n2 * (int64_t)sizeof(T));
+    const uint32_t P = Y.slots;
+    Task2 K;
+    K.active = task < Y.tasks;
+    const Place at0 = task_place(Y, task);
+    K.whole = at0.whole;
+    const int64_t block = at0.strip, left = at0.left;
+    const uint32_t c0 = at0.c0;
+    K.y0 = block * depth;
+    // the lane's places, computed here for each brick (strip_task)
+    uint32_t lane = lane_id();
+    asm volatile("" : "+v"(lane));
+    const uint32_t m = 65536u / P + 1u;
+    const uint32_t block_bytes = (uint32_t)depth * row_bytes;
+    uint32_t x[2], oob = 0, own = 0, oob_last = 0, first = 0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t at = (uint32_t)(h * kLaneCols) + lane;
+        const bool in = (int64_t)at < left;
+        const uint32_t c = in ? c0 + at : 0u;
+        const uint32_t q = K.whole ? strips_passed(c, P, m) : 0u;
+        const int32_t col = org + (int32_t)(c - q * P);
+        const bool ok = in && col >= 0 && col < (int32_t)G.n2;
+        const uint32_t cx = ok ? (uint32_t)col : (col < 0 ? 0u : (uint32_t)G.n2 - 1u);
+        x[h] = cx * (uint32_t)sizeof(T) + q * block_bytes;
+        // the row after the block, or its last row where the image ends with it
+        const bool ends = K.whole && (block + (int64_t)q + 1) * depth >= G.n1;
+        K.xl[h] = x[h] + block_bytes - (ends ? row_bytes : 0u);
+        if (!ok) oob |= sm << (16 * h);
+        if (!ok || ends) oob_last |= sm << (16 * h);
+        if (in && lane < (uint32_t)kLaneCols) own |= 0x00010001u << (8 * h);
+        if (block + (int64_t)q == 0) first |= 0x00FF00FFu << (8 * h);
+    }
+    K.lanes = Lanes{x[0], x[1], oob, own};
+    K.oob_last = oob_last;
+    K.first = first;
+    return K;
+}
+
+// Runs wave task K of the 2D image at data.
+template <int DT, int CONS, bool WIN>
+__device__ __forceinline__ void run_march_2d(const void* data, const Geom& G, int64_t depth, const BinParams& P,
+                                             const WinKeys& W, const HistRef& H, const Task2& K)
+{
+    if (!K.active) return;
+    using T = typename ValT<DT>::T;
+    const int64_t row_bytes = G.n2 * (int64_t)sizeof(T);
+    const char* base = (const char*)data + K.y0 * row_bytes;
+    const uint32_t avail = (uint32_t)(G.n1 - K.y0);
+    const uint32_t rows = (int64_t)avail < depth ? avail : (uint32_t)depth;
+    if (DT != DT_F32 && uniform_flag(P.ident)) {
+        if (K.whole) march_2d<DT, CONS, WIN, true, false>(base, (uint32_t)row_bytes, P, W, H, K, rows, avail);
+        else march_2d<DT, CONS, WIN, true, true>(base, (uint32_t)row_bytes, P, W, H, K, rows, avail);
+    } else {
+        if (K.whole) march_2d<DT, CONS, WIN, false, false>(base, (uint32_t)row_bytes, P, W, H, K, rows, avail);
+        else march_2d<DT, CONS, WIN, false, true>(base, (uint32_t)row_bytes, P, W, H, K, rows, avail);
     }
 }
 

@@ -64,3 +64,30 @@ def test_strips_and_units_3d(oracle_mod, cons, kind):
                 assert np.array_equal(got.cpu().numpy(), want), (cons, kind, shape, depth)
     finally:
         ctx.close()
+
+
+SHAPES_2D = [(1, 1), (1, 200), (16, 62), (15, 63), (17, 64), (32, 125), (33, 126), (48, 127), (16, 2), (200, 1),
+             (160, 3), (97, 41), (256, 189)]
+
+
+@pytest.mark.parametrize("cons", ["vertex", "top"])
+@pytest.mark.parametrize("kind", ["u8", "u16", "u16wide", "f32", "f32one"])
+def test_blocks_and_units_2d(oracle_mod, cons, kind):
+    """2D: blocks of `depth` rows in place of strips; heights of whole blocks, one
+    row more and one row less."""
+    from paper_2203_09087_amd import ecc
+    rng = np.random.default_rng(4200)
+    ctx = ecc.Context(0, cons)
+    try:
+        for shape in SHAPES_2D:
+            img, nbins, r = draw_image(rng, shape, kind)
+            say(f"case: {cons} {kind} {shape} nbins={nbins}")
+            dev = to_dev(img)
+            want = oracle_mod.ecc(img, nbins, cons, value_range=r, threads=8)
+            for depth in (0, 16, 32, 48):
+                ctx.set_launch_shape(dev, nbins, depth=depth)
+                got = ctx.compute(dev, nbins, value_range=r)
+                torch.cuda.synchronize()
+                assert np.array_equal(got.cpu().numpy(), want), (cons, kind, shape, depth)
+    finally:
+        ctx.close()
