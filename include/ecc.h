@@ -310,8 +310,10 @@ ecc_status ecc_batch_plan_destroy(ecc_batch_plan* plan);
  * point to, enqueues nothing): how ecc_compute_batch on a context of filtration
  * `construction` (ecc_construction), or a plan with launch shape `shape` (HOST
  * pointer; null = the default shape), splits a batch over the workgroups of
- * `cu_count` compute units.  The bricks of every image are cut into segments,
- * one workgroup histogram each; a segment covers at most 2^27 voxels, so its
+ * `cu_count` compute units.  The bricks of every image (the units its work is
+ * counted in; a run of them stands for the same share of the image's wave tasks)
+ * are cut into segments, one workgroup histogram each; a segment covers at most
+ * 2^27 voxels, so its
  * int32 counters cannot overflow (a voxel position adds at most 8 in absolute
  * value; Sec. 4.3's shared-memory counters hold the sums).  Outputs (HOST
  * pointers): *segments = the number of segments, *max_segment_voxels = the most

@@ -280,8 +280,6 @@ ecc::BinParams host_params(const Job& j, int32_t nbins)
     ecc::BinParams p = {};
     p.dtype = j.dtype;
     p.nbins = nbins;
-    p.lo = j.lo;
-    p.hi = j.hi;
     if (j.dtype == ECC_F32) {
         p.flat = (j.hi == j.lo) ? 1 : 0;
         // a flat range bins through scale = +inf (see key_of in the kernels)
@@ -854,7 +852,8 @@ struct BatchTables {
     int count = 0;
     int32_t nbins = 0, window = 0;
     std::vector<ecc::BatchImage> images;
-    std::vector<ecc::BatchSeg> segs;
+    std::vector<ecc::BatchWork> work;    // of each volume
+    std::vector<ecc::BatchSeg> segs;     // in bricks (the kernel's table: in wave tasks)
     std::vector<int32_t> wg_seg, slot_off, slots;
     std::vector<uint32_t> mm;
     std::vector<ecc::BatchPiece> pieces;
@@ -864,7 +863,7 @@ struct BatchTables {
 };
 
 // The batch's launch shape unless a plan was tuned.
-constexpr ecc_batch_shape kDefaultBatchShape = {8, 128, 2, 0, 0.0};
+constexpr ecc_batch_shape kDefaultBatchShape = {8, 128, 0, 0, 0.0};   // wgs_per_cu 0: batch_wgs
 
 // Voxels one batch segment may cover (counted over whole bricks, so including
 // brick parts outside the image).  Its workgroup histogram and its partial row
@@ -873,11 +872,25 @@ constexpr ecc_batch_shape kDefaultBatchShape = {8, 128, 2, 0, 0.0};
 // plane or row), so 2^27 voxels keep every counter below 2^31.
 constexpr int64_t kSegVoxels = int64_t(1) << 27;
 
+// Workgroups per CU of a batch launch with `work` vector instructions per CU.  More
+// workgroups even out the end of the launch (two fit a CU at a time, the others
+// follow), but each clears, flushes and has merged a histogram of its own, about
+// ten instructions per counter: so many that a workgroup still counts for one and a
+// half times that.  Measured: 512 uneven uint8 images, 256 bins: 572, 442, 441 and
+// 419 us with 1 to 4; 16 uint16 images (33 M voxels), 4096 bins: 94, 107, 128 and
+// 138 us.  At most 6 over the launches of all dtypes (ecc_reserve's segment bound).
+int batch_wgs(double work, int32_t window, int ndtypes)
+{
+    const double counters = (double)window * (double)ecc::hist_copies(window);
+    for (int wgs : {4, 3, 2})
+        if (wgs * ndtypes <= 6 && work / wgs >= 15.0 * counters) return wgs;
+    return 1;
+}
+
 void build_batch_tables(int cu_count, int construction, const std::vector<Job>& jobs, int32_t nbins, BatchTables& T,
                         const ecc_batch_shape& shape = kDefaultBatchShape)
 {
     const int count = (int)jobs.size();
-    const int waves = ecc::kBatchWaves;
     T.count = count;
     T.nbins = nbins;
     T.window = std::min<int32_t>(nbins, ecc::kMaxLdsBins);
@@ -894,7 +907,6 @@ void build_batch_tables(int cu_count, int construction, const std::vector<Job>& 
         im.ndim = j.ndim;
         im.dtype = j.dtype;
         im.auto_range = j.range_mode == ECC_RANGE_AUTO ? 1 : 0;
-        im.nvox = j.nvox;
         im.params = host_params(j, nbins);
         im.out = j.out;
         im.sign = 1;
@@ -912,7 +924,6 @@ void build_batch_tables(int cu_count, int construction, const std::vector<Job>& 
                 if (sign == 0 || (pair && w + 1 >= nw)) continue;
                 ecc::BatchImage v = T.images[(size_t)i];
                 v.ndim = 3;
-                v.nvox = hv;
                 v.data = (const char*)j.data + (size_t)w * (size_t)hv * esize;
                 v.data2 = pair ? (const char*)j.data + (size_t)(w + 1) * (size_t)hv * esize : nullptr;
                 v.sign = sign;
@@ -922,21 +933,23 @@ void build_batch_tables(int cu_count, int construction, const std::vector<Job>& 
         }
     }
     const size_t nrec = T.images.size();
+    T.work.assign(nrec, ecc::BatchWork{});
     std::vector<int64_t> bricks(nrec, 0), max_take(nrec, 1);
     std::vector<double> brick_cost(nrec, 0.0);
     T.owner_bricks.assign((size_t)count, 0);
     for (int i : vols) {
         ecc::BatchImage& im = T.images[(size_t)i];
-        bricks[(size_t)i] = ecc::batch_bricks(im, construction, waves, shape.depth3, shape.depth2);
-        T.owner_bricks[(size_t)im.owner] += bricks[(size_t)i];
-        // time of one brick: a team of wpb waves walks its rows (two 2D problems
-        // per row in 3D, twice the loads for a pair volume); W / wpb teams of a
-        // workgroup share one pass
-        const double teams = (double)(waves / im.wpb);
-        brick_cost[(size_t)i] = (im.ndim == 3 ? 2.0 * ecc::kRows3 : 1.0) * (double)im.depth / teams;
+        const ecc::BatchWork w = ecc::batch_work(im, construction, shape.depth3, shape.depth2);
+        T.work[(size_t)i] = w;
+        bricks[(size_t)i] = w.bricks;
+        T.owner_bricks[(size_t)im.owner] += w.bricks;
+        brick_cost[(size_t)i] = w.cost;
         // a segment's histogram is an int32 row: at most kSegVoxels voxels each
-        max_take[(size_t)i] = std::max<int64_t>(1, kSegVoxels / ecc::batch_brick_voxels(im));
+        max_take[(size_t)i] = std::max<int64_t>(1, kSegVoxels / w.brick_voxels);
     }
+    int ndtypes = 0;
+    for (int dt = 0; dt < 3; ++dt)
+        ndtypes += std::any_of(vols.begin(), vols.end(), [&](int i) { return T.images[(size_t)i].dtype == dt; });
     // One launch per dtype present; the bricks of its volumes, in order, are cut
     // into one contiguous run per workgroup with about equal work.
     for (int dt = 0; dt < 3; ++dt) {
@@ -950,7 +963,8 @@ void build_batch_tables(int cu_count, int construction, const std::vector<Job>& 
                 pairs = pairs || T.images[(size_t)i].data2 != nullptr;
             }
         if (nbr == 0) continue;
-        const int G = (int)std::max<int64_t>(1, std::min<int64_t>(nbr, (int64_t)shape.wgs_per_cu * cu_count));
+        const int wgs = shape.wgs_per_cu > 0 ? shape.wgs_per_cu : batch_wgs(total / cu_count, T.window, ndtypes);
+        const int G = (int)std::max<int64_t>(1, std::min<int64_t>(nbr, (int64_t)wgs * cu_count));
         BatchGroup gr{dt, G, T.wg_seg.size(), pairs};
         const double per = total / G;
         int wg = 0;
@@ -992,8 +1006,8 @@ void build_batch_tables(int cu_count, int construction, const std::vector<Job>& 
     const int64_t piece = int64_t(1) << 20;
     for (int i = 0; i < count; ++i)
         if (T.images[(size_t)i].auto_range)
-            for (int64_t b = 0; b < T.images[(size_t)i].nvox; b += piece)
-                T.pieces.push_back(ecc::BatchPiece{i, 0, b, std::min(T.images[(size_t)i].nvox, b + piece)});
+            for (int64_t b = 0; b < jobs[(size_t)i].nvox; b += piece)
+                T.pieces.push_back(ecc::BatchPiece{i, 0, b, std::min(jobs[(size_t)i].nvox, b + piece)});
     T.mm.assign((size_t)count * 2, 0u);
     for (int i = 0; i < count; ++i) T.mm[2 * (size_t)i] = 0xFFFFFFFFu;
 
@@ -1010,12 +1024,25 @@ void build_batch_tables(int cu_count, int construction, const std::vector<Job>& 
     lay.total = lay.partials + align_up((size_t)nseg * (size_t)T.window * sizeof(int32_t));
 }
 
+// The wave tasks of a volume before its brick b: tasks * b / bricks, rounded down
+// (at most 2^32 tasks and 2^40 bricks).
+int64_t share(const ecc::BatchWork& w, int64_t b)
+{
+    return (int64_t)((unsigned __int128)w.tasks * (uint64_t)b / (uint64_t)w.bricks);
+}
+
 // Copies the tables into host memory laid out as lay (bytes [0, tables_end)).
 void pack_batch_tables(const BatchTables& T, char* h)
 {
     const BatchLayout& lay = T.lay;
     memcpy(h + lay.images, T.images.data(), T.images.size() * sizeof(ecc::BatchImage));
-    memcpy(h + lay.segs, T.segs.data(), T.segs.size() * sizeof(ecc::BatchSeg));
+    // the run [b0, b1) of a volume's bricks stands for this share of its wave tasks
+    ecc::BatchSeg* segs = (ecc::BatchSeg*)(h + lay.segs);
+    for (size_t k = 0; k < T.segs.size(); ++k) {
+        const ecc::BatchSeg& g = T.segs[k];
+        const ecc::BatchWork& w = T.work[(size_t)g.image];
+        segs[k] = ecc::BatchSeg{g.image, g.slot, share(w, g.b0), share(w, g.b1)};
+    }
     memcpy(h + lay.wg_seg, T.wg_seg.data(), T.wg_seg.size() * sizeof(int32_t));
     memcpy(h + lay.slot_off, T.slot_off.data(), T.slot_off.size() * sizeof(int32_t));
     memcpy(h + lay.slots, T.slots.data(), T.slots.size() * sizeof(int32_t));
@@ -1043,8 +1070,7 @@ ecc_status launch_batch_kernels(ecc_ctx* ctx, const BatchTables& T, char* d, boo
     B.windowed = T.window < T.nbins ? 1 : 0;
     B.hist_stride = ecc::lds_stride(T.window);
     B.hist_copies = ecc::hist_copies(T.window);
-    B.sentinel = ecc::lds_sentinel(T.nbins);
-    B.lds_bytes = 4u * ecc::lds_words(T.window, B.windowed != 0, B.sentinel, B.hist_copies);
+    B.lds_bytes = 4u * B.hist_copies * B.hist_stride;
     hipError_t e;
     if (!T.pieces.empty()) {
         if (reset_mm && (e = ecc::launch_mm_init(B.mm, T.count, stream)) != hipSuccess)
@@ -1465,7 +1491,7 @@ ecc_status ecc_batch_schedule(const ecc_image* imgs, int32_t count, int32_t nbin
         return ECC_ERR_INVALID_ARG;
     }
     ecc_batch_shape sh = shape ? *shape : kDefaultBatchShape;
-    if (sh.depth3 < 1 || sh.depth2 < 1 || sh.wgs_per_cu < 1) {
+    if (shape && (sh.depth3 < 1 || sh.depth2 < 1 || sh.wgs_per_cu < 1)) {
         g_create_err = "ecc_batch_schedule: shape fields must be positive";
         return ECC_ERR_INVALID_ARG;
     }
@@ -1485,7 +1511,7 @@ ecc_status ecc_batch_schedule(const ecc_image* imgs, int32_t count, int32_t nbin
     int64_t mx = 0;
     std::vector<int64_t> cov((size_t)count, 0);
     for (const auto& sg : T.segs) {
-        const int64_t v = (sg.b1 - sg.b0) * ecc::batch_brick_voxels(T.images[(size_t)sg.image]);
+        const int64_t v = (sg.b1 - sg.b0) * T.work[(size_t)sg.image].brick_voxels;
         mx = std::max(mx, v);
         cov[(size_t)T.images[(size_t)sg.image].owner] += sg.b1 - sg.b0;
     }

@@ -3,7 +3,7 @@
 //
 // The host cuts the bricks of all images (in order) into one contiguous run per
 // workgroup, balanced by work, and lists each run as segments of single images.
-// A workgroup processes its segments in order with the same brick bodies as the
+// A workgroup processes its segments in order with the same marching bodies as the
 // single-image kernels, and writes one partial histogram row per segment.  The
 // merge kernels then give every image the sum of its rows (and its prefix scan)
 // without any atomic operation on the histogram bins, so the result of an image
@@ -12,7 +12,7 @@
 
 #include <hip/hip_ext.h>
 
-#include "ecc_device.h"
+#include "ecc_march.h"
 
 namespace ecc {
 
@@ -69,74 +69,58 @@ __global__ __launch_bounds__(kThreads) void k_minmax_batch(const BatchImage* ima
     }
 }
 
-// PAIRS: the launch holds pair volumes (their bricks load two hyperplanes).
+// Every workgroup takes its segments in turn: a segment's wave tasks go to its
+// waves one after the other, their counts to one histogram.  PAIRS: the launch
+// holds pair volumes (their tasks load two hyperplanes).
 template <int DT, int CONS, bool WIN, bool PAIRS>
-__global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(ECC_WAVES_PER_EU_BATCH)))
+__global__ __launch_bounds__(kBatchWaves * 64) __attribute__((amdgpu_waves_per_eu(ECC_WAVES_PER_EU_BATCH)))
 void k_ecc_batch(BatchLaunch B)
 {
     extern __shared__ __align__(16) int32_t hist[];
-    const HistRef H = hist_ref(hist, B.bin_lo, B.width, B.hist_stride, B.sentinel, B.hist_copies);
-    const int W = (int)(blockDim.x >> 6), wave = wave_id();
+    const HistRef H = march_hist<WIN>(hist, B.width, B.hist_stride, B.hist_copies);
+    const WinKeys W = win_keys<WIN>(B.bin_lo, B.width);
     const int s_end = B.wg_seg[blockIdx.x + 1];
     for (int si = B.wg_seg[blockIdx.x]; si < s_end; ++si) {
         // The tables are read with vector loads (the kernel also writes global
         // memory, so the scalar cache is not used for them): every value the
-        // brick loops depend on is read back from the first lane, so that sizes,
-        // offsets and pointers stay in scalar registers there.
+        // marching bodies depend on is read back from the first lane, so that
+        // sizes, offsets and pointers stay in scalar registers there.
         const BatchSeg S = B.segs[si];
         const int vol = (int)uniform_u32((uint32_t)S.image);
         const BatchImage& I = B.images[vol];
-        const BinParams P = I.auto_range
-                                ? params_from_keys(B.mm[2 * I.owner], B.mm[2 * I.owner + 1], DT, B.nbins)
-                                : I.params;
-        EccLaunch L;   // the fields the brick bodies read
+        const BinParams P = uniform_params<DT>(
+            I.auto_range ? params_from_keys(B.mm[2 * I.owner], B.mm[2 * I.owner + 1], DT, B.nbins) : I.params);
+        EccLaunch L;   // the fields the marching bodies read
         L.data = uniform_ptr(I.data);
         L.data2 = PAIRS ? uniform_ptr(I.data2) : nullptr;
         L.g = Geom{uniform_i64(I.g.n0), uniform_i64(I.g.n1), uniform_i64(I.g.n2)};
         L.depth = uniform_i64(I.depth);
-        L.z_own = L.g.n0;
         L.z_base = 0;
         L.pass_stride = 0;
         L.n0_global = L.g.n0;
+        L.bin_lo = B.bin_lo;
+        L.width = B.width;
+        const Units Y = {uniform_u32(I.units.slots), uniform_u32(I.units.sa), uniform_u32(I.units.sb),
+                         uniform_u32(I.units.pairs_full), uniform_u32(I.units.pairs_edge),
+                         uniform_u32(I.units.tasks)};
         const int ndim = (int)uniform_u32((uint32_t)I.ndim);
         zero_hist(H, B.width);
-        // the workgroup's waves form W / wpb teams of wpb waves; team t takes
-        // bricks b0 + t, b0 + t + teams, ... (waves beyond the last team idle)
-        const int wpb = uniform_u32((uint32_t)I.wpb);
-        const int teams = W / wpb, team = wave / wpb, xw = wave - team * wpb;
-        const int64_t chunk = kLaneCols * (int64_t)wpb;
-        const uint32_t nxc = uniform_u32((uint32_t)I.nxc);
-        const int64_t b0 = uniform_i64(S.b0), b1 = uniform_i64(S.b1);
-        if (team < teams && ndim == 3) {
-            // per plane block: ordinary bricks (x-chunk fastest), packed tail
-            // bricks, the tails of the strips not packed (layout_3d, as k_ecc_3d)
-            const Layout3 Y = layout_3d(L.g, CONS, wpb);
-            const int64_t per_z = Y.per_z, main = Y.nxc * Y.nyb;
-            for (int64_t b = b0 + team; b < b1; b += teams) {
-                // brick coordinates from the 64-bit index; each fits 32 bits
-                const int64_t zb = b / per_z, r = b - zb * per_z;
-                Brick3 K;
-                if (r < main) {
-                    K = chunk_brick_3d<DT, CONS, WIN>(L, H, chunk, (uint32_t)(r % nxc), (uint32_t)(r / nxc),
-                                                      (uint32_t)zb, xw);
-                } else if (r - main < Y.npk) {
-                    K = tail_brick_3d<DT, CONS, WIN>(L, H, Y, wpb, (uint32_t)(r - main), (uint32_t)zb, xw);
-                } else {
-                    const int64_t e = r - main - Y.npk;   // the strips before sa, then those from sb on
-                    K = chunk_brick_3d<DT, CONS, WIN>(L, H, chunk, nxc, (uint32_t)(e < Y.sa ? e : Y.sb + (e - Y.sa)),
-                                                      (uint32_t)zb, xw);
-                }
-                if (PAIRS && L.data2) run_brick3<DT, CONS, WIN, true>(L, P, H, K);
-                else run_brick3<DT, CONS, WIN>(L, P, H, K);
+        const uint32_t t1 = uniform_u32((uint32_t)S.b1);
+        for (uint32_t t = uniform_u32((uint32_t)S.b0) + (uint32_t)wave_id(); t < t1; t += (uint32_t)kBatchWaves) {
+            if (ndim == 2) {
+                run_march_2d<DT, CONS, WIN>(L.data, L.g, L.depth, P, W, H, block_task<DT, CONS>(L.g, Y, L.depth, H.sm, t));
+                continue;
             }
-        } else if (team < teams) {
-            for (int64_t b = b0 + team; b < b1; b += teams) {
-                const int64_t row = b / nxc;
-                run_brick_2d<DT, CONS, WIN>(L, P, H, chunk, (uint32_t)(b - row * nxc), (uint32_t)row, xw);
-            }
+            const uint32_t zb = uniform_u32(t / Y.tasks);
+            const Task3 K = strip_task<DT, CONS, kStripRows>(L.g, Y, H.sm, t - zb * Y.tasks);
+            const uint32_t z0 = zb * (uint32_t)L.depth;
+            const uint32_t ze = (int64_t)z0 + L.depth < L.g.n0 ? z0 + (uint32_t)L.depth : (uint32_t)L.g.n0;
+            if (PAIRS && L.data2) run_march_3d<DT, CONS, kStripRows, WIN, true>(L, P, H, K, z0, ze);
+            else run_march_3d<DT, CONS, kStripRows, WIN, false>(L, P, H, K, z0, ze);
         }
         flush_hist(H, B.partials + (size_t)uniform_u32((uint32_t)S.slot) * (size_t)B.width, B.width, false,
                    (int)uniform_u32((uint32_t)I.sign));
+        __syncthreads();   // the histogram is read before the next segment clears it
     }
 }
 
@@ -204,46 +188,47 @@ hipError_t launch_batch_d(const BatchLaunch& B, hipStream_t s, hipEvent_t t0, hi
 
 }  // namespace
 
-int64_t batch_bricks(BatchImage& im, int construction, int waves, int depth3, int depth2)
+BatchWork batch_work(BatchImage& im, int construction, int depth3, int depth2)
 {
     const int64_t xpos = axis_positions(im.g.n2, construction);
     const int64_t cols = (xpos + kLaneCols - 1) / kLaneCols;
-    // waves per brick: the fraction of the workgroup's lanes that own a column,
-    // (wave columns needed / wave columns covered) x (waves in teams / waves),
-    // is largest (ties: the wider brick).  A 256-wide row takes 1 wave per
-    // brick (9 teams, 81% of the lanes busy) rather than 5 (one team, 45%).
-    int best = 1;
+    // waves per brick: the fraction of kBrickWaves waves' lanes that own a column,
+    // (wave columns needed / wave columns covered) x (waves in bricks side by side
+    // / waves), is largest (ties: the wider brick)
+    int wpb = 1;
     double best_eff = -1.0;
-    for (int w = (int)std::min<int64_t>(cols, waves); w >= 1; --w) {
+    for (int w = (int)std::min<int64_t>(cols, kBrickWaves); w >= 1; --w) {
         const int64_t nx = (cols + w - 1) / w;
-        const double eff = (double)cols / (double)(nx * w) * (double)((waves / w) * w) / (double)waves;
+        const double eff = (double)cols / (double)(nx * w) * (double)((kBrickWaves / w) * w) / (double)kBrickWaves;
         if (eff > best_eff + 1e-9) {
             best_eff = eff;
-            best = w;
+            wpb = w;
         }
     }
-    im.wpb = best;
-    const int64_t chunk = kLaneCols * (int64_t)im.wpb;
-    im.nxc = (int32_t)((xpos + chunk - 1) / chunk);
+    const int64_t chunk = kLaneCols * (int64_t)wpb;
+    BatchWork b;
     if (im.ndim == 3) {
-        // the bricks of k_ecc_3d's layout for a workgroup of wpb waves (a narrow
-        // row tail packed several strips per team, layout_3d)
-        const Layout3 Y = layout_3d(im.g, construction, im.wpb);
         im.depth = depth3;
-        im.nxc = (int32_t)Y.nxc;
-        im.nyb = (int32_t)Y.nyb;
-        return Y.per_z * ((im.g.n0 + im.depth - 1) / im.depth);
+        im.units = units_3d(im.g, construction);
+        const int64_t nzb = (im.g.n0 + im.depth - 1) / im.depth;
+        b.bricks = layout_3d(im.g, construction, wpb).per_z * nzb;
+        b.brick_voxels = chunk * kRows3 * im.depth;
+        b.tasks = (int64_t)im.units.tasks * nzb;
+        // a plane step is about 240 instructions (a pair volume bins twice as
+        // much), a task starts with about three steps' worth
+        b.cost = (double)b.tasks * ((double)std::min<int64_t>(im.depth, im.g.n0) + 3.0) * (im.data2 ? 300.0 : 240.0);
+    } else {
+        // whole chunks of rows per brick (the 2D march steps groups of rows)
+        im.depth = ((int64_t)(depth2 < 1 ? 1 : depth2) + kChunk2 - 1) / kChunk2 * kChunk2;
+        im.units = units_2d(im.g, construction, im.depth);
+        b.bricks = (xpos + chunk - 1) / chunk * ((im.g.n1 + im.depth - 1) / im.depth);
+        b.brick_voxels = chunk * im.depth;
+        b.tasks = (int64_t)im.units.tasks;
+        // 25 instructions a row, and about 20 rows' worth to start a task
+        b.cost = (double)b.tasks * ((double)std::min<int64_t>(im.depth, im.g.n1) + 20.0) * 25.0;
     }
-    // whole chunks of rows per brick (the 2D brick body steps a chunk at a time)
-    im.depth = ((int64_t)(depth2 < 1 ? 1 : depth2) + kChunk2 - 1) / kChunk2 * kChunk2;
-    im.nyb = (int32_t)((im.g.n1 + im.depth - 1) / im.depth);
-    return (int64_t)im.nxc * im.nyb;
-}
-
-int64_t batch_brick_voxels(const BatchImage& im)
-{
-    const int64_t cols = kLaneCols * (int64_t)im.wpb;
-    return im.ndim == 3 ? cols * kRows3 * im.depth : cols * im.depth;
+    b.cost /= (double)b.bricks;
+    return b;
 }
 
 hipError_t launch_minmax_batch(const BatchImage* images, const BatchPiece* pieces, int npieces, uint32_t* mm,

@@ -27,7 +27,6 @@ struct BinParams {
     uint32_t ilo, ihi;  // integer range
     int32_t flat;       // float data, hi == lo
     int32_t ident;      // integer data, nbins == D = hi - lo + 1: bin = level - lo
-    double lo, hi;      // the range used
     double base;        // float data: subtrahend (lo, or the next double above lo if flat)
     double scale;       // float data: nbins / (hi - lo), +inf if flat
     double rcp;         // integer data: 1 / D rounded up
@@ -56,13 +55,11 @@ constexpr int kMaxLdsBins = 4096;
 #define ECC_WAVES_PER_EU_3D 5   // resident waves per SIMD the 3D kernels are compiled for
 #endif
 #ifndef ECC_WAVES_PER_EU_BATCH
-#define ECC_WAVES_PER_EU_BATCH 6   // the batched kernel: at most 80 vector registers, so two 9-wave workgroups fit a CU
+#define ECC_WAVES_PER_EU_BATCH 5   // resident waves per SIMD the batched kernel is compiled for
 #endif
 #ifndef ECC_WAVES_PER_EU_2D
 #define ECC_WAVES_PER_EU_2D 5   // resident waves per SIMD the 2D kernels are compiled for
 #endif
-// A key is 4 * bin: the LDS byte address of its counter.
-constexpr int kKeyShift = 2;
 // A workgroup histogram is kept in several copies, lane l of every wave adding to
 // copy l mod copies: equal keys of neighbouring lanes (frequent in smooth images)
 // then fall into different copies, each starting 8 words further in the bank
@@ -79,26 +76,11 @@ inline __host__ __device__ uint32_t hist_copies(int32_t width)
     return width <= 256 ? 8u : (width <= 1024 ? 4u : (uint32_t)kHistCopies);
 }
 // Words from one copy to the next for a window of `width` bins (a multiple of 32
-// plus 8: the 8-bank offset; with windows the word after the window is spare).
+// plus 8: the 8-bank offset; at least two words are spare: the sentinel's, and with
+// windows the one of the keys below the window).
 inline __host__ __device__ uint32_t lds_stride(int32_t width)
 {
     return ((uint32_t)width + 31u) / 32u * 32u + 8u;
-}
-// Sentinel key of a one-window launch of nbins bins: 4 (2^k - 1) with 2^k > nbins,
-// so it is above every key (4 * bin, bin < nbins) and OR-ing it into a key gives it.
-inline __host__ __device__ uint32_t lds_sentinel(int32_t nbins)
-{
-    uint32_t p = 1;
-    while (p <= (uint32_t)nbins) p <<= 1;
-    return 4u * (p - 1u);
-}
-// LDS words of a workgroup histogram: the copies and, with one window, spare
-// words up to the second copy's sentinel word, which absorbs the counts of
-// cells that do not exist (4096 bins: 12,296 words).
-inline __host__ __device__ uint32_t lds_words(int32_t width, bool windowed, uint32_t sentinel, uint32_t copies)
-{
-    const uint32_t stride = lds_stride(width);
-    return windowed ? copies * stride : stride * (copies - 1) + sentinel / 4u + 1u;
 }
 // Positions a wave owns along x (lanes 0..62; lane 63 only supplies lane 62's
 // right neighbour).
@@ -116,14 +98,12 @@ constexpr int kChunk2 = ECC_CHUNK2;    // rows loaded together in the 2D kernel
 // Waves per workgroup of the main kernels (x-chunk = waves * 63 position columns).
 constexpr int kMaxWaves = 9;
 
-// Bricks of a 3D volume of a batch (k_ecc_batch).  Ordinary bricks are an
-// x-chunk of 63 * waves position columns x kRows3 rows (a strip) x `depth`
-// planes, each wave on 63 columns of the chunk.  When the positions of a row
-// leave a narrow tail after the full chunks (t < 32 columns), a wave on the
-// tail would own t of its 63 lanes; instead the tail is packed: t + 1 lanes per
-// strip (t owning, one supplying the right neighbour), floor(64 / (t + 1))
-// strips per wave, for the strips whose rows (and the row after them) all lie
-// in the image; the few other strips' tails run as ordinary bricks.
+// Bricks of a 3D volume, the units in which a batch is scheduled (BatchWork).
+// Ordinary bricks are an x-chunk of 63 * waves position columns x kRows3 rows (a
+// strip) x `depth` planes.  A narrow tail of t < 32 columns after the full chunks
+// counts as packed bricks: t + 1 lanes per strip, floor(64 / (t + 1)) strips per
+// wave, for the strips whose rows (and the row after them) all lie in the image;
+// the few other strips' tails count as ordinary bricks.
 struct Layout3 {
     int64_t nxc;        // x-chunks of the ordinary bricks of each strip (full ones)
     int64_t nyb;        // strips
@@ -133,7 +113,7 @@ struct Layout3 {
     int64_t npk;        // packed bricks per plane block
     int64_t per_z;      // bricks per plane block
 };
-inline __host__ __device__ Layout3 layout_3d(const Geom& g, int construction, int waves)
+inline Layout3 layout_3d(const Geom& g, int construction, int waves)
 {
     Layout3 y = {};
     const int64_t cw = (int64_t)kLaneCols * waves;
@@ -266,19 +246,18 @@ struct BatchImage {
     Geom g;
     int32_t ndim, dtype;
     int32_t auto_range;   // parameters come from the min/max keys mm[2*owner], mm[2*owner+1]
-    int32_t nxc;          // x-chunks of 63 * wpb position columns
-    int32_t nyb;          // row blocks (3D: kRows3 rows; 2D: `depth` rows)
-    int32_t wpb;          // waves per brick; a workgroup works on kBatchWaves / wpb bricks side by side
     int32_t sign;         // +1, or -1: the volume's histogram enters its image's rows negated
     int32_t owner;        // the image whose output, range and partial rows the volume uses
-    int64_t depth;        // planes (3D) or rows (2D) per brick
-    int64_t nvox;
+    Units units;          // wave tasks (3D: per plane block)
+    int64_t depth;        // planes (3D) or rows (2D) per wave task
     BinParams params;     // explicit or default range
     int64_t* out;         // the caller's output, nbins int64
 };
+static_assert(sizeof(BatchImage) <= 160, "ecc_reserve's table bound counts 160 bytes per volume");
 
-// A run of consecutive bricks [b0, b1) of one volume (an index into the images)
-// handled by one workgroup; its histogram lands in partial row `slot`.
+// A run of one volume's work handled by one workgroup; its histogram lands in
+// partial row `slot`.  In the host's schedule [b0, b1) are bricks (BatchWork), in
+// the tables of the kernel the wave tasks that they stand for.
 struct BatchSeg {
     int32_t image;
     int32_t slot;
@@ -305,7 +284,7 @@ struct BatchLaunch {
     int32_t nbins, bin_lo, width, windowed;
     int32_t grid, waves;
     int32_t pairs;              // the launch counts pair volumes (4D images)
-    uint32_t hist_stride, hist_copies, sentinel, lds_bytes;   // LDS layout, as in EccLaunch
+    uint32_t hist_stride, hist_copies, lds_bytes;   // LDS layout, as in EccLaunch
 };
 
 // Launchers (ecc_batch.hip).
@@ -319,16 +298,24 @@ hipError_t launch_mm_init(uint32_t* mm, int count, hipStream_t s);
 // Sums every image's partial rows into its out[bin_lo .. bin_lo+width) and, with
 // `scan`, prefix-sums its out[0 .. nbins).
 hipError_t launch_merge_batch(const BatchLaunch& B, bool scan, hipStream_t s);
-// Bricks of one batch image for the batched launch shape (sets nxc, nyb, depth):
-// 3D bricks of depth3 planes, 2D bricks of depth2 rows (a multiple of kChunk2).
-int64_t batch_bricks(BatchImage& im, int construction, int waves, int depth3, int depth2);
-// Voxels of one brick of a batch image whose shape batch_bricks has set (whole
-// brick, including any part outside the image).
-int64_t batch_brick_voxels(const BatchImage& im);
+// How a batch image's work is scheduled.  The schedule counts in bricks: 3D, an
+// x-chunk of 63 * wpb position columns x kRows3 rows x depth3 planes (layout_3d);
+// 2D, a chunk x depth2 rows (a multiple of kChunk2).  The kernel divides the
+// volume into wave tasks (Units) instead; a run of bricks stands for the same
+// share of the volume's wave tasks, in order.
+struct BatchWork {
+    int64_t bricks;
+    int64_t brick_voxels;   // whole brick, including any part outside the image
+    int64_t tasks;          // wave tasks of the volume
+    double cost;            // time of a brick, in vector instructions of a wave
+};
+// Sets the image's depth and units.
+BatchWork batch_work(BatchImage& im, int construction, int depth3, int depth2);
 #ifndef ECC_BATCH_WAVES
-#define ECC_BATCH_WAVES 9
+#define ECC_BATCH_WAVES 8
 #endif
 constexpr int kBatchWaves = ECC_BATCH_WAVES;   // waves per workgroup of the batched kernel
+constexpr int kBrickWaves = 9;                 // waves that a brick's width is chosen for
 
 // Launchers (ecc_kernels.hip: histogram kernels; ecc_reduce.hip: min/max,
 // parameters, merge).  All enqueue on `s` and return the launch status.

@@ -50,7 +50,7 @@ __global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(
     const HistRef H = march_hist<WIN>(hist, L.width, L.hist_stride, L.hist_copies);
     zero_hist(H, L.width);
     const uint32_t waves = blockDim.x >> 6;
-    const WinKeys W = win_keys<WIN>(L);
+    const WinKeys W = win_keys<WIN>(L.bin_lo, L.width);
     for (uint32_t task = blockIdx.x * waves + (uint32_t)wave_id(); task < L.units.tasks; task += gridDim.x * waves)
         run_march_2d<DT, CONS, WIN>(L.data, L.g, L.depth, P, W, H,
                                     block_task<DT, CONS>(L.g, L.units, L.depth, H.sm, task));

@@ -129,7 +129,7 @@ template <bool WIN>
 __device__ __forceinline__ HistRef march_hist(int32_t* hist, int32_t width, uint32_t stride, uint32_t copies)
 {
     const uint32_t base = (uint32_t)(uintptr_t)(lds_int*)hist;
-    return HistRef{hist, 0u, (uint32_t)width, base + (__lane_id() & (copies - 1u)) * stride * 4u, stride,
+    return HistRef{hist, (uint32_t)width, base + (__lane_id() & (copies - 1u)) * stride * 4u, stride,
                    (uint32_t)width + (WIN ? 1u : 0u), copies, WIN ? 1u : 0u};
 }
 __device__ __forceinline__ void lds_add(uint32_t addr, int32_t v)
@@ -142,14 +142,14 @@ struct WinKeys {
     uint32_t floor, sub, top;   // packed: max(key, floor) - sub, at most top
 };
 template <bool WIN>
-__device__ __forceinline__ WinKeys win_keys(const EccLaunch& L)
+__device__ __forceinline__ WinKeys win_keys(int32_t bin_lo, int32_t width)
 {
     WinKeys w = {};
     if constexpr (WIN) {
-        const uint32_t lo = (uint32_t)L.bin_lo;
+        const uint32_t lo = (uint32_t)bin_lo;
         w.floor = halves(lo > 0 ? lo - 1u : 0u);
         w.sub = halves((lo - 1u) & 0xFFFFu);
-        w.top = halves((uint32_t)L.width + 1u);
+        w.top = halves((uint32_t)width + 1u);
     }
     return w;
 }
@@ -191,9 +191,8 @@ __device__ __forceinline__ void add_pair(const HistRef& H, uint32_t key, uint32_
     asm("v_mad_u32_u16 %0, %1, 4, %2 op_sel:[1,0,0,0]" : "=v"(ab) : "v"(key), "v"(H.copy));
     const int32_t va = (int32_t)(sums << 28) >> 28, vb = (int32_t)(sums << 20) >> 28;
     if constexpr (WIN) {
-        const uint32_t span = H.key_span;   // bins of the window
-        if (va != 0 && (key & 0xFFFFu) - 1u < span) lds_add(aa, va);
-        if (vb != 0 && (key >> 16) - 1u < span) lds_add(ab, vb);
+        if (va != 0 && (key & 0xFFFFu) - 1u < H.span) lds_add(aa, va);
+        if (vb != 0 && (key >> 16) - 1u < H.span) lds_add(ab, vb);
     } else {
         lds_add(aa, va);
         lds_add(ab, vb);
@@ -220,7 +219,7 @@ __device__ __forceinline__ void march_3d(const EccLaunch& L, const BinParams& P,
 {
     using T = typename ValT<DT>::T;
     const uint32_t S = halves(H.sm);
-    const WinKeys W = win_keys<WIN>(L);
+    const WinKeys W = win_keys<WIN>(L.bin_lo, L.width);
     const uint32_t n0 = (uint32_t)L.g.n0;
     const uint32_t row_bytes = (uint32_t)(L.g.n2 * (int64_t)sizeof(T));
     const int64_t pass_off = (int64_t)blockIdx.y * L.pass_stride;

@@ -91,3 +91,38 @@ def test_blocks_and_units_2d(oracle_mod, cons, kind):
                 assert np.array_equal(got.cpu().numpy(), want), (cons, kind, shape, depth)
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("cons", ["vertex", "top"])
+def test_batch_shares_of_wave_tasks(oracle_mod, cons):
+    """A batch's segments are shares of each volume's wave tasks: images of one
+    task and less than one task per workgroup, uneven 2D, 3D and 4D ones together,
+    one window and several, unplanned and at plan shapes with 1 to 4 workgroups
+    per CU."""
+    from paper_2203_09087_amd import ecc
+    rng = np.random.default_rng(4300)
+    shapes = SHAPES_3D + SHAPES_2D + [(3, 4, 7, 64), (2, 9, 13, 130), (1, 2, 5, 3)]
+    ctx = ecc.Context(0, cons)
+    try:
+        for kind in ("u8", "u16wide", "f32"):
+            drawn = [draw_image(rng, s, kind) for s in shapes]
+            nbins, r = drawn[0][1], drawn[0][2]
+            hosts = [d[0] for d in drawn]
+            devs = [to_dev(h) for h in hosts]
+            say(f"case: batch {cons} {kind} {len(hosts)} images nbins={nbins}")
+            want = [oracle_mod.ecc(h, nbins, cons, value_range=r, threads=8) for h in hosts]
+            got = ctx.compute_batch(devs, nbins, value_ranges=[r] * len(devs))
+            torch.cuda.synchronize()
+            for h, g, w in zip(hosts, got, want):
+                assert np.array_equal(g.cpu().numpy(), w), (cons, kind, h.shape)
+            plan = ctx.plan_batch(devs, nbins, [r] * len(devs))
+            plan.autotune(1)
+            for o in plan.outs:
+                o.fill_(-1)
+            plan.launch()
+            torch.cuda.synchronize()
+            for h, g, w in zip(hosts, plan.outs, want):
+                assert np.array_equal(g.cpu().numpy(), w), (cons, kind, h.shape, "plan")
+            plan.close()
+    finally:
+        ctx.close()
