@@ -3,7 +3,7 @@
 // Validates every argument before anything is enqueued, resolves the binning
 // parameters (on the host for explicit ranges, on the device for AUTO ranges),
 // owns the context's scratch memory, and enqueues the kernel sequence
-//     [minmax -> params]  ->  hist (per LDS bin window) -> reduce  ->  scan
+//     [minmax -> params]  ->  hist (per LDS bin window)  ->  merge
 // on the caller's stream.
 #include <stdio.h>
 #include <string.h>
@@ -302,7 +302,7 @@ struct Sizes {
     int64_t depth;
     int32_t window;
     uint32_t hist_stride, hist_copies, lds_bytes;   // LDS layout of the histogram kernel
-    size_t off_params, off_counters, off_mm, off_level2, off_partials, total;
+    size_t off_params, off_counters, off_mm, off_carry, off_partials, total;
 };
 
 // Launch shape of the main kernel for one image:
@@ -421,8 +421,8 @@ Sizes plan_sizes(const ecc_ctx* ctx, const Job& j, int32_t nbins, const ecc_laun
     s.off_counters = 0;   // fixed place, shared with the batch layout (never overwritten)
     s.off_params = kCounterBytes;
     s.off_mm = s.off_params + align_up(sizeof(ecc::BinParams));
-    s.off_level2 = s.off_mm + align_up((size_t)(kMinmaxBlocks + 1) * 2 * sizeof(uint32_t));
-    s.off_partials = s.off_level2 + align_up(ecc::kLevel2Words * sizeof(int64_t));
+    s.off_carry = s.off_mm + align_up((size_t)(kMinmaxBlocks + 1) * 2 * sizeof(uint32_t));
+    s.off_partials = s.off_carry + align_up((size_t)s.grid * sizeof(int32_t));
     s.total = s.off_partials + align_up((size_t)s.grid * (size_t)s.window * sizeof(int32_t));
     return s;
 }
@@ -517,11 +517,11 @@ ecc_status call_scratch(ecc_ctx* ctx, const Job& j, bool no_alloc, Sizes& sz, ch
 // which a later merge sums.  pdev: binning
 // parameters on the device (AUTO), else the host parameters of j.  Planes
 // [0, z_own) of j's planes are counted; they are planes z_base.. of a volume
-// of n0_global planes.  accumulate: add the VCEC to out instead of writing it;
-// scan: prefix-sum out after the last window.
+// of n0_global planes.  accumulate: add the ECC to out instead of writing it
+// (the rows are prefix-summed, so ECCs of passes and slabs add up).
 ecc_status enqueue_hist(ecc_ctx* ctx, char* base, const Job& j, int32_t nbins, hipStream_t stream, const Sizes& sz,
                         const ecc::BinParams* pdev, int64_t z_own, int64_t z_base, int64_t n0_global,
-                        bool accumulate, bool scan, int sign = 1, bool pass_only = false, bool pass_add = false)
+                        bool accumulate, int sign = 1, bool pass_only = false, bool pass_add = false)
 {
     uint32_t* counters = (uint32_t*)(base + sz.off_counters);
     ecc::EccLaunch L;
@@ -548,6 +548,7 @@ ecc_status enqueue_hist(ecc_ctx* ctx, char* base, const Job& j, int32_t nbins, h
     L.flush_sign = sign;
     L.out = j.out;
     L.counter = counters;
+    L.carry = (int32_t*)(base + sz.off_carry);
     L.fused = 0;
     L.hist_stride = sz.hist_stride;
     L.hist_copies = sz.hist_copies;
@@ -564,9 +565,9 @@ ecc_status enqueue_hist(ecc_ctx* ctx, char* base, const Job& j, int32_t nbins, h
     }
     L.flush_add = 0;
     L.flush_sign = 1;
-    if (!accumulate && scan && sign > 0 && L.npass == 1 && sz.window >= nbins &&
+    if (!accumulate && sign > 0 && L.npass == 1 && sz.window >= nbins &&
         (int64_t)L.grid * nbins <= ecc::kFusedMergeWords) {
-        // few rows: the histogram kernel's last workgroup merges and scans them
+        // few rows: the histogram kernel's last workgroup merges them
         L.bin_lo = 0;
         L.width = nbins;
         L.fused = 1;
@@ -577,12 +578,17 @@ ecc_status enqueue_hist(ecc_ctx* ctx, char* base, const Job& j, int32_t nbins, h
     for (int32_t b0 = 0; b0 < nbins; b0 += sz.window) {
         L.bin_lo = b0;
         L.width = std::min<int32_t>(sz.window, nbins - b0);
-        const bool last = b0 + L.width >= nbins;
         if ((e = timed_launch(ctx, launch_l)) != hipSuccess)
             return hip_fail(ctx, e, "ecc launch");
-        if ((e = ecc::launch_merge(L.partials, L.grid * L.npass, L.width, L.bin_lo, (int64_t*)(base + sz.off_level2),
-                                   j.out, nbins, counters, accumulate, scan && last, sign, stream)) != hipSuccess)
-            return hip_fail(ctx, e, "merge launch");
+        ecc::MergeArgs A = {};
+        A.partials = L.partials;
+        A.rows = L.grid * L.npass;
+        A.out = j.out;
+        A.width = L.width;
+        A.bin_lo = L.bin_lo;
+        A.accumulate = accumulate ? 1 : 0;
+        A.sign = sign;
+        if ((e = ecc::launch_merge(A, stream)) != hipSuccess) return hip_fail(ctx, e, "merge launch");
     }
     return ECC_OK;
 }
@@ -605,7 +611,7 @@ ecc_status enqueue_one(ecc_ctx* ctx, const Job& j, int32_t nbins, hipStream_t st
         if ((e = ecc::launch_params_from_minmax(mm, blocks, j.dtype, nbins, pdev, stream)) != hipSuccess)
             return hip_fail(ctx, e, "params launch");
     }
-    return enqueue_hist(ctx, base, j, nbins, stream, sz, pdev, j.g.n0, 0, j.g.n0, false, true);
+    return enqueue_hist(ctx, base, j, nbins, stream, sz, pdev, j.g.n0, 0, j.g.n0, false);
 }
 
 // An image of four or more dimensions as signed 3D passes.  The cells of a
@@ -619,15 +625,14 @@ ecc_status enqueue_one(ecc_ctx* ctx, const Job& j, int32_t nbins, hipStream_t st
 // Above four dimensions it is applied one axis at a time, and the max (min) of
 // two hyperplanes of a reduced axis is written into a buffer of that axis in
 // the scratch, whose hyperplanes the next axis then reads.  Every pass adds
-// into (or subtracts from) the caller's output, the last one scans it.  The
-// binning parameters are the whole image's.
+// into (or subtracts from) the caller's output.  The binning parameters are the whole image's.
 
 // The 3D passes of one 4D image or 4D part (at img4, nw hyperplanes of the
 // shape of h), each times `outer`; the first part writes out, the others add
-// to it, and the last one scans it.
+// to it.
 ecc_status enqueue_4d_part(ecc_ctx* ctx, char* base, const Sizes& sz, Job h, const char* img4, int64_t nw,
                            const ecc::BinParams* pdev, int32_t nbins, hipStream_t stream, int outer, bool first,
-                           bool last, int64_t w_first = 0, int64_t nw_all = -1, int64_t n_own = -1)
+                           int64_t w_first = 0, int64_t nw_all = -1, int64_t n_own = -1)
 {
     // img4 holds hyperplanes w_first .. of a 4D image of nw_all hyperplanes (all
     // nw of them unless a streamed slab); the terms of its own n_own hyperplanes
@@ -690,9 +695,8 @@ ecc_status enqueue_4d_part(ecc_ctx* ctx, char* base, const Sizes& sz, Job h, con
     // voxels per launch, and a voxel adds at most 8 in absolute value.
     const int64_t bricks = ecc::wg_bricks(3, ctx->construction, h.g, sz.waves, sz.depth);
     const int64_t brick_vox = 2 * ecc::kLaneCols * sz.waves * ecc::kStripRows * sz.depth;
-    int64_t nlaunch = 0, per_row = 0;
+    int64_t per_row = 0;
     for_launches([&](int64_t, int64_t, int, bool, int64_t gx) {
-        ++nlaunch;
         per_row += (bricks + gx - 1) / gx * brick_vox;
         return ECC_OK;
     });
@@ -707,16 +711,20 @@ ecc_status enqueue_4d_part(ecc_ctx* ctx, char* base, const Sizes& sz, Job h, con
         Sizes s = sz;
         s.grid = (int)gx;
         const ecc_status r = enqueue_hist(ctx, base, p, nbins, stream, s, pdev, h.g.n0, 0, h.g.n0, !first || k > 0,
-                                          last && k + 1 == nlaunch, sign * outer, one_merge, k > 0);
+                                          sign * outer, one_merge, k > 0);
         ++k;
         return r;
     });
     if (st != ECC_OK) return st;
     if (one_merge) {
-        uint32_t* counters = (uint32_t*)(base + sz.off_counters);
-        const hipError_t e = ecc::launch_merge((int32_t*)(base + sz.off_partials), (int)rows, nbins, 0,
-                                               (int64_t*)(base + sz.off_level2), h.out, nbins, counters, !first,
-                                               last, 1, stream);
+        ecc::MergeArgs A = {};
+        A.partials = (int32_t*)(base + sz.off_partials);
+        A.rows = (int)rows;
+        A.out = h.out;
+        A.width = nbins;
+        A.accumulate = first ? 0 : 1;
+        A.sign = 1;
+        const hipError_t e = ecc::launch_merge(A, stream);
         if (e != hipSuccess) return hip_fail(ctx, e, "merge launch");
     }
     return ECC_OK;
@@ -767,20 +775,13 @@ ecc_status enqueue_nd(ecc_ctx* ctx, const Job& j, int32_t nbins, hipStream_t str
     }
     const bool vertex = ctx->construction == ECC_VERTEX;
     auto single_sign = [&](int64_t w, int64_t n) { return vertex ? 1 : -1 + (w == 0) + (w == n - 1); };
-    // 4D parts in all: per reduced axis, its hyperplanes of nonzero sign and its pairs
-    int64_t parts = 1;
-    for (int a = 0; a + 4 < d; ++a) {
-        int64_t c = j.dims[a] - 1;
-        for (int64_t w = 0; w < j.dims[a]; ++w) c += single_sign(w, j.dims[a]) != 0;
-        parts *= c;
-    }
-    int64_t done = 0;
+    bool first = true;
     // axis a of the (d-a)-dimensional volume at vol, counted with sign
     std::function<ecc_status(int, const char*, int)> visit = [&](int a, const char* vol, int sign) -> ecc_status {
         if (a + 4 == d) {
-            const bool first = done == 0, last = done + 1 == parts;
-            ++done;
-            return enqueue_4d_part(ctx, base, sz, h, vol, j.dims[a], pdev, nbins, stream, sign, first, last);
+            const bool write = first;
+            first = false;
+            return enqueue_4d_part(ctx, base, sz, h, vol, j.dims[a], pdev, nbins, stream, sign, write);
         }
         const int64_t n = j.dims[a];
         const size_t pb = (size_t)plane_vox[a] * esize;
@@ -837,7 +838,7 @@ ecc_status ensure_staging(ecc_ctx* ctx, size_t bytes, ecc_ctx::Staging** out)
 // same in the pinned staging buffer and in device memory), followed by the
 // partial histogram rows on the device.
 struct BatchLayout {
-    size_t images, segs, wg_seg, slot_off, slots, mm, pieces, tables_end, partials, total;
+    size_t images, segs, wg_seg, slot_off, slots, mm, pieces, tables_end, carry, partials, total;
 };
 
 struct BatchGroup {
@@ -1020,7 +1021,8 @@ void build_batch_tables(int cu_count, int construction, const std::vector<Job>& 
     lay.mm = align_up(lay.slots + T.slots.size() * sizeof(int32_t));
     lay.pieces = align_up(lay.mm + T.mm.size() * sizeof(uint32_t));
     lay.tables_end = align_up(lay.pieces + T.pieces.size() * sizeof(ecc::BatchPiece));
-    lay.partials = lay.tables_end;
+    lay.carry = lay.tables_end;
+    lay.partials = align_up(lay.carry + (size_t)nseg * sizeof(int32_t));
     lay.total = lay.partials + align_up((size_t)nseg * (size_t)T.window * sizeof(int32_t));
 }
 
@@ -1065,6 +1067,8 @@ ecc_status launch_batch_kernels(ecc_ctx* ctx, const BatchTables& T, char* d, boo
     B.slots = (const int32_t*)(d + lay.slots);
     B.mm = (uint32_t*)(d + lay.mm);
     B.partials = (int32_t*)(d + lay.partials);
+    B.carry = (int32_t*)(d + lay.carry);
+    B.avg_rows = (int32_t)(T.segs.size() / (size_t)T.count);
     B.nbins = T.nbins;
     B.waves = ecc::kBatchWaves;
     B.windowed = T.window < T.nbins ? 1 : 0;
@@ -1092,7 +1096,7 @@ ecc_status launch_batch_kernels(ecc_ctx* ctx, const BatchTables& T, char* d, boo
             };
             if ((e = timed_launch(ctx, launch_b)) != hipSuccess) return hip_fail(ctx, e, "batch launch");
         }
-        if ((e = ecc::launch_merge_batch(B, b0 + B.width >= T.nbins, stream)) != hipSuccess)
+        if ((e = ecc::launch_merge_batch(B, stream)) != hipSuccess)
             return hip_fail(ctx, e, "batch merge launch");
     }
     return ECC_OK;
@@ -1235,19 +1239,13 @@ ecc_status enqueue_streamed(ecc_ctx* ctx, const Job& vol, int32_t nbins, int64_t
     // pass 2: slab k counts its own planes [k*S, k*S + n) and reads one collar
     // plane beyond them (the plane its last plane pairs with).  A 4D slab may
     // own no term (the top filtration's last hyperplane has c_w = 0 and no
-    // pair): it is skipped, and the first and last slabs with terms write and
-    // scan the output.
+    // pair): it is skipped, and the first slab with terms writes the output.
     auto has_terms = [&](int64_t z0, int64_t n) {
         if (!four || ctx->construction == ECC_VERTEX || N == 1) return true;
         const int64_t pairs = std::min<int64_t>(n, N - 1 - z0);
         return pairs > 0 || std::min<int64_t>(z0 + n, N - 1) > std::max<int64_t>(z0, 1);
     };
-    int64_t k_first = -1, k_last = -1;
-    for (int64_t k = 0; k < nslabs; ++k)
-        if (has_terms(k * S, std::min<int64_t>(S, N - k * S))) {
-            if (k_first < 0) k_first = k;
-            k_last = k;
-        }
+    bool first_slab = true;
     for (int64_t k = 0; k < nslabs; ++k) {
         const int b = (int)(k & 1);
         const int64_t z0 = k * S, n = std::min<int64_t>(S, N - z0);
@@ -1260,8 +1258,9 @@ ecc_status enqueue_streamed(ecc_ctx* ctx, const Job& vol, int32_t nbins, int64_t
             Job h = first;
             h.data = nullptr;
             if ((st = enqueue_4d_part(ctx, base, sz, h, (const char*)ctx->slab_buf[b], loaded, pdev, nbins, stream,
-                                      1, k == k_first, k == k_last, z0, N, n)) != ECC_OK)
+                                      1, first_slab, z0, N, n)) != ECC_OK)
                 return st;
+            first_slab = false;
             if ((e = hipEventRecord(ctx->consumed[b], stream)) != hipSuccess)
                 return hip_fail(ctx, e, "hipEventRecord(consumed)");
             continue;
@@ -1273,7 +1272,7 @@ ecc_status enqueue_streamed(ecc_ctx* ctx, const Job& vol, int32_t nbins, int64_t
         Sizes ssz = plan_sizes(ctx, slab, nbins);
         ssz.off_counters = sz.off_counters;   // the layout of the scratch sized above
         if (ssz.total > sz.total) ssz = sz;
-        if ((st = enqueue_hist(ctx, base, slab, nbins, stream, ssz, pdev, n, z0, N, k > 0, k == nslabs - 1)) != ECC_OK)
+        if ((st = enqueue_hist(ctx, base, slab, nbins, stream, ssz, pdev, n, z0, N, k > 0)) != ECC_OK)
             return st;
         if ((e = hipEventRecord(ctx->consumed[b], stream)) != hipSuccess)
             return hip_fail(ctx, e, "hipEventRecord(consumed)");

@@ -13,6 +13,7 @@
 #include <hip/hip_ext.h>
 
 #include "ecc_march.h"
+#include "ecc_merge.h"
 
 namespace ecc {
 
@@ -118,39 +119,11 @@ void k_ecc_batch(BatchLaunch B)
             if (PAIRS && L.data2) run_march_3d<DT, CONS, kStripRows, WIN, true>(L, P, H, K, z0, ze);
             else run_march_3d<DT, CONS, kStripRows, WIN, false>(L, P, H, K, z0, ze);
         }
-        flush_hist(H, B.partials + (size_t)uniform_u32((uint32_t)S.slot) * (size_t)B.width, B.width, false,
-                   (int)uniform_u32((uint32_t)I.sign));
+        const size_t slot = (size_t)uniform_u32((uint32_t)S.slot);
+        flush_hist(H, B.partials + slot * (size_t)B.width, B.width, false, (int)uniform_u32((uint32_t)I.sign),
+                   WIN ? B.carry + slot : nullptr, B.bin_lo == 0);
         __syncthreads();   // the histogram is read before the next segment clears it
     }
-}
-
-// Block (image i, bins y * 256 ..): out[bin_lo + j] = the sum of the image's
-// partial rows.  16 rows are loaded before they are added (rows past the last
-// re-read it and are dropped), so a wide image spread over many workgroups costs
-// a few memory latencies, not one per row.
-__global__ __launch_bounds__(kThreads) void k_merge_batch(BatchLaunch B)
-{
-    constexpr int K = 16;
-    const int i = blockIdx.x;
-    const int j = blockIdx.y * kThreads + threadIdx.x;
-    if (j >= B.width) return;
-    const int r0 = B.slot_off[i], r1 = B.slot_off[i + 1];
-    int64_t s = 0;
-    for (int base = r0; base < r1; base += K) {
-        int32_t x[K];
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-            x[k] = B.partials[(size_t)B.slots[min(base + k, r1 - 1)] * (size_t)B.width + j];
-#pragma unroll
-        for (int k = 0; k < K; ++k) s += base + k < r1 ? x[k] : 0;
-    }
-    B.images[i].out[B.bin_lo + j] = s;
-}
-
-// One block per image: out[0 .. nbins) prefix-summed in place.
-__global__ __launch_bounds__(kThreads) void k_scan_batch(BatchLaunch B)
-{
-    block_scan_inplace(B.images[blockIdx.x].out, B.nbins);
 }
 
 template <class K>
@@ -253,15 +226,20 @@ hipError_t launch_ecc_batch(const BatchLaunch& B, int construction, hipStream_t 
     return construction == CONS_TOP ? launch_batch_d<CONS_TOP>(B, s, t0, t1) : launch_batch_d<CONS_VERTEX>(B, s, t0, t1);
 }
 
-hipError_t launch_merge_batch(const BatchLaunch& B, bool scan, hipStream_t s)
+hipError_t launch_merge_batch(const BatchLaunch& B, hipStream_t s)
 {
     if (B.count <= 0) return hipSuccess;
-    const unsigned by = (unsigned)((B.width + kThreads - 1) / kThreads);
-    hipLaunchKernelGGL(k_merge_batch, dim3((unsigned)B.count, by), dim3(kThreads), 0, s, B);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || !scan) return e;
-    hipLaunchKernelGGL(k_scan_batch, dim3((unsigned)B.count), dim3(kThreads), 0, s, B);
-    return hipGetLastError();
+    MergeArgs A = {};
+    A.partials = B.partials;
+    A.slot_off = B.slot_off;
+    A.slots = B.slots;
+    A.images = B.images;
+    A.width = B.width;
+    A.bin_lo = B.bin_lo;
+    A.sign = 1;
+    // few rows per image (many images): fewer threads per bin
+    if (B.avg_rows <= 12) return launch_merge_k<4, 64>(A, B.count, s);
+    return B.width >= kWideMerge ? launch_merge_k<32, 32>(A, B.count, s) : launch_merge_k<64, 16>(A, B.count, s);
 }
 
 }  // namespace ecc

@@ -190,59 +190,6 @@ __device__ __forceinline__ void block_minmax(uint32_t& lo, uint32_t& hi)
     hi = shi[0];
 }
 
-// Inclusive prefix sum of v[0..n) by one block of kThreads threads.  The values
-// pass through LDS in chunks of kScanChunk: coalesced loads, a sequential scan
-// of kScanPer values per thread, a scan of the thread totals, coalesced stores.
-constexpr int kScanPer = 16;
-constexpr int kScanChunk = kThreads * kScanPer;
-
-__device__ __forceinline__ void block_scan_inplace(int64_t* v, int32_t n)
-{
-    __shared__ int64_t buf[kScanChunk];
-    __shared__ int64_t tot[kThreads];
-    const int t = threadIdx.x;
-    int64_t carry = 0;
-    for (int32_t base = 0; base < n; base += kScanChunk) {
-        const int m = min(kScanChunk, n - base);
-        // every load is issued before any is used (indices past the chunk
-        // re-read its last value, which is dropped)
-        int64_t x[kScanPer];
-#pragma unroll
-        for (int k = 0; k < kScanPer; ++k) x[k] = v[base + min(k * kThreads + t, m - 1)];
-#pragma unroll
-        for (int k = 0; k < kScanPer; ++k) {
-            const int i = k * kThreads + t;
-            buf[i] = i < m ? x[k] : 0;
-        }
-        __syncthreads();
-        int64_t run = 0;
-#pragma unroll
-        for (int k = 0; k < kScanPer; ++k) {
-            run += buf[t * kScanPer + k];
-            buf[t * kScanPer + k] = run;
-        }
-        tot[t] = run;
-        __syncthreads();
-        for (int off = 1; off < kThreads; off <<= 1) {
-            const int64_t add = t >= off ? tot[t - off] : 0;
-            __syncthreads();
-            tot[t] += add;
-            __syncthreads();
-        }
-        const int64_t before = carry + (t > 0 ? tot[t - 1] : 0);
-#pragma unroll
-        for (int k = 0; k < kScanPer; ++k) buf[t * kScanPer + k] += before;
-        carry += tot[kThreads - 1];
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kScanPer; ++k) {
-            const int i = k * kThreads + t;
-            if (i < m) v[base + i] = buf[i];
-        }
-        __syncthreads();
-    }
-}
-
 // ------------------------------------------------------------ wave helpers
 
 __device__ __forceinline__ uint32_t lane_id() { return __lane_id(); }
@@ -277,70 +224,40 @@ __device__ __forceinline__ bool last_to_arrive(uint32_t* counter, uint32_t total
     return last;
 }
 
-// Inclusive scan of one value per thread across the wave (lanes shift by 1, 2,
-// 4, ... 32).
-__device__ __forceinline__ int64_t wave_scan(int64_t v)
-{
-    const int lane = (int)(threadIdx.x & 63);
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const int64_t u = __shfl_up(v, off, 64);
-        if (lane >= off) v += u;
-    }
-    return v;
-}
-
 // Merge of a small single-window launch inside the histogram kernel: the last
-// workgroup to finish (all partial rows written and fenced) sums the rows into
-// int64 counts in its LDS (the histogram's space, free after the flush), scans
-// them and writes the ECC to out[0..width), then re-arms the counter.  It saves
-// the two merge launches where the rows are few enough for one workgroup.
-__device__ __forceinline__ void fused_merge_scan(int32_t* hist, const int32_t* partials, int width, int64_t* out,
-                                                 uint32_t* counter)
+// workgroup to finish (all partial rows written and fenced) sums the prefix-summed
+// rows into the ECC, then re-arms the counter.  It saves the merge launch where the
+// rows are few enough for one workgroup.
+__device__ __forceinline__ void fused_merge(int32_t* hist, const int32_t* partials, int width, int64_t* out,
+                                            uint32_t* counter)
 {
-    const uint32_t rows = gridDim.x * gridDim.y;
-    if (!last_to_arrive(counter, rows)) return;
-    __shared__ int64_t wave_tot[kMaxWaves];
+    const int rows = (int)(gridDim.x * gridDim.y);
+    if (!last_to_arrive(counter, (uint32_t)rows)) return;
+    // the rows as one flat array, 16 loads in flight per thread, added with LDS
+    // atomics into int64 counters (the histogram's space, free after the flush);
+    // element i adds to bin i mod width (tracked incrementally)
     const int bd = (int)blockDim.x, t = (int)threadIdx.x;
     uint64_t* acc = reinterpret_cast<uint64_t*>(hist);
     for (int j = t; j < width; j += bd) acc[j] = 0;
     __syncthreads();
-    // the rows as one flat array, 16 loads in flight per thread; element i adds
-    // to bin i mod width (tracked incrementally)
     constexpr int U = 16;
-    const int64_t total = (int64_t)rows * width;
+    const int total = rows * width;
     const int step = bd % width;
     int j = t % width;
-    for (int64_t i0 = t; i0 < total; i0 += (int64_t)bd * U) {
+    for (int i0 = t; i0 < total; i0 += bd * U) {
         int32_t x[U];
 #pragma unroll
-        for (int k = 0; k < U; ++k) {
-            const int64_t i = i0 + (int64_t)k * bd;
-            x[k] = i < total ? partials[i] : 0;
-        }
+        for (int k = 0; k < U; ++k) x[k] = partials[min(i0 + k * bd, total - 1)];
 #pragma unroll
         for (int k = 0; k < U; ++k) {
-            if (x[k] != 0) atomicAdd((unsigned long long*)&acc[j], (unsigned long long)(int64_t)x[k]);
+            if (i0 + k * bd < total && x[k] != 0)
+                atomicAdd((unsigned long long*)&acc[j], (unsigned long long)(int64_t)x[k]);
             j += step;
             if (j >= width) j -= width;
         }
     }
     __syncthreads();
-    // each thread scans a contiguous run of bins, then adds the runs before it
-    const int per = (width + bd - 1) / bd;
-    const int j0 = min(t * per, width), j1 = min(j0 + per, width);
-    int64_t run = 0;
-    for (int b = j0; b < j1; ++b) {
-        run += (int64_t)acc[b];
-        acc[b] = (uint64_t)run;
-    }
-    const int64_t inc = wave_scan(run);
-    const int w = t >> 6;
-    if ((t & 63) == 63) wave_tot[w] = inc;
-    __syncthreads();
-    int64_t before = inc - run;
-    for (int k = 0; k < w; ++k) before += wave_tot[k];
-    for (int b = j0; b < j1; ++b) out[b] = (int64_t)acc[b] + before;
+    for (int b = t; b < width; b += bd) out[b] = (int64_t)acc[b];
     if (t == 0) atomicExch(counter, 0u);
 }
 
@@ -363,36 +280,57 @@ __device__ __forceinline__ int32_t hist_value(const HistRef& H, int j)
     return t;
 }
 
-// Writes the workgroup histogram (negated with sign -1) to dst[0..width), or
-// adds it to what dst holds (add).
-__device__ __forceinline__ void flush_hist(const HistRef& H, int32_t* dst, int width, bool add = false,
-                                           int sign = 1)
+// Inclusive scan of one value per lane across the wave: within rows of 16 lanes,
+// then from row to row (DPP lane moves).
+__device__ __forceinline__ int32_t wave_scan32(int32_t v)
 {
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111 /* row_shr:1 */, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112 /* row_shr:2 */, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114 /* row_shr:4 */, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118 /* row_shr:8 */, 0xF, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142 /* row_bcast:15 */, 0xA, 0xF, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143 /* row_bcast:31 */, 0xC, 0xF, false);
+    return v;
+}
+
+// Prefix-sums the workgroup histogram (negated with sign -1) into its partial row
+// dst[0..width), or adds it to what dst holds (add).  With windows the row goes on
+// from the sum of the windows before (`first` window: 0), which `carry` keeps.  The
+// merge then only adds rows (ecc_merge.h).  An int32 holds every prefix: a
+// workgroup takes at most 2^27 voxels of at most 8 in absolute value.  Each wave
+// scans a run of 64-bin segments in place in LDS, then adds the runs before it.
+__device__ __forceinline__ void flush_hist(const HistRef& H, int32_t* dst, int width, bool add, int sign,
+                                           int32_t* carry, bool first)
+{
+    __shared__ int32_t run_total[kMaxWaves];
     __syncthreads();
-    if (!add) {
-        for (int j = threadIdx.x; j < width; j += blockDim.x) {
-            const int32_t t = hist_value(H, j);
-            dst[j] = sign < 0 ? -t : t;
-        }
-        return;
+    const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6), waves = (int)(blockDim.x >> 6);
+    const int segs = (width + 63) / 64, per = (segs + waves - 1) / waves;
+    const int s0 = min(w * per, segs), s1 = min(s0 + per, segs);
+    int32_t run = 0;
+    for (int s = s0; s < s1; ++s) {
+        const int j = s * 64 + lane;
+        const int32_t v = wave_scan32(j < width ? hist_value(H, j) : 0) + run;
+        if (j < width) H.hist[j + (int)H.first] = v;
+        run = __builtin_amdgcn_readlane(v, 63);
     }
-    // adding: a round of the row's old values is loaded before any is written
-    // (indices past the row re-read its last word, which is dropped)
-    constexpr int R = 8;
-    const int step = (int)blockDim.x;
-    for (int j0 = (int)threadIdx.x; j0 < width; j0 += R * step) {
-        int32_t old[R];
-#pragma unroll
-        for (int k = 0; k < R; ++k) old[k] = dst[min(j0 + k * step, width - 1)];
-#pragma unroll
-        for (int k = 0; k < R; ++k) {
-            const int j = j0 + k * step;
-            if (j < width) {
-                const int32_t t = hist_value(H, j);
-                dst[j] = old[k] + (sign < 0 ? -t : t);
-            }
+    if (lane == 0) run_total[w] = run;
+    const int32_t from = carry && !first ? *carry : 0;
+    __syncthreads();
+    int32_t before = from, total = from;
+    for (int k = 0; k < waves; ++k) {
+        before += k < w ? run_total[k] : 0;
+        total += run_total[k];
+    }
+#pragma unroll 4
+    for (int s = s0; s < s1; ++s) {
+        const int j = s * 64 + lane;
+        if (j < width) {
+            const int32_t v = H.hist[j + (int)H.first] + before;
+            dst[j] = (add ? dst[j] : 0) + (sign < 0 ? -v : v);
         }
     }
+    if (carry && threadIdx.x == 0) *carry = total;
 }
 
 // Values the whole wave shares, read back from the first lane so that the

@@ -218,11 +218,12 @@ struct EccLaunch {
     // plus y * pass_stride bytes; its histograms go to partial rows y * grid ..
     int32_t npass;
     int64_t pass_stride;
-    int32_t* partials;             // [grid * npass][width] workgroup histograms
+    int32_t* partials;             // [grid * npass][width] workgroup histograms, prefix-summed
     int32_t flush_add;             // add the workgroup histogram to its partial row (else write it)
     int32_t flush_sign;            // +1, or -1: the histogram enters its row negated
     int64_t* out;                  // the caller's output
-    uint32_t* counter;             // counters[0]: the merge's; counters[1]: the fused merge's
+    uint32_t* counter;             // the fused merge's
+    int32_t* carry;                // windows: each workgroup's sum over the windows before this one
     int32_t fused;                 // one window, few rows: the last workgroup merges and scans into out
     uint32_t hist_stride;          // LDS words between the histogram copies (lds_stride(width))
     uint32_t hist_copies;          // copies of the histogram (a power of two up to kMaxHistCopies)
@@ -281,6 +282,8 @@ struct BatchLaunch {
     const int32_t* slots;
     uint32_t* mm;               // [count][2] min/max keys of AUTO images
     int32_t* partials;          // [nslots][width]
+    int32_t* carry;             // windows: each row's sum over the windows before this one
+    int32_t avg_rows;           // partial rows per image, on average
     int32_t nbins, bin_lo, width, windowed;
     int32_t grid, waves;
     int32_t pairs;              // the launch counts pair volumes (4D images)
@@ -295,9 +298,8 @@ hipError_t launch_ecc_batch(const BatchLaunch& B, int construction, hipStream_t 
 // Sets mm[2i] = ~0, mm[2i+1] = 0 for the `count` images (a kernel, so that the
 // enqueue stays valid inside a captured graph).
 hipError_t launch_mm_init(uint32_t* mm, int count, hipStream_t s);
-// Sums every image's partial rows into its out[bin_lo .. bin_lo+width) and, with
-// `scan`, prefix-sums its out[0 .. nbins).
-hipError_t launch_merge_batch(const BatchLaunch& B, bool scan, hipStream_t s);
+// Merges every image's partial rows into its out[bin_lo .. bin_lo+width).
+hipError_t launch_merge_batch(const BatchLaunch& B, hipStream_t s);
 // How a batch image's work is scheduled.  The schedule counts in bricks: 3D, an
 // x-chunk of 63 * wpb position columns x kRows3 rows x depth3 planes (layout_3d);
 // 2D, a chunk x depth2 rows (a multiple of kChunk2).  The kernel divides the
@@ -336,19 +338,22 @@ hipError_t launch_combine(const void* a, const void* b, void* out, int64_t n, in
 hipError_t launch_params_from_minmax(const uint32_t* mm, int blocks, int dtype, int32_t nbins,
                                      BinParams* out, hipStream_t s);
 hipError_t launch_ecc(const EccLaunch& L, hipStream_t s, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
-// Sums the `rows` partial histograms into out[bin_lo..bin_lo+width) (through
-// `level2`, kLevel2Words int64 of scratch) and, with `scan`, prefix-sums
-// out[0..nbins).  counters[0] is the merge's last-block counter, which the merge
-// re-arms.
-constexpr int kMergeGroups = 32;
-// group sums (kMergeGroups x window) and per-group totals of 256-bin blocks
-constexpr size_t kLevel2Words = (size_t)kMergeGroups * (kMaxLdsBins + kMaxLdsBins / 256);
+// The merge of partial rows into out[bin_lo .. bin_lo + width) of one image or of
+// every image of a batch (ecc_merge.h).
+struct MergeArgs {
+    const int32_t* partials;       // rows of `width` bins, prefix-summed
+    int rows;                      // one image: rows 0 .. rows - 1
+    const int32_t* slot_off;       // a batch: image i has rows slots[slot_off[i] .. slot_off[i + 1])
+    const int32_t* slots;
+    const BatchImage* images;      // a batch: its images' outputs; else null, and `out`
+    int64_t* out;
+    int32_t width, bin_lo;
+    int32_t accumulate;            // add to out instead of writing it (slabs, the 3D passes of a 4D image)
+    int32_t sign;                  // -1: subtract the sums
+};
+constexpr int32_t kWideMerge = 1536;   // bins from which a merge block takes 32 of them, else 16
 constexpr int kCounterWords = 256;
-// accumulate: add to out instead of writing it (slabs of a streamed volume, the
-// 3D passes of a 4D image); sign -1: subtract the sums.
-hipError_t launch_merge(const int32_t* partials, int rows, int32_t width, int32_t bin_lo, int64_t* level2,
-                        int64_t* out, int32_t nbins, uint32_t* counters, bool accumulate, bool scan, int sign,
-                        hipStream_t s);
+hipError_t launch_merge(const MergeArgs& A, hipStream_t s);
 // Folds `blocks` min/max key pairs into the running pair acc (first: start it).
 hipError_t launch_mm_fold(const uint32_t* mm, int blocks, uint32_t* acc, bool first, hipStream_t s);
 

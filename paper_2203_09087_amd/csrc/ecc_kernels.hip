@@ -36,8 +36,10 @@ __global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(
         const Task3 K = strip_task<DT, CONS, kStripRows>(L.g, L.units, H.sm, r * waves + (uint32_t)wave_id());
         run_march_3d<DT, CONS, kStripRows, WIN, PAIR>(L, P, H, K, z0, ze);
     }
-    flush_hist(H, L.partials + ((size_t)blockIdx.y * gridDim.x + blockIdx.x) * (size_t)L.width, L.width, L.flush_add != 0, L.flush_sign);
-    if (L.fused) fused_merge_scan(hist, L.partials, L.width, L.out, L.counter + 1);
+    const size_t row = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
+    flush_hist(H, L.partials + row * (size_t)L.width, L.width, L.flush_add != 0, L.flush_sign, WIN ? L.carry + row : nullptr,
+               L.bin_lo == 0);
+    if (L.fused) fused_merge(hist, L.partials, L.width, L.out, L.counter);
 }
 
 // 2D images.  A workgroup brick is as many consecutive wave tasks (Units: 2 x 63
@@ -54,8 +56,9 @@ __global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(
     for (uint32_t task = blockIdx.x * waves + (uint32_t)wave_id(); task < L.units.tasks; task += gridDim.x * waves)
         run_march_2d<DT, CONS, WIN>(L.data, L.g, L.depth, P, W, H,
                                     block_task<DT, CONS>(L.g, L.units, L.depth, H.sm, task));
-    flush_hist(H, L.partials + (size_t)blockIdx.x * (size_t)L.width, L.width, L.flush_add != 0, L.flush_sign);
-    if (L.fused) fused_merge_scan(hist, L.partials, L.width, L.out, L.counter + 1);
+    flush_hist(H, L.partials + (size_t)blockIdx.x * (size_t)L.width, L.width, L.flush_add != 0, L.flush_sign,
+               WIN ? L.carry + blockIdx.x : nullptr, L.bin_lo == 0);
+    if (L.fused) fused_merge(hist, L.partials, L.width, L.out, L.counter);
 }
 
 }  // namespace
