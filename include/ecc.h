@@ -208,8 +208,8 @@ ecc_status ecc_compute_streamed(ecc_ctx* ctx, const ecc_image* img, int32_t nbin
  * the sum over k = 0..12, in that order from 0, of taps[k] times the neighbour
  * at offset k - 6 (border pixels repeated), every product and sum rounded once
  * in float32.  in, out: device pointers to n1 * n2 floats (row-major), out may
- * equal in; taps: HOST array of 13 floats.  The context keeps an n1 * n2 float
- * intermediate buffer.  Asynchronous on hip_stream.
+ * equal in; taps: HOST array of 13 floats.  Where out overlaps in, the context
+ * keeps an n1 * n2 float intermediate buffer.  Asynchronous on hip_stream.
  * Errors: ECC_ERR_INVALID_ARG (null pointer, n1 or n2 outside [1, 2^31], more
  * than 2^40 pixels), ECC_ERR_OUT_OF_MEMORY, ECC_ERR_DEVICE. */
 ecc_status ecc_smooth13(ecc_ctx* ctx, const float* in, float* out, int64_t n1, int64_t n2, const float* taps,

@@ -1866,6 +1866,16 @@ ecc_status ecc_smooth13(ecc_ctx* ctx, const float* in, float* out, int64_t n1, i
     if (!g.ok) return fail(ctx, ECC_ERR_DEVICE, "hipSetDevice failed");
     const size_t bytes = (size_t)n1 * (size_t)n2 * sizeof(float);
     hipError_t e;
+    ecc::Taps13 w;
+    for (int k = 0; k < 13; ++k) w.w[k] = taps[k];
+    // one launch unless the images overlap (a tile's output would overwrite what
+    // its neighbours still read)
+    const uintptr_t i0 = (uintptr_t)in, o0 = (uintptr_t)out;
+    if (i0 + bytes <= o0 || o0 + bytes <= i0) {
+        if ((e = ecc::launch_smooth13_tile(in, out, n1, n2, w, (hipStream_t)hip_stream)) != hipSuccess)
+            return hip_fail(ctx, e, "smoothing launch");
+        return ECC_OK;
+    }
     if (bytes > ctx->smooth_cap) {
         if (ctx->smooth_tmp) {
             if ((e = hipDeviceSynchronize()) != hipSuccess) return hip_fail(ctx, e, "hipDeviceSynchronize");
@@ -1879,8 +1889,6 @@ ecc_status ecc_smooth13(ecc_ctx* ctx, const float* in, float* out, int64_t n1, i
         }
         ctx->smooth_cap = bytes;
     }
-    ecc::Taps13 w;
-    for (int k = 0; k < 13; ++k) w.w[k] = taps[k];
     if ((e = ecc::launch_smooth13(in, out, (float*)ctx->smooth_tmp, n1, n2, w, (hipStream_t)hip_stream)) !=
         hipSuccess)
         return hip_fail(ctx, e, "smoothing launch");

@@ -326,6 +326,8 @@ constexpr int kBrickWaves = 9;                 // waves that a brick's width is 
 struct Taps13 {
     float w[13];
 };
+// Both passes in one launch; out must not overlap in.
+hipError_t launch_smooth13_tile(const float* in, float* out, int64_t n1, int64_t n2, const Taps13& w, hipStream_t s);
 // Rows (in -> tmp), then columns (tmp -> out) of an n1 x n2 float image; out may be in.
 hipError_t launch_smooth13(const float* in, float* out, float* tmp, int64_t n1, int64_t n2, const Taps13& w,
                            hipStream_t s);
