@@ -302,7 +302,7 @@ struct Sizes {
     int64_t depth;
     int32_t window;
     uint32_t hist_stride, hist_copies, lds_bytes;   // LDS layout of the histogram kernel
-    size_t off_params, off_counters, off_mm, off_carry, off_partials, total;
+    size_t off_counters, off_mm, off_carry, off_partials, total;
 };
 
 // Launch shape of the main kernel for one image:
@@ -419,8 +419,7 @@ Sizes plan_sizes(const ecc_ctx* ctx, const Job& j, int32_t nbins, const ecc_laun
     grid = std::max<int64_t>(grid, std::min<int64_t>(bricks, (j.nvox >> 27) + 1));
     s.grid = (int)std::max<int64_t>(grid, 1);
     s.off_counters = 0;   // fixed place, shared with the batch layout (never overwritten)
-    s.off_params = kCounterBytes;
-    s.off_mm = s.off_params + align_up(sizeof(ecc::BinParams));
+    s.off_mm = kCounterBytes;
     s.off_carry = s.off_mm + align_up((size_t)(kMinmaxBlocks + 1) * 2 * sizeof(uint32_t));
     s.off_partials = s.off_carry + align_up((size_t)s.grid * sizeof(int32_t));
     s.total = s.off_partials + align_up((size_t)s.grid * (size_t)s.window * sizeof(int32_t));
@@ -510,17 +509,23 @@ ecc_status call_scratch(ecc_ctx* ctx, const Job& j, bool no_alloc, Sizes& sz, ch
     return ECC_OK;
 }
 
+// Min/max key pairs of an image with an AUTO range, on the device (mm null: none).
+struct AutoRange {
+    const uint32_t* mm = nullptr;
+    int32_t count = 0;
+};
+
 // The histogram launches (and merges) of one image or slab, with the scratch
 // laid out as `sz` from `base`.  With pass_only
 // (one LDS window only) just the histogram kernel runs, writing (or with
 // pass_add adding) its workgroup histograms times `sign` into the partial rows,
-// which a later merge sums.  pdev: binning
-// parameters on the device (AUTO), else the host parameters of j.  Planes
+// which a later merge sums.  range: the
+// image's min/max keys (AUTO), else the host parameters of j hold.  Planes
 // [0, z_own) of j's planes are counted; they are planes z_base.. of a volume
 // of n0_global planes.  accumulate: add the ECC to out instead of writing it
 // (the rows are prefix-summed, so ECCs of passes and slabs add up).
 ecc_status enqueue_hist(ecc_ctx* ctx, char* base, const Job& j, int32_t nbins, hipStream_t stream, const Sizes& sz,
-                        const ecc::BinParams* pdev, int64_t z_own, int64_t z_base, int64_t n0_global,
+                        const AutoRange& range, int64_t z_own, int64_t z_base, int64_t n0_global,
                         bool accumulate, int sign = 1, bool pass_only = false, bool pass_add = false)
 {
     uint32_t* counters = (uint32_t*)(base + sz.off_counters);
@@ -531,7 +536,8 @@ ecc_status enqueue_hist(ecc_ctx* ctx, char* base, const Job& j, int32_t nbins, h
     L.dtype = j.dtype;
     L.construction = ctx->construction;
     L.g = j.g;
-    L.params_dev = pdev;
+    L.mm = range.mm;
+    L.mm_count = range.count;
     L.params = host_params(j, nbins);
     L.windowed = sz.window < nbins ? 1 : 0;
     L.grid = sz.grid;
@@ -600,18 +606,16 @@ ecc_status enqueue_one(ecc_ctx* ctx, const Job& j, int32_t nbins, hipStream_t st
     char* base = nullptr;
     ecc_status st = call_scratch(ctx, j, no_alloc, sz, &base);
     if (st != ECC_OK) return st;
-    ecc::BinParams* pdev = nullptr;
+    AutoRange range;
     hipError_t e;
     if (j.range_mode == ECC_RANGE_AUTO) {
         uint32_t* mm = (uint32_t*)(base + sz.off_mm);
-        pdev = (ecc::BinParams*)(base + sz.off_params);
         const int blocks = (int)std::min<int64_t>(kMinmaxBlocks, (j.nvox + 4095) / 4096);
         if ((e = ecc::launch_minmax(j.data, j.dtype, j.nvox, mm, blocks, stream)) != hipSuccess)
             return hip_fail(ctx, e, "minmax launch");
-        if ((e = ecc::launch_params_from_minmax(mm, blocks, j.dtype, nbins, pdev, stream)) != hipSuccess)
-            return hip_fail(ctx, e, "params launch");
+        range = AutoRange{mm, blocks};
     }
-    return enqueue_hist(ctx, base, j, nbins, stream, sz, pdev, j.g.n0, 0, j.g.n0, false);
+    return enqueue_hist(ctx, base, j, nbins, stream, sz, range, j.g.n0, 0, j.g.n0, false);
 }
 
 // An image of four or more dimensions as signed 3D passes.  The cells of a
@@ -631,7 +635,7 @@ ecc_status enqueue_one(ecc_ctx* ctx, const Job& j, int32_t nbins, hipStream_t st
 // shape of h), each times `outer`; the first part writes out, the others add
 // to it.
 ecc_status enqueue_4d_part(ecc_ctx* ctx, char* base, const Sizes& sz, Job h, const char* img4, int64_t nw,
-                           const ecc::BinParams* pdev, int32_t nbins, hipStream_t stream, int outer, bool first,
+                           const AutoRange& range, int32_t nbins, hipStream_t stream, int outer, bool first,
                            int64_t w_first = 0, int64_t nw_all = -1, int64_t n_own = -1)
 {
     // img4 holds hyperplanes w_first .. of a 4D image of nw_all hyperplanes (all
@@ -710,7 +714,7 @@ ecc_status enqueue_4d_part(ecc_ctx* ctx, char* base, const Sizes& sz, Job h, con
         p.pass_stride = (int64_t)hv * (int64_t)esize;
         Sizes s = sz;
         s.grid = (int)gx;
-        const ecc_status r = enqueue_hist(ctx, base, p, nbins, stream, s, pdev, h.g.n0, 0, h.g.n0, !first || k > 0,
+        const ecc_status r = enqueue_hist(ctx, base, p, nbins, stream, s, range, h.g.n0, 0, h.g.n0, !first || k > 0,
                                           sign * outer, one_merge, k > 0);
         ++k;
         return r;
@@ -762,16 +766,14 @@ ecc_status enqueue_nd(ecc_ctx* ctx, const Job& j, int32_t nbins, hipStream_t str
     char* base = nullptr;
     ecc_status st = call_scratch(ctx, h, no_alloc, sz, &base);
     if (st != ECC_OK) return st;
-    ecc::BinParams* pdev = nullptr;
+    AutoRange range;
     hipError_t e;
     if (j.range_mode == ECC_RANGE_AUTO) {
         uint32_t* mm = (uint32_t*)(base + sz.off_mm);
-        pdev = (ecc::BinParams*)(base + sz.off_params);
         const int blocks = (int)std::min<int64_t>(kMinmaxBlocks, (j.nvox + 4095) / 4096);
         if ((e = ecc::launch_minmax(j.data, j.dtype, j.nvox, mm, blocks, stream)) != hipSuccess)
             return hip_fail(ctx, e, "minmax launch");
-        if ((e = ecc::launch_params_from_minmax(mm, blocks, j.dtype, nbins, pdev, stream)) != hipSuccess)
-            return hip_fail(ctx, e, "params launch");
+        range = AutoRange{mm, blocks};
     }
     const bool vertex = ctx->construction == ECC_VERTEX;
     auto single_sign = [&](int64_t w, int64_t n) { return vertex ? 1 : -1 + (w == 0) + (w == n - 1); };
@@ -781,7 +783,7 @@ ecc_status enqueue_nd(ecc_ctx* ctx, const Job& j, int32_t nbins, hipStream_t str
         if (a + 4 == d) {
             const bool write = first;
             first = false;
-            return enqueue_4d_part(ctx, base, sz, h, vol, j.dims[a], pdev, nbins, stream, sign, write);
+            return enqueue_4d_part(ctx, base, sz, h, vol, j.dims[a], range, nbins, stream, sign, write);
         }
         const int64_t n = j.dims[a];
         const size_t pb = (size_t)plane_vox[a] * esize;
@@ -1213,12 +1215,11 @@ ecc_status enqueue_streamed(ecc_ctx* ctx, const Job& vol, int32_t nbins, int64_t
             return hip_fail(ctx, e, "hipEventRecord(consumed)");
     const char* host = (const char*)vol.data;
     char* base = (char*)ctx->ws;
-    ecc::BinParams* pdev = nullptr;
+    AutoRange range;
     if (vol.range_mode == ECC_RANGE_AUTO) {
         // pass 1: min/max keys of every slab's own planes, folded on the device
         uint32_t* mm = (uint32_t*)(base + sz.off_mm);
         uint32_t* acc = mm + 2 * kMinmaxBlocks;
-        pdev = (ecc::BinParams*)(base + sz.off_params);
         for (int64_t k = 0; k < nslabs; ++k) {
             const int b = (int)(k & 1);
             const int64_t z0 = k * S, n = std::min<int64_t>(S, N - z0);
@@ -1233,8 +1234,7 @@ ecc_status enqueue_streamed(ecc_ctx* ctx, const Job& vol, int32_t nbins, int64_t
             if ((e = hipEventRecord(ctx->consumed[b], stream)) != hipSuccess)
                 return hip_fail(ctx, e, "hipEventRecord(consumed)");
         }
-        if ((e = ecc::launch_params_from_minmax(acc, 1, vol.dtype, nbins, pdev, stream)) != hipSuccess)
-            return hip_fail(ctx, e, "params launch");
+        range = AutoRange{acc, 1};
     }
     // pass 2: slab k counts its own planes [k*S, k*S + n) and reads one collar
     // plane beyond them (the plane its last plane pairs with).  A 4D slab may
@@ -1257,7 +1257,7 @@ ecc_status enqueue_streamed(ecc_ctx* ctx, const Job& vol, int32_t nbins, int64_t
         if (four) {
             Job h = first;
             h.data = nullptr;
-            if ((st = enqueue_4d_part(ctx, base, sz, h, (const char*)ctx->slab_buf[b], loaded, pdev, nbins, stream,
+            if ((st = enqueue_4d_part(ctx, base, sz, h, (const char*)ctx->slab_buf[b], loaded, range, nbins, stream,
                                       1, first_slab, z0, N, n)) != ECC_OK)
                 return st;
             first_slab = false;
@@ -1272,7 +1272,7 @@ ecc_status enqueue_streamed(ecc_ctx* ctx, const Job& vol, int32_t nbins, int64_t
         Sizes ssz = plan_sizes(ctx, slab, nbins);
         ssz.off_counters = sz.off_counters;   // the layout of the scratch sized above
         if (ssz.total > sz.total) ssz = sz;
-        if ((st = enqueue_hist(ctx, base, slab, nbins, stream, ssz, pdev, n, z0, N, k > 0)) != ECC_OK)
+        if ((st = enqueue_hist(ctx, base, slab, nbins, stream, ssz, range, n, z0, N, k > 0)) != ECC_OK)
             return st;
         if ((e = hipEventRecord(ctx->consumed[b], stream)) != hipSuccess)
             return hip_fail(ctx, e, "hipEventRecord(consumed)");

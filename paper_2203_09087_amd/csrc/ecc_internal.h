@@ -201,8 +201,9 @@ struct EccLaunch {
     int ndim, dtype, construction;
     Geom g;
     Units units;                   // units_3d or units_2d of g
-    const BinParams* params_dev;   // non-null: read the parameters from device memory
-    BinParams params;              // used when params_dev is null
+    const uint32_t* mm;            // non-null: AUTO range, the mm_count min/max key pairs of the image
+    int32_t mm_count;
+    BinParams params;              // used when mm is null (nbins always)
     int32_t bin_lo, width;
     int32_t windowed;              // nbins > width: skip bins outside the window
     int32_t grid;                  // number of workgroups
@@ -337,8 +338,6 @@ hipError_t launch_minmax(const void* data, int dtype, int64_t nvox, uint32_t* mm
 // taken as the largest float (the reduction of images of 5+ dimensions).
 hipError_t launch_combine(const void* a, const void* b, void* out, int64_t n, int dtype, bool take_max,
                           hipStream_t s);
-hipError_t launch_params_from_minmax(const uint32_t* mm, int blocks, int dtype, int32_t nbins,
-                                     BinParams* out, hipStream_t s);
 hipError_t launch_ecc(const EccLaunch& L, hipStream_t s, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
 // The merge of partial rows into out[bin_lo .. bin_lo + width) of one image or of
 // every image of a batch (ecc_merge.h).

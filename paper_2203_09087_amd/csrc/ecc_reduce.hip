@@ -1,5 +1,5 @@
 // ecc_reduce.hip -- the small kernels around the histogram kernels of one
-// image: the AUTO-range min/max pass and its binning parameters, and the merge of
+// image: the AUTO-range min/max pass and the merge of
 // workgroup histograms (ecc_merge.h).
 #include "ecc_merge.h"
 
@@ -50,18 +50,6 @@ __global__ __launch_bounds__(kThreads) void k_combine(const void* a, const void*
             z[i] = MAX ? (u > v ? u : v) : (u < v ? u : v);
         }
     }
-}
-
-__global__ __launch_bounds__(kThreads) void k_params(const uint32_t* mm, int blocks, int dtype,
-                                                     int32_t nbins, BinParams* out)
-{
-    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
-    for (int i = threadIdx.x; i < blocks; i += kThreads) {
-        lo = min(lo, mm[2 * i]);
-        hi = max(hi, mm[2 * i + 1]);
-    }
-    block_minmax(lo, hi);
-    if (threadIdx.x == 0) *out = params_from_keys(lo, hi, dtype, nbins);
 }
 
 // Folds the per-block min/max keys of one slab into a running pair acc[0..1]
@@ -119,13 +107,5 @@ hipError_t launch_combine(const void* a, const void* b, void* out, int64_t n, in
     }
     return hipGetLastError();
 }
-
-hipError_t launch_params_from_minmax(const uint32_t* mm, int blocks, int dtype, int32_t nbins,
-                                     BinParams* out, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_params, dim3(1), dim3(kThreads), 0, s, mm, blocks, dtype, nbins, out);
-    return hipGetLastError();
-}
-
 
 }  // namespace ecc

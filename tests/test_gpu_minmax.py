@@ -57,3 +57,30 @@ def test_batch_auto_range_sees_every_element(oracle_mod, dtype, sizes):
             assert np.array_equal(g.cpu().numpy(), want), h.shape
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("shape", [(1, 1), (1, 4096), (1, 4097), (3, 5, 700), (2050, 2049), (3, 2, 70, 90)])
+def test_workgroups_fold_the_key_pairs(oracle_mod, shape):
+    """A single image's AUTO range: 1 to 1024 key pairs, folded by workgroups of
+    one to eight waves, the extremes at either end of the image."""
+    from paper_2203_09087_amd import ecc
+    rng = np.random.default_rng(78)
+    n = int(np.prod(shape))
+    for cons in ("vertex", "top"):
+        ctx = ecc.Context(0, cons)
+        try:
+            for ends in ((0, n - 1), (n - 1, 0)):
+                a = rng.random(n).astype(np.float32)
+                a[ends[1]] = 4.0
+                a[ends[0]] = -2.0
+                img = a.reshape(shape)
+                d = torch.from_numpy(img).cuda()
+                say(f"case: AUTO {cons} {shape} extremes at {ends}")
+                want = oracle_mod.ecc(img, 700, cons, value_range="auto", threads=8)
+                for waves in (0, 1, 3):
+                    ctx.set_launch_shape(d, 700, waves=waves)
+                    got = ctx.compute(d, 700, value_range="auto")
+                    torch.cuda.synchronize()
+                    assert np.array_equal(got.cpu().numpy(), want), (cons, shape, ends, waves)
+        finally:
+            ctx.close()
