@@ -221,9 +221,10 @@ ecc_status ecc_smooth13(ecc_ctx* ctx, const float* in, float* out, int64_t n1, i
  * workgroup brick, resident workgroups per CU aimed for, `window`, the bins
  * one pass counts in LDS (Sec. 4.3's block-shared histogram; fewer than nbins
  * makes several passes over the image, each with less LDS; 0: all of nbins up to
- * 4096), and `copies`, the copies of that histogram the lanes of a wave spread
- * their adds over (2, 4 or 8; 0: 8 up to 256 bins, 4 up to 1024, else 2).  `ms`
- * is the mean time of one call measured by ecc_autotune. */
+ * 16384, of 8-bit data up to 4096), and `copies`, the copies of that histogram the lanes of a wave spread
+ * their adds over (2, 4 or 8, fewer where the LDS does not hold them; 0: 8 up to
+ * 256 bins, 4 up to 1024, 2 up to 8192, else 1).  `ms` is the mean time of one call
+ * measured by ecc_autotune. */
 typedef struct {
     int32_t waves;
     int32_t wgs_per_cu;

@@ -349,20 +349,24 @@ void pick_shape(const ecc_ctx* ctx, const Job& j, const ecc_launch_shape* tuned,
     static const double eff[9] = {0.2, 0.40, 0.66, 0.80, 0.87, 0.91, 0.94, 0.96, 0.97};
     const double most = flat ? std::ceil(tasks * std::ceil(length / dmin)) : tasks;   // waves with work
     const int forced_w =
-        tuned && tuned->waves > 0 ? (int)std::min<double>(std::min<int>(tuned->waves, ecc::kMaxWaves), most) : 0;
+        tuned && tuned->waves > 0 ? (int)std::min<double>(std::min<int>(tuned->waves, ecc::kMaxSetWaves), most) : 0;
     double forced_d = 0.0;
     if (tuned && tuned->depth > 0)
         forced_d = flat ? (double)((std::min<int64_t>(tuned->depth, 4096) + ecc::kChunk2 - 1) / ecc::kChunk2 * ecc::kChunk2)
                         : (double)std::min<int64_t>(tuned->depth, 256);
+    // wide windows are cleared and flushed by more waves than a small image has work for
+    const double least = s.window >= ecc::kMaxLdsBins ? 8 : (s.window >= 1024 ? 4 : 1);
     double best = HUGE_VAL;
     s.waves = 0;
-    for (int w : {8, 4, 2, 1}) {
+    for (int w : {16, 8, 4, 2, 1}) {
+        if (w == 16 && s.window <= ecc::kMaxLdsBins) continue;   // only where wide rows make workgroups costly
         if (forced_w) w = forced_w;
-        else if (w > most || (w < 4 && s.waves > 0)) continue;
+        else if (w > std::max(most, least) || (w < 4 && s.waves > 0)) continue;
         // bricks of a block of rows (2D, fractional: blocks share bricks) or planes
         const double per_block = flat ? tasks / w : std::ceil(tasks / w);
         const int rmax = resident(w);
-        int r0 = 1, r1 = std::min(rmax, 6);
+        // at most the rows that ecc_reserve's bound holds (6 per CU of kMaxLdsBins bins)
+        int r0 = 1, r1 = std::max(1, std::min(rmax, 6 * ecc::kMaxLdsBins / std::max(s.window, ecc::kMaxLdsBins)));
         if (tuned && tuned->wgs_per_cu > 0) r0 = r1 = std::min(tuned->wgs_per_cu, rmax);
         for (int r = r0; r <= r1; ++r) {
             const double gx = std::max(1.0, std::floor(cus * r / npass));   // workgroups per pass
@@ -391,6 +395,9 @@ void pick_shape(const ecc_ctx* ctx, const Job& j, const ecc_launch_shape* tuned,
     }
 }
 
+// LDS words a histogram may take (128 KB and the copies' offsets, of a CU's 160 KB).
+constexpr uint32_t kMaxLdsWords = (128 << 10) / 4 + 8 * 40;
+
 // The default launch shape of an image (waves 0 / depth 0 / wgs 0 in a forced
 // shape mean "default" for that field).
 Sizes plan_sizes(const ecc_ctx* ctx, const Job& j, int32_t nbins, const ecc_launch_shape* force = nullptr)
@@ -402,13 +409,18 @@ Sizes plan_sizes(const ecc_ctx* ctx, const Job& j, int32_t nbins, const ecc_laun
         if (it != ctx->tuned.end()) tuned = &it->second;
     }
     const int cons = ctx->construction;
-    // bins per LDS pass: all of them up to kMaxLdsBins, or fewer when tuned so
-    s.window = std::min<int32_t>(nbins, ecc::kMaxLdsBins);
+    // bins per LDS pass: all of them up to kWideLdsBins, or fewer when tuned so.  Up
+    // to kMaxLdsBins for images so large that the rows they need at least would not
+    // fit the fixed scratch of ecc_compute_noalloc, and for 8-bit data (256 levels:
+    // more bins than that are only asked for in tests of the passes).
+    const bool wide = j.dtype != ECC_U8 && j.nvox < (int64_t(1) << 34);
+    s.window = std::min<int32_t>(nbins, wide ? ecc::kWideLdsBins : ecc::kMaxLdsBins);
     if (tuned && tuned->window > 0) s.window = std::min<int32_t>(s.window, tuned->window);
     const bool windowed = s.window < nbins;
     s.hist_stride = ecc::lds_stride(s.window);
     s.hist_copies = ecc::hist_copies(s.window);
     if (tuned && tuned->copies > 0) s.hist_copies = (uint32_t)tuned->copies;
+    while (s.hist_copies > 1 && s.hist_copies * s.hist_stride > kMaxLdsWords) s.hist_copies /= 2;
     s.lds_bytes = 4u * s.hist_copies * s.hist_stride;
     auto resident = [&](int waves) {
         return ecc::resident_wgs_per_cu(j.ndim, j.dtype, cons, windowed, waves, s.lds_bytes);
@@ -572,7 +584,7 @@ ecc_status enqueue_hist(ecc_ctx* ctx, char* base, const Job& j, int32_t nbins, h
     L.flush_add = 0;
     L.flush_sign = 1;
     if (!accumulate && sign > 0 && L.npass == 1 && sz.window >= nbins &&
-        (int64_t)L.grid * nbins <= ecc::kFusedMergeWords) {
+        (int64_t)L.grid * nbins <= ecc::kFusedMergeWords && sz.lds_bytes >= 8u * (uint32_t)nbins) {
         // few rows: the histogram kernel's last workgroup merges them
         L.bin_lo = 0;
         L.width = nbins;
@@ -1683,7 +1695,7 @@ ecc_status ecc_set_launch_shape(ecc_ctx* ctx, const ecc_image* img, int32_t nbin
     if (!ctx) return ECC_ERR_INVALID_ARG;
     ctx->err.clear();
     if (!img || !shape) return fail(ctx, ECC_ERR_INVALID_ARG, "ecc_set_launch_shape: null pointer");
-    if (shape->waves > ecc::kMaxWaves || shape->wgs_per_cu > 16 || shape->depth > 4096 ||
+    if (shape->waves > ecc::kMaxSetWaves || shape->wgs_per_cu > 16 || shape->depth > 4096 ||
         shape->window > ecc::kMaxLdsBins ||
         (shape->copies != 0 && shape->copies != 2 && shape->copies != 4 && shape->copies != 8))
         return fail(ctx, ECC_ERR_INVALID_ARG,
@@ -1735,7 +1747,7 @@ ecc_status ecc_autotune(ecc_ctx* ctx, const ecc_image* img, int32_t nbins, int32
     std::vector<ecc_launch_shape> cand;
     auto add = [&](int waves, int64_t depth, int wgs, int32_t window = 0, int32_t copies = 0) {
         ecc_launch_shape c = {};
-        c.waves = (int32_t)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(waves, ecc::kMaxWaves), cols));
+        c.waves = (int32_t)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(waves, ecc::kMaxSetWaves), cols));
         c.depth = std::max<int64_t>(1, depth);
         c.wgs_per_cu = wgs;
         c.window = window;
@@ -1747,6 +1759,7 @@ ecc_status ecc_autotune(ecc_ctx* ctx, const ecc_image* img, int32_t nbins, int32
         cand.push_back(c);
     };
     const int def_wgs = std::max(1, (def.grid + ctx->cu_count - 1) / ctx->cu_count);
+    if (def.waves > ecc::kMaxSetWaves) cand.push_back(ecc_launch_shape{});   // all fields at their default
     add(def.waves, def.depth, def_wgs);
     for (int wgs : {1, 2, 3, 4})
         for (int64_t dm : {1, 2, 4}) {
@@ -1780,7 +1793,8 @@ ecc_status ecc_autotune(ecc_ctx* ctx, const ecc_image* img, int32_t nbins, int32
     // at the default shape and with more workgroups per CU, which the smaller
     // LDS allows
     if (def.window >= 2048)
-        for (int wgs : {def_wgs, def_wgs + 2}) add(def.waves, def.depth, wgs, def.window / 2);
+        for (int wgs : {def_wgs, def_wgs + 2})
+            add(def.waves, def.depth, wgs, std::min<int32_t>(def.window / 2, ecc::kMaxLdsBins));
     // histogram copies for narrow windows (few bins leave LDS for more)
     if (def.window <= 1024)
         for (int copies : {2, 4, 8}) add(def.waves, def.depth, def_wgs, 0, copies);

@@ -38,7 +38,13 @@ struct Geom {
 };
 
 // Histogram window: bins [bin_lo, bin_lo + width) are accumulated in LDS.
-constexpr int kMaxLdsBins = 4096;
+constexpr int kMaxLdsBins = 4096;     // batches, and shapes that are set
+// Bins a single image takes in one pass: one copy of 16384 counters is 64 KB of LDS,
+// two workgroups per CU.  Every pass reads and bins the whole image again, which
+// costs more than the one copy's conflicts: 190x310x263 uint16, 16384 bins: four passes
+// 130 us, one 34; 32^3 to 2048^2 and 256^3 with 5000 to 65535 bins 1.5 to 4 times
+// faster.
+constexpr int kWideLdsBins = 16384;
 
 // Brick shapes of the wave kernels (64 x-lanes, 63 of them owned).  The
 // ECC_* macros exist for tuning builds; the defaults are the shipped shapes.
@@ -68,12 +74,13 @@ constexpr int kMaxLdsBins = 4096;
 // (hist_copies), which smooth data with few bins needs.  The LDS a launch takes
 // is sized to its window and copies (dynamic shared memory), so a histogram of
 // few bins leaves room for more workgroups.
-constexpr int kHistCopies = 2;   // copies of a window wider than 1024 bins
+constexpr int kHistCopies = 2;   // copies of a window of 1025 to 8192 bins
 constexpr int kMaxHistCopies = 8;
-// Default copies for a window of `width` bins: 8 up to 256 bins, 4 up to 1024.
+// Default copies for a window of `width` bins: 8 up to 256 bins, 4 up to 1024, 2 up
+// to 8192, then one.
 inline __host__ __device__ uint32_t hist_copies(int32_t width)
 {
-    return width <= 256 ? 8u : (width <= 1024 ? 4u : (uint32_t)kHistCopies);
+    return width <= 256 ? 8u : (width <= 1024 ? 4u : (width <= 2 * kMaxLdsBins ? (uint32_t)kHistCopies : 1u));
 }
 // Words from one copy to the next for a window of `width` bins (a multiple of 32
 // plus 8: the 8-bank offset; at least two words are spare: the sentinel's, and with
@@ -96,7 +103,8 @@ constexpr int kRows3 = ECC_ROWS3;      // rows per 3D brick of a batch
 constexpr int kStripRows = ECC_STRIP_ROWS;   // rows per strip of a single 3D image
 constexpr int kChunk2 = ECC_CHUNK2;    // rows loaded together in the 2D kernel
 // Waves per workgroup of the main kernels (x-chunk = waves * 63 position columns).
-constexpr int kMaxWaves = 9;
+constexpr int kMaxWaves = 16;
+constexpr int kMaxSetWaves = 9;   // the most that a launch shape can ask for
 
 // Bricks of a 3D volume, the units in which a batch is scheduled (BatchWork).
 // Ordinary bricks are an x-chunk of 63 * waves position columns x kRows3 rows (a

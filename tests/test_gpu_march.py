@@ -126,3 +126,39 @@ def test_batch_shares_of_wave_tasks(oracle_mod, cons):
             plan.close()
     finally:
         ctx.close()
+
+
+@pytest.mark.parametrize("nbins", [4097, 8192, 8193, 16384, 16385, 40000, 65535])
+def test_wide_histograms(oracle_mod, nbins):
+    """Histograms wider than 4096 bins: one pass up to 16384 bins (two copies of the
+    counters up to 8192, then one), passes of 16384 above; 2D, 3D and 4D, small and
+    large enough for several workgroups, also without allocation, with forced copies
+    and windows, and in a batch (passes of 4096)."""
+    from paper_2203_09087_amd import ecc
+    rng = np.random.default_rng(4400)
+    for cons in ("vertex", "top"):
+        ctx = ecc.Context(0, cons)
+        try:
+            for shape in ((3, 2), (130, 257), (9, 30, 141), (2, 3, 14, 65)):
+                for dtype in (np.uint16, np.float32):
+                    img = (rng.integers(0, 65536, size=shape).astype(np.uint16) if dtype == np.uint16
+                           else rng.standard_normal(shape).astype(np.float32))
+                    say(f"case: wide {cons} {nbins} {shape} {np.dtype(dtype).name}")
+                    dev = to_dev(img)
+                    want = oracle_mod.ecc(img, nbins, cons, value_range="auto", threads=8)
+                    got = [ctx.compute(dev, nbins, value_range="auto")]
+                    out = torch.full((nbins,), -5, dtype=torch.int64, device="cuda")
+                    got.append(ctx.compute_noalloc(dev, nbins, out, value_range="auto"))
+                    for copies, window in ((8, 0), (2, 4096), (0, 1500)):
+                        ctx.set_launch_shape(dev, nbins, copies=copies, window=window)
+                        got.append(ctx.compute(dev, nbins, value_range="auto"))
+                    got += ctx.compute_batch([dev], nbins, value_ranges=["auto"])
+                    torch.cuda.synchronize()
+                    for k, g in enumerate(got):
+                        assert np.array_equal(g.cpu().numpy(), want), (cons, nbins, shape, dtype, k)
+            ctx.autotune(dev, nbins, value_range="auto", reps=1)
+            got = ctx.compute(dev, nbins, value_range="auto")
+            torch.cuda.synchronize()
+            assert np.array_equal(got.cpu().numpy(), want), (cons, nbins, "tuned")
+        finally:
+            ctx.close()
