@@ -72,9 +72,10 @@ __global__ __launch_bounds__(kThreads) void k_minmax_batch(const BatchImage* ima
 
 // Every workgroup takes its segments in turn: a segment's wave tasks go to its
 // waves one after the other, their counts to one histogram.  PAIRS: the launch
-// holds pair volumes (their tasks load two hyperplanes).
-template <int DT, int CONS, bool WIN, bool PAIRS>
-__global__ __launch_bounds__(kBatchWaves * 64) __attribute__((amdgpu_waves_per_eu(ECC_WAVES_PER_EU_BATCH)))
+// holds pair volumes (their tasks load two hyperplanes).  WAVES per workgroup, as a
+// constant (read from the launch it costs the 512-image batch 5%).
+template <int DT, int CONS, bool WIN, bool PAIRS, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(ECC_WAVES_PER_EU_BATCH)))
 void k_ecc_batch(BatchLaunch B)
 {
     extern __shared__ __align__(16) int32_t hist[];
@@ -107,7 +108,7 @@ void k_ecc_batch(BatchLaunch B)
         const int ndim = (int)uniform_u32((uint32_t)I.ndim);
         zero_hist(H, B.width);
         const uint32_t t1 = uniform_u32((uint32_t)S.b1);
-        for (uint32_t t = uniform_u32((uint32_t)S.b0) + (uint32_t)wave_id(); t < t1; t += (uint32_t)kBatchWaves) {
+        for (uint32_t t = uniform_u32((uint32_t)S.b0) + (uint32_t)wave_id(); t < t1; t += (uint32_t)WAVES) {
             if (ndim == 2) {
                 run_march_2d<DT, CONS, WIN>(L.data, L.g, L.depth, P, W, H, block_task<DT, CONS>(L.g, Y, L.depth, H.sm, t));
                 continue;
@@ -139,8 +140,12 @@ hipError_t launch_batch_k(K kernel, const BatchLaunch& B, hipStream_t s, hipEven
 template <int DT, int CONS, bool PAIRS>
 hipError_t launch_batch_p(const BatchLaunch& B, hipStream_t s, hipEvent_t t0, hipEvent_t t1)
 {
-    return B.windowed ? launch_batch_k(k_ecc_batch<DT, CONS, true, PAIRS>, B, s, t0, t1)
-                      : launch_batch_k(k_ecc_batch<DT, CONS, false, PAIRS>, B, s, t0, t1);
+    constexpr int N = kBatchWaves;
+    if constexpr (!PAIRS)   // 16 waves only there (build_batch_tables)
+        if (!B.windowed && B.waves > N)
+            return launch_batch_k(k_ecc_batch<DT, CONS, false, false, kMaxWaves>, B, s, t0, t1);
+    return B.windowed ? launch_batch_k(k_ecc_batch<DT, CONS, true, PAIRS, N>, B, s, t0, t1)
+                      : launch_batch_k(k_ecc_batch<DT, CONS, false, PAIRS, N>, B, s, t0, t1);
 }
 
 template <int DT, int CONS>

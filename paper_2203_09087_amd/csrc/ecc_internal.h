@@ -103,8 +103,9 @@ constexpr int kRows3 = ECC_ROWS3;      // rows per 3D brick of a batch
 constexpr int kStripRows = ECC_STRIP_ROWS;   // rows per strip of a single 3D image
 constexpr int kChunk2 = ECC_CHUNK2;    // rows loaded together in the 2D kernel
 // Waves per workgroup of the main kernels (x-chunk = waves * 63 position columns).
-constexpr int kMaxWaves = 16;
 constexpr int kMaxSetWaves = 9;   // the most that a launch shape can ask for
+constexpr int kBatchWaves = 8;    // of a batch launch, or kMaxWaves (build_batch_tables)
+constexpr int kMaxWaves = 16;
 
 // Bricks of a 3D volume, the units in which a batch is scheduled (BatchWork).
 // Ordinary bricks are an x-chunk of 63 * waves position columns x kRows3 rows (a
@@ -322,10 +323,6 @@ struct BatchWork {
 };
 // Sets the image's depth and units.
 BatchWork batch_work(BatchImage& im, int construction, int depth3, int depth2);
-#ifndef ECC_BATCH_WAVES
-#define ECC_BATCH_WAVES 8
-#endif
-constexpr int kBatchWaves = ECC_BATCH_WAVES;   // waves per workgroup of the batched kernel
 constexpr int kBrickWaves = 9;                 // waves that a brick's width is chosen for
 
 // Launchers (ecc_kernels.hip: histogram kernels; ecc_reduce.hip: min/max,
