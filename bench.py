@@ -74,8 +74,8 @@ PROFILES = {
     "minmax": {"kernel": "k_minmax", "file": "k_minmax_f32_512cubed", "per_call": 1,
                "what": "the AUTO-range min/max pass over the 512^3 float32 GRF (seed 3), 4096 bins",
                "shape": {"waves": 8, "wgs_per_cu": 3, "depth": 32}},
-    "smooth": {"kernel": "k_smooth", "file": "k_smooth13_f32_8192sq", "per_call": 2,
-               "what": "one 13-tap smoothing pass (rows, then columns) of an 8192^2 float32 GRF (seed 8)",
+    "smooth": {"kernel": "k_smooth", "file": "k_smooth13_f32_8192sq", "per_call": 1,
+               "what": "one 13-tap smoothing pass (rows, then columns, in one launch) of an 8192^2 float32 GRF (seed 8)",
                "shape": None},
     "4d": {"kernel": "k_ecc_3d<2, 0, false, true>", "file": "k_ecc_3d_pair_f32_8x256cubed", "per_call": 1,
            "what": "the launch of the 7 pair terms (elementwise max of two neighbouring 256^3 hyperplanes, one "
@@ -92,7 +92,7 @@ def kernel_sources_sha256():
     import hashlib
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2203_09087_amd", "csrc")
-    for name in ("ecc_internal.h", "ecc_device.h", "ecc_kernels.hip", "ecc_batch.hip"):
+    for name in ("ecc_internal.h", "ecc_device.h", "ecc_march.h", "ecc_kernels_dt.h", "ecc_batch.hip"):
         h.update(open(os.path.join(csrc, name), "rb").read())
     return h.hexdigest()
 
@@ -167,7 +167,7 @@ def profile_input(which):
         o = torch.empty_like(t)
         taps = np.exp(-0.5 * (np.arange(13) - 6.0) ** 2 / 4.0)
         taps = (taps / taps.sum()).astype(np.float32)
-        return ctx, (lambda: ctx.smooth13(t, taps, out=o)), 16 * int(a.size)
+        return ctx, (lambda: ctx.smooth13(t, taps, out=o)), 8 * int(a.size)
     if which == "batch":
         imgs = [torch.from_numpy(a).to(dev) for a in synth.batch_images(count=512, seed=5)]
         outs = [torch.empty(256, dtype=torch.int64, device=dev) for _ in imgs]
@@ -297,7 +297,7 @@ def _alg_bytes(which):
     if which == "minmax":
         return 512 ** 3 * 4
     if which == "smooth":
-        return 16 * 8192 ** 2   # rows and columns each read and write every pixel
+        return 8 * 8192 ** 2   # every pixel read and written once
     if which == "c2":
         return 256 ** 3
     if which == "4d":

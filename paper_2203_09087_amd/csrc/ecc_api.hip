@@ -290,7 +290,8 @@ ecc::BinParams host_params(const Job& j, int32_t nbins)
         const uint32_t D = ihi - ilo + 1u;
         p.ilo = ilo;
         p.ihi = ihi;
-        p.ident = ((uint32_t)nbins == D) ? 1 : 0;
+        const bool whole = ilo == 0u && ihi == (j.dtype == ECC_U8 ? 255u : 65535u);
+        p.ident = (uint32_t)nbins == D ? (whole ? ecc::kIdentRaw : ecc::kIdentLevel) : 0;
         p.rcp = std::nextafter(1.0 / (double)D, HUGE_VAL);
     }
     return p;

@@ -4,15 +4,12 @@
 // The host cuts the bricks of all images (in order) into one contiguous run per
 // workgroup, balanced by work, and lists each run as segments of single images.
 // A workgroup processes its segments in order with the same marching bodies as the
-// single-image kernels, and writes one partial histogram row per segment.  The
-// merge kernels then give every image the sum of its rows (and its prefix scan)
+// single-image kernels (ecc_kernels_dt.h), and writes one prefix-summed histogram
+// row per segment.  The merge then gives every image the sum of its rows, its ECC,
 // without any atomic operation on the histogram bins, so the result of an image
 // does not depend on the batch it is in.
 #include <algorithm>
 
-#include <hip/hip_ext.h>
-
-#include "ecc_march.h"
 #include "ecc_merge.h"
 
 namespace ecc {
@@ -67,100 +64,6 @@ __global__ __launch_bounds__(kThreads) void k_minmax_batch(const BatchImage* ima
     case DT_U8: minmax_part<DT_U8>(I, pc, part, parts, mm); break;
     case DT_U16: minmax_part<DT_U16>(I, pc, part, parts, mm); break;
     default: minmax_part<DT_F32>(I, pc, part, parts, mm); break;
-    }
-}
-
-// Every workgroup takes its segments in turn: a segment's wave tasks go to its
-// waves one after the other, their counts to one histogram.  PAIRS: the launch
-// holds pair volumes (their tasks load two hyperplanes).  WAVES per workgroup, as a
-// constant (read from the launch it costs the 512-image batch 5%).
-template <int DT, int CONS, bool WIN, bool PAIRS, int WAVES>
-__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(ECC_WAVES_PER_EU_BATCH)))
-void k_ecc_batch(BatchLaunch B)
-{
-    extern __shared__ __align__(16) int32_t hist[];
-    const HistRef H = march_hist<WIN>(hist, B.width, B.hist_stride, B.hist_copies);
-    const WinKeys W = win_keys<WIN>(B.bin_lo, B.width);
-    const int s_end = B.wg_seg[blockIdx.x + 1];
-    for (int si = B.wg_seg[blockIdx.x]; si < s_end; ++si) {
-        // The tables are read with vector loads (the kernel also writes global
-        // memory, so the scalar cache is not used for them): every value the
-        // marching bodies depend on is read back from the first lane, so that
-        // sizes, offsets and pointers stay in scalar registers there.
-        const BatchSeg S = B.segs[si];
-        const int vol = (int)uniform_u32((uint32_t)S.image);
-        const BatchImage& I = B.images[vol];
-        const BinParams P = uniform_params<DT>(
-            I.auto_range ? params_from_keys(B.mm[2 * I.owner], B.mm[2 * I.owner + 1], DT, B.nbins) : I.params);
-        EccLaunch L;   // the fields the marching bodies read
-        L.data = uniform_ptr(I.data);
-        L.data2 = PAIRS ? uniform_ptr(I.data2) : nullptr;
-        L.g = Geom{uniform_i64(I.g.n0), uniform_i64(I.g.n1), uniform_i64(I.g.n2)};
-        L.depth = uniform_i64(I.depth);
-        L.z_base = 0;
-        L.pass_stride = 0;
-        L.n0_global = L.g.n0;
-        L.bin_lo = B.bin_lo;
-        L.width = B.width;
-        const Units Y = {uniform_u32(I.units.slots), uniform_u32(I.units.sa), uniform_u32(I.units.sb),
-                         uniform_u32(I.units.pairs_full), uniform_u32(I.units.pairs_edge),
-                         uniform_u32(I.units.tasks)};
-        const int ndim = (int)uniform_u32((uint32_t)I.ndim);
-        zero_hist(H, B.width);
-        const uint32_t t1 = uniform_u32((uint32_t)S.b1);
-        for (uint32_t t = uniform_u32((uint32_t)S.b0) + (uint32_t)wave_id(); t < t1; t += (uint32_t)WAVES) {
-            if (ndim == 2) {
-                run_march_2d<DT, CONS, WIN>(L.data, L.g, L.depth, P, W, H, block_task<DT, CONS>(L.g, Y, L.depth, H.sm, t));
-                continue;
-            }
-            const uint32_t zb = uniform_u32(t / Y.tasks);
-            const Task3 K = strip_task<DT, CONS, kStripRows>(L.g, Y, H.sm, t - zb * Y.tasks);
-            const uint32_t z0 = zb * (uint32_t)L.depth;
-            const uint32_t ze = (int64_t)z0 + L.depth < L.g.n0 ? z0 + (uint32_t)L.depth : (uint32_t)L.g.n0;
-            if (PAIRS && L.data2) run_march_3d<DT, CONS, kStripRows, WIN, true>(L, P, H, K, z0, ze);
-            else run_march_3d<DT, CONS, kStripRows, WIN, false>(L, P, H, K, z0, ze);
-        }
-        const size_t slot = (size_t)uniform_u32((uint32_t)S.slot);
-        flush_hist(H, B.partials + slot * (size_t)B.width, B.width, false, (int)uniform_u32((uint32_t)I.sign),
-                   WIN ? B.carry + slot : nullptr, B.bin_lo == 0);
-        __syncthreads();   // the histogram is read before the next segment clears it
-    }
-}
-
-template <class K>
-hipError_t launch_batch_k(K kernel, const BatchLaunch& B, hipStream_t s, hipEvent_t t0, hipEvent_t t1)
-{
-    if (t0 || t1)
-        hipExtLaunchKernelGGL(kernel, dim3(B.grid), dim3(B.waves * 64), B.lds_bytes, s, t0, t1, 0, B);
-    else
-        hipLaunchKernelGGL(kernel, dim3(B.grid), dim3(B.waves * 64), B.lds_bytes, s, B);
-    return hipGetLastError();
-}
-
-template <int DT, int CONS, bool PAIRS>
-hipError_t launch_batch_p(const BatchLaunch& B, hipStream_t s, hipEvent_t t0, hipEvent_t t1)
-{
-    constexpr int N = kBatchWaves;
-    if constexpr (!PAIRS)   // 16 waves only there (build_batch_tables)
-        if (!B.windowed && B.waves > N)
-            return launch_batch_k(k_ecc_batch<DT, CONS, false, false, kMaxWaves>, B, s, t0, t1);
-    return B.windowed ? launch_batch_k(k_ecc_batch<DT, CONS, true, PAIRS, N>, B, s, t0, t1)
-                      : launch_batch_k(k_ecc_batch<DT, CONS, false, PAIRS, N>, B, s, t0, t1);
-}
-
-template <int DT, int CONS>
-hipError_t launch_batch_w(const BatchLaunch& B, hipStream_t s, hipEvent_t t0, hipEvent_t t1)
-{
-    return B.pairs ? launch_batch_p<DT, CONS, true>(B, s, t0, t1) : launch_batch_p<DT, CONS, false>(B, s, t0, t1);
-}
-
-template <int CONS>
-hipError_t launch_batch_d(const BatchLaunch& B, hipStream_t s, hipEvent_t t0, hipEvent_t t1)
-{
-    switch (B.dtype) {
-    case DT_U8: return launch_batch_w<DT_U8, CONS>(B, s, t0, t1);
-    case DT_U16: return launch_batch_w<DT_U16, CONS>(B, s, t0, t1);
-    default: return launch_batch_w<DT_F32, CONS>(B, s, t0, t1);
     }
 }
 
@@ -228,7 +131,11 @@ hipError_t launch_mm_init(uint32_t* mm, int count, hipStream_t s)
 
 hipError_t launch_ecc_batch(const BatchLaunch& B, int construction, hipStream_t s, hipEvent_t t0, hipEvent_t t1)
 {
-    return construction == CONS_TOP ? launch_batch_d<CONS_TOP>(B, s, t0, t1) : launch_batch_d<CONS_VERTEX>(B, s, t0, t1);
+    switch (B.dtype) {
+    case DT_U8: return launch_batch_dt<DT_U8>(B, construction, s, t0, t1);
+    case DT_U16: return launch_batch_dt<DT_U16>(B, construction, s, t0, t1);
+    default: return launch_batch_dt<DT_F32>(B, construction, s, t0, t1);
+    }
 }
 
 hipError_t launch_merge_batch(const BatchLaunch& B, hipStream_t s)

@@ -111,7 +111,7 @@ __device__ __forceinline__ BinParams params_from_keys(uint32_t lo_key, uint32_t 
         const uint32_t D = ihi - ilo + 1u;
         p.ilo = ilo;
         p.ihi = ihi;
-        p.ident = ((uint32_t)nbins == D) ? 1 : 0;
+        p.ident = (uint32_t)nbins == D ? (ilo == 0u ? kIdentRaw : kIdentLevel) : 0;   // every value lies in the range
         // 1/D rounded up: one step above the correctly rounded quotient
         p.rcp = __longlong_as_double(__double_as_longlong(__ddiv_rn(1.0, (double)D)) + 1);
     }

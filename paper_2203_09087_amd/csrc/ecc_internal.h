@@ -10,6 +10,10 @@ namespace ecc {
 enum : int32_t { DT_U8 = 0, DT_U16 = 1, DT_F32 = 2 };
 enum : int32_t { CONS_VERTEX = 0, CONS_TOP = 1 };
 
+// nbins == D = hi - lo + 1: the bin is level - lo (kIdentLevel); with lo == 0 and no
+// value above hi the level itself (kIdentRaw: a full type range, or an AUTO range).
+enum : int32_t { kIdentLevel = 1, kIdentRaw = 2 };
+
 // Bin of a value (the library's reading of the paper's gray-level histogram
 // index for data that is not 0..255 integers):
 //   integer data: a = clamp(v, ilo, ihi) - ilo ; bin = floor(a * nbins / D),
@@ -26,7 +30,7 @@ struct BinParams {
     int32_t nbins;
     uint32_t ilo, ihi;  // integer range
     int32_t flat;       // float data, hi == lo
-    int32_t ident;      // integer data, nbins == D = hi - lo + 1: bin = level - lo
+    int32_t ident;      // integer data: kIdentRaw, kIdentLevel or 0 (any nbins)
     double base;        // float data: subtrahend (lo, or the next double above lo if flat)
     double scale;       // float data: nbins / (hi - lo), +inf if flat
     double rcp;         // integer data: 1 / D rounded up
@@ -344,6 +348,12 @@ hipError_t launch_minmax(const void* data, int dtype, int64_t nvox, uint32_t* mm
 hipError_t launch_combine(const void* a, const void* b, void* out, int64_t n, int dtype, bool take_max,
                           hipStream_t s);
 hipError_t launch_ecc(const EccLaunch& L, hipStream_t s, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr);
+// The same for one data type, and the address of its single-image kernel
+// (ecc_kernels_dt.h).
+template <int DT> hipError_t launch_ecc_dt(const EccLaunch& L, hipStream_t s, hipEvent_t t0, hipEvent_t t1);
+template <int DT> const void* kernel_dt(int ndim, int construction, bool windowed);
+template <int DT>
+hipError_t launch_batch_dt(const BatchLaunch& B, int construction, hipStream_t s, hipEvent_t t0, hipEvent_t t1);
 // The merge of partial rows into out[bin_lo .. bin_lo + width) of one image or of
 // every image of a batch (ecc_merge.h).
 struct MergeArgs {

@@ -1,0 +1,222 @@
+// ecc_kernels_dt.h -- the histogram kernels of one data type, for one image (2D and
+// 3D) and for batches, and their launchers.  A source per data type includes it with
+// ECC_KERNEL_DT defined (they compile side by side).  The method and its mapping to
+// the hardware are described in ecc_device.h and ecc_march.h.
+#pragma once
+
+#include <hip/hip_ext.h>
+
+#include "ecc_march.h"
+
+namespace ecc {
+
+namespace {
+
+using namespace dev;
+
+// 3D images.  A workgroup brick is as many consecutive wave tasks (Units: 2 x 63
+// slots of kStripRows rows each) as it has waves x L.depth planes.  Its waves read
+// neighbouring parts of the same rows at about the same time.
+template <int DT, int CONS, bool WIN, bool PAIR>
+__global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(ECC_WAVES_PER_EU_3D))) void k_ecc_3d(EccLaunch L)
+{
+    extern __shared__ __align__(16) int32_t hist[];
+    const BinParams P = load_params<DT>(L);
+    const HistRef H = march_hist<WIN>(hist, L.width, L.hist_stride, L.hist_copies);
+    zero_hist(H, L.width);
+    const uint32_t waves = blockDim.x >> 6;
+    const uint32_t per_z = (L.units.tasks + waves - 1u) / waves;
+    const uint32_t nbricks = per_z * (uint32_t)((L.z_own + L.depth - 1) / L.depth);
+    for (uint32_t brick = blockIdx.x; brick < nbricks; brick += gridDim.x) {
+        const uint32_t zb = uniform_u32(brick / per_z), r = uniform_u32(brick - zb * per_z);
+        const uint32_t z0 = zb * (uint32_t)L.depth;
+        const uint32_t ze = (int64_t)z0 + L.depth < L.z_own ? z0 + (uint32_t)L.depth : (uint32_t)L.z_own;
+        const Task3 K = strip_task<DT, CONS, kStripRows>(L.g, L.units, H.sm, r * waves + (uint32_t)wave_id());
+        run_march_3d<DT, CONS, kStripRows, WIN, PAIR>(L, P, H, K, z0, ze);
+    }
+    const size_t row = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
+    flush_hist(H, L.partials + row * (size_t)L.width, L.width, L.flush_add != 0, L.flush_sign, WIN ? L.carry + row : nullptr,
+               L.bin_lo == 0);
+    if (L.fused) fused_merge(hist, L.partials, L.width, L.out, L.counter);
+}
+
+// 2D images.  A workgroup brick is as many consecutive wave tasks (Units: 2 x 63
+// slots x L.depth rows each) as it has waves.
+template <int DT, int CONS, bool WIN>
+__global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(ECC_WAVES_PER_EU_2D))) void k_ecc_2d(EccLaunch L)
+{
+    extern __shared__ __align__(16) int32_t hist[];
+    const BinParams P = load_params<DT>(L);
+    const HistRef H = march_hist<WIN>(hist, L.width, L.hist_stride, L.hist_copies);
+    zero_hist(H, L.width);
+    const uint32_t waves = blockDim.x >> 6;
+    const WinKeys W = win_keys<WIN>(L.bin_lo, L.width);
+    for (uint32_t task = blockIdx.x * waves + (uint32_t)wave_id(); task < L.units.tasks; task += gridDim.x * waves)
+        run_march_2d<DT, CONS, WIN>(L.data, L.g, L.depth, P, W, H,
+                                    block_task<DT, CONS>(L.g, L.units, L.depth, H.sm, task));
+    flush_hist(H, L.partials + (size_t)blockIdx.x * (size_t)L.width, L.width, L.flush_add != 0, L.flush_sign,
+               WIN ? L.carry + blockIdx.x : nullptr, L.bin_lo == 0);
+    if (L.fused) fused_merge(hist, L.partials, L.width, L.out, L.counter);
+}
+
+// Every workgroup takes its segments in turn: a segment's wave tasks go to its
+// waves one after the other, their counts to one histogram.  PAIRS: the launch
+// holds pair volumes (their tasks load two hyperplanes).  WAVES per workgroup, as a
+// constant (read from the launch it costs the 512-image batch 5%).
+template <int DT, int CONS, bool WIN, bool PAIRS, int WAVES>
+__global__ __launch_bounds__(WAVES * 64) __attribute__((amdgpu_waves_per_eu(ECC_WAVES_PER_EU_BATCH)))
+void k_ecc_batch(BatchLaunch B)
+{
+    extern __shared__ __align__(16) int32_t hist[];
+    const HistRef H = march_hist<WIN>(hist, B.width, B.hist_stride, B.hist_copies);
+    const WinKeys W = win_keys<WIN>(B.bin_lo, B.width);
+    const int s_end = B.wg_seg[blockIdx.x + 1];
+    for (int si = B.wg_seg[blockIdx.x]; si < s_end; ++si) {
+        // The tables are read with vector loads (the kernel also writes global
+        // memory, so the scalar cache is not used for them): every value the
+        // marching bodies depend on is read back from the first lane, so that
+        // sizes, offsets and pointers stay in scalar registers there.
+        const BatchSeg S = B.segs[si];
+        const int vol = (int)uniform_u32((uint32_t)S.image);
+        const BatchImage& I = B.images[vol];
+        const BinParams P = uniform_params<DT>(
+            I.auto_range ? params_from_keys(B.mm[2 * I.owner], B.mm[2 * I.owner + 1], DT, B.nbins) : I.params);
+        EccLaunch L;   // the fields the marching bodies read
+        L.data = uniform_ptr(I.data);
+        L.data2 = PAIRS ? uniform_ptr(I.data2) : nullptr;
+        L.g = Geom{uniform_i64(I.g.n0), uniform_i64(I.g.n1), uniform_i64(I.g.n2)};
+        L.depth = uniform_i64(I.depth);
+        L.z_base = 0;
+        L.pass_stride = 0;
+        L.n0_global = L.g.n0;
+        L.bin_lo = B.bin_lo;
+        L.width = B.width;
+        const Units Y = {uniform_u32(I.units.slots), uniform_u32(I.units.sa), uniform_u32(I.units.sb),
+                         uniform_u32(I.units.pairs_full), uniform_u32(I.units.pairs_edge),
+                         uniform_u32(I.units.tasks)};
+        const int ndim = (int)uniform_u32((uint32_t)I.ndim);
+        zero_hist(H, B.width);
+        const uint32_t t1 = uniform_u32((uint32_t)S.b1);
+        for (uint32_t t = uniform_u32((uint32_t)S.b0) + (uint32_t)wave_id(); t < t1; t += (uint32_t)WAVES) {
+            if (ndim == 2) {
+                run_march_2d<DT, CONS, WIN>(L.data, L.g, L.depth, P, W, H, block_task<DT, CONS>(L.g, Y, L.depth, H.sm, t));
+                continue;
+            }
+            const uint32_t zb = uniform_u32(t / Y.tasks);
+            const Task3 K = strip_task<DT, CONS, kStripRows>(L.g, Y, H.sm, t - zb * Y.tasks);
+            const uint32_t z0 = zb * (uint32_t)L.depth;
+            const uint32_t ze = (int64_t)z0 + L.depth < L.g.n0 ? z0 + (uint32_t)L.depth : (uint32_t)L.g.n0;
+            if (PAIRS && L.data2) run_march_3d<DT, CONS, kStripRows, WIN, true>(L, P, H, K, z0, ze);
+            else run_march_3d<DT, CONS, kStripRows, WIN, false>(L, P, H, K, z0, ze);
+        }
+        const size_t slot = (size_t)uniform_u32((uint32_t)S.slot);
+        flush_hist(H, B.partials + slot * (size_t)B.width, B.width, false, (int)uniform_u32((uint32_t)I.sign),
+                   WIN ? B.carry + slot : nullptr, B.bin_lo == 0);
+        __syncthreads();   // the histogram is read before the next segment clears it
+    }
+}
+
+// ----------------------------------------------------------------- launchers
+
+template <class K>
+inline hipError_t launch_k(K kernel, const EccLaunch& L, hipStream_t s, hipEvent_t t0, hipEvent_t t1)
+{
+    const dim3 grid((unsigned)L.grid, (unsigned)(L.npass > 1 ? L.npass : 1));
+    if (t0 || t1)
+        hipExtLaunchKernelGGL(kernel, grid, dim3(L.waves * 64), L.lds_bytes, s, t0, t1, 0, L);
+    else
+        hipLaunchKernelGGL(kernel, grid, dim3(L.waves * 64), L.lds_bytes, s, L);
+    return hipGetLastError();
+}
+
+template <int NDIM, int DT, int CONS, bool WIN>
+inline hipError_t launch_t(const EccLaunch& L, hipStream_t s, hipEvent_t t0, hipEvent_t t1)
+{
+    if constexpr (NDIM == 2) return launch_k(k_ecc_2d<DT, CONS, WIN>, L, s, t0, t1);
+    else if (L.data2) return launch_k(k_ecc_3d<DT, CONS, WIN, true>, L, s, t0, t1);
+    else return launch_k(k_ecc_3d<DT, CONS, WIN, false>, L, s, t0, t1);
+}
+
+template <int NDIM, int DT, int CONS>
+inline hipError_t launch_w(const EccLaunch& L, hipStream_t s, hipEvent_t t0, hipEvent_t t1)
+{
+    return L.windowed ? launch_t<NDIM, DT, CONS, true>(L, s, t0, t1) : launch_t<NDIM, DT, CONS, false>(L, s, t0, t1);
+}
+
+template <int NDIM, int DT>
+inline hipError_t launch_c(const EccLaunch& L, hipStream_t s, hipEvent_t t0, hipEvent_t t1)
+{
+    return L.construction == CONS_TOP ? launch_w<NDIM, DT, CONS_TOP>(L, s, t0, t1)
+                                      : launch_w<NDIM, DT, CONS_VERTEX>(L, s, t0, t1);
+}
+
+template <int NDIM, int DT, int CONS, bool WIN>
+inline const void* kernel_of()
+{
+    if constexpr (NDIM == 2) return (const void*)k_ecc_2d<DT, CONS, WIN>;
+    else return (const void*)k_ecc_3d<DT, CONS, WIN, false>;
+}
+
+template <int NDIM, int DT, int CONS>
+inline const void* kernel_w(bool win)
+{
+    return win ? kernel_of<NDIM, DT, CONS, true>() : kernel_of<NDIM, DT, CONS, false>();
+}
+
+template <int NDIM, int DT>
+inline const void* kernel_c(int cons, bool win)
+{
+    return cons == CONS_TOP ? kernel_w<NDIM, DT, CONS_TOP>(win) : kernel_w<NDIM, DT, CONS_VERTEX>(win);
+}
+
+template <class K>
+hipError_t launch_batch_k(K kernel, const BatchLaunch& B, hipStream_t s, hipEvent_t t0, hipEvent_t t1)
+{
+    if (t0 || t1)
+        hipExtLaunchKernelGGL(kernel, dim3(B.grid), dim3(B.waves * 64), B.lds_bytes, s, t0, t1, 0, B);
+    else
+        hipLaunchKernelGGL(kernel, dim3(B.grid), dim3(B.waves * 64), B.lds_bytes, s, B);
+    return hipGetLastError();
+}
+
+template <int DT, int CONS, bool PAIRS>
+hipError_t launch_batch_p(const BatchLaunch& B, hipStream_t s, hipEvent_t t0, hipEvent_t t1)
+{
+    constexpr int N = kBatchWaves;
+    if constexpr (!PAIRS)   // 16 waves only there (build_batch_tables)
+        if (!B.windowed && B.waves > N)
+            return launch_batch_k(k_ecc_batch<DT, CONS, false, false, kMaxWaves>, B, s, t0, t1);
+    return B.windowed ? launch_batch_k(k_ecc_batch<DT, CONS, true, PAIRS, N>, B, s, t0, t1)
+                      : launch_batch_k(k_ecc_batch<DT, CONS, false, PAIRS, N>, B, s, t0, t1);
+}
+
+template <int DT, int CONS>
+hipError_t launch_batch_w(const BatchLaunch& B, hipStream_t s, hipEvent_t t0, hipEvent_t t1)
+{
+    return B.pairs ? launch_batch_p<DT, CONS, true>(B, s, t0, t1) : launch_batch_p<DT, CONS, false>(B, s, t0, t1);
+}
+
+}  // namespace
+
+template <>
+hipError_t launch_ecc_dt<ECC_KERNEL_DT>(const EccLaunch& L, hipStream_t s, hipEvent_t t0, hipEvent_t t1)
+{
+    return L.ndim == 2 ? launch_c<2, ECC_KERNEL_DT>(L, s, t0, t1) : launch_c<3, ECC_KERNEL_DT>(L, s, t0, t1);
+}
+
+template <>
+const void* kernel_dt<ECC_KERNEL_DT>(int ndim, int construction, bool windowed)
+{
+    return ndim == 2 ? kernel_c<2, ECC_KERNEL_DT>(construction, windowed)
+                     : kernel_c<3, ECC_KERNEL_DT>(construction, windowed);
+}
+
+template <>
+hipError_t launch_batch_dt<ECC_KERNEL_DT>(const BatchLaunch& B, int construction, hipStream_t s, hipEvent_t t0,
+                                          hipEvent_t t1)
+{
+    return construction == CONS_TOP ? launch_batch_w<ECC_KERNEL_DT, CONS_TOP>(B, s, t0, t1)
+                                    : launch_batch_w<ECC_KERNEL_DT, CONS_VERTEX>(B, s, t0, t1);
+}
+
+}  // namespace ecc

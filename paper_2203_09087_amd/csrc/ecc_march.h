@@ -155,7 +155,7 @@ __device__ __forceinline__ WinKeys win_keys(int32_t bin_lo, int32_t width)
 }
 
 // Packed keys of two values.
-template <int DT, bool IDENT, bool WIN>
+template <int DT, int IDENT, bool WIN>
 __device__ __forceinline__ uint32_t pair_key(typename ValT<DT>::T a, typename ValT<DT>::T b, const BinParams& p,
                                              const WinKeys& w, uint32_t oob)
 {
@@ -164,8 +164,8 @@ __device__ __forceinline__ uint32_t pair_key(typename ValT<DT>::T a, typename Va
         k = bin_of<DT>(a, p) | (bin_of<DT>(b, p) << 16);
     } else {
         k = (uint32_t)a | ((uint32_t)b << 16);
-        k = pk_min(pk_subsat(k, halves(p.ilo)), halves(p.ihi - p.ilo));
-        if constexpr (!IDENT) {
+        if constexpr (IDENT != kIdentRaw) k = pk_min(pk_subsat(k, halves(p.ilo)), halves(p.ihi - p.ilo));
+        if constexpr (IDENT == 0) {
             // bin_of on both halves; v_mad_u32_u16 takes a half and multiplies it
             uint32_t na, nb;
             asm("v_mad_u32_u16 %0, %1, %2, 0" : "=v"(na) : "v"(k), "s"(p.nbins));
@@ -213,7 +213,7 @@ __device__ __forceinline__ void add_pair(const HistRef& H, uint32_t key, uint32_
 // types can take the registers that the row before it has just freed and are
 // back in place after two steps: one set of types and one spare row instead of two
 // sets.
-template <int DT, int CONS, int R, bool WIN, bool FULL, bool IDENT, bool PAIR>
+template <int DT, int CONS, int R, bool WIN, bool FULL, int IDENT, bool PAIR>
 __device__ __forceinline__ void march_3d(const EccLaunch& L, const BinParams& P, const HistRef& H, const Lanes& N,
                                          int64_t ys, uint32_t z0, uint32_t zend, int r_lo, int r_hi)
 {
@@ -499,19 +499,25 @@ __device__ __forceinline__ Task3 strip_task(const Geom& G, const Units& Y, uint3
 }
 
 // Runs a wave task over planes [z0, zend).
+template <int DT, int CONS, int R, bool WIN, bool PAIR, int IDENT>
+__device__ __forceinline__ void run_march_3d_as(const EccLaunch& L, const BinParams& P, const HistRef& H,
+                                                const Task3& K, uint32_t z0, uint32_t ze)
+{
+    const bool full = K.r_lo == 0 && K.r_hi == R + 1;
+    if (full) march_3d<DT, CONS, R, WIN, true, IDENT, PAIR>(L, P, H, K.lanes, K.ys, z0, ze, K.r_lo, K.r_hi);
+    else march_3d<DT, CONS, R, WIN, false, IDENT, PAIR>(L, P, H, K.lanes, K.ys, z0, ze, K.r_lo, K.r_hi);
+}
 template <int DT, int CONS, int R, bool WIN, bool PAIR>
 __device__ __forceinline__ void run_march_3d(const EccLaunch& L, const BinParams& P, const HistRef& H, const Task3& K,
                                              uint32_t z0, uint32_t ze)
 {
     if (!K.active) return;
-    const bool full = K.r_lo == 0 && K.r_hi == R + 1;
-    if (DT != DT_F32 && uniform_flag(P.ident)) {
-        if (full) march_3d<DT, CONS, R, WIN, true, true, PAIR>(L, P, H, K.lanes, K.ys, z0, ze, K.r_lo, K.r_hi);
-        else march_3d<DT, CONS, R, WIN, false, true, PAIR>(L, P, H, K.lanes, K.ys, z0, ze, K.r_lo, K.r_hi);
-    } else {
-        if (full) march_3d<DT, CONS, R, WIN, true, false, PAIR>(L, P, H, K.lanes, K.ys, z0, ze, K.r_lo, K.r_hi);
-        else march_3d<DT, CONS, R, WIN, false, false, PAIR>(L, P, H, K.lanes, K.ys, z0, ze, K.r_lo, K.r_hi);
+    if constexpr (DT != DT_F32) {
+        const int ident = __builtin_amdgcn_readfirstlane(P.ident);
+        if (ident == kIdentRaw) return run_march_3d_as<DT, CONS, R, WIN, PAIR, kIdentRaw>(L, P, H, K, z0, ze);
+        if (ident == kIdentLevel) return run_march_3d_as<DT, CONS, R, WIN, PAIR, kIdentLevel>(L, P, H, K, z0, ze);
     }
+    run_march_3d_as<DT, CONS, R, WIN, PAIR, 0>(L, P, H, K, z0, ze);
 }
 
 // ------------------------------------------------------------------------- 2D
@@ -534,7 +540,7 @@ struct Task2 {
 // (whole blocks, `rows` a multiple of 8) the lanes may sit in different blocks.
 // Bound by vector issue: 20 instructions a row of two positions beside the
 // binning, every one 4 cycles; loads run 8 rows ahead.
-template <int DT, int CONS, bool WIN, bool IDENT, bool EDGE>
+template <int DT, int CONS, bool WIN, int IDENT, bool EDGE>
 __device__ __forceinline__ void march_2d(const void* base, uint32_t row_bytes, const BinParams& P, const WinKeys& W,
                                          const HistRef& H, const Task2& K, uint32_t rows, uint32_t avail)
 {
@@ -659,23 +665,29 @@ __device__ __forceinline__ Task2 block_task(const Geom& G, const Units& Y, int64
 }
 
 // Runs wave task K of the 2D image at data.
-template <int DT, int CONS, bool WIN>
-__device__ __forceinline__ void run_march_2d(const void* data, const Geom& G, int64_t depth, const BinParams& P,
-                                             const WinKeys& W, const HistRef& H, const Task2& K)
+template <int DT, int CONS, bool WIN, int IDENT>
+__device__ __forceinline__ void run_march_2d_as(const void* data, const Geom& G, int64_t depth, const BinParams& P,
+                                                const WinKeys& W, const HistRef& H, const Task2& K)
 {
-    if (!K.active) return;
     using T = typename ValT<DT>::T;
     const int64_t row_bytes = G.n2 * (int64_t)sizeof(T);
     const char* base = (const char*)data + K.y0 * row_bytes;
     const uint32_t avail = (uint32_t)(G.n1 - K.y0);
     const uint32_t rows = (int64_t)avail < depth ? avail : (uint32_t)depth;
-    if (DT != DT_F32 && uniform_flag(P.ident)) {
-        if (K.whole) march_2d<DT, CONS, WIN, true, false>(base, (uint32_t)row_bytes, P, W, H, K, rows, avail);
-        else march_2d<DT, CONS, WIN, true, true>(base, (uint32_t)row_bytes, P, W, H, K, rows, avail);
-    } else {
-        if (K.whole) march_2d<DT, CONS, WIN, false, false>(base, (uint32_t)row_bytes, P, W, H, K, rows, avail);
-        else march_2d<DT, CONS, WIN, false, true>(base, (uint32_t)row_bytes, P, W, H, K, rows, avail);
+    if (K.whole) march_2d<DT, CONS, WIN, IDENT, false>(base, (uint32_t)row_bytes, P, W, H, K, rows, avail);
+    else march_2d<DT, CONS, WIN, IDENT, true>(base, (uint32_t)row_bytes, P, W, H, K, rows, avail);
+}
+template <int DT, int CONS, bool WIN>
+__device__ __forceinline__ void run_march_2d(const void* data, const Geom& G, int64_t depth, const BinParams& P,
+                                             const WinKeys& W, const HistRef& H, const Task2& K)
+{
+    if (!K.active) return;
+    if constexpr (DT != DT_F32) {
+        const int ident = __builtin_amdgcn_readfirstlane(P.ident);
+        if (ident == kIdentRaw) return run_march_2d_as<DT, CONS, WIN, kIdentRaw>(data, G, depth, P, W, H, K);
+        if (ident == kIdentLevel) return run_march_2d_as<DT, CONS, WIN, kIdentLevel>(data, G, depth, P, W, H, K);
     }
+    run_march_2d_as<DT, CONS, WIN, 0>(data, G, depth, P, W, H, K);
 }
 
 }  // namespace dev

@@ -162,3 +162,41 @@ def test_wide_histograms(oracle_mod, nbins):
             assert np.array_equal(got.cpu().numpy(), want), (cons, nbins, "tuned")
         finally:
             ctx.close()
+
+
+@pytest.mark.parametrize("dtype", [np.uint8, np.uint16])
+def test_integer_levels_as_bins(oracle_mod, dtype):
+    """The three binnings of integer data: the level itself (an AUTO range from 0 or
+    the type's whole range, one bin per level), the level minus the lowest one with
+    levels outside the range clamped, and the general one; data that start at 0 and
+    that do not, and explicit ranges narrower than the data on either side.  2D, 3D
+    and 4D, alone and in a batch."""
+    from paper_2203_09087_amd import ecc
+    rng = np.random.default_rng(4500)
+    top = int(np.iinfo(dtype).max)
+    cases = []   # (lowest level, highest level, value range, bins)
+    for lo, hi in ((0, 199), (17, 90), (top - 199, top), (3, 3), (0, 0)):
+        cases += [(lo, hi, "auto", hi - lo + 1), (lo, hi, "auto", hi - lo + 2), (lo, hi, (lo, hi), hi - lo + 1)]
+    cases += [(0, 199, (0, 120), 121), (0, 199, (40, 120), 81), (0, 199, (40, 255), 216), (0, 199, (40, 120), 50)]
+    most = min(top + 1, 65535)
+    cases += [(0, top, (0, top), most), (0, top, "auto", most), (0, top, (1, top), top), (0, top - 1, "auto", top)]
+    for cons in ("vertex", "top"):
+        ctx = ecc.Context(0, cons)
+        try:
+            for lo, hi, r, nbins in cases:
+                hosts = []
+                for shape in ((19, 131), (4, 9, 70), (2, 3, 8, 65)):
+                    img = rng.integers(lo, hi + 1, size=shape).astype(dtype)
+                    img.flat[0], img.flat[-1] = lo, hi
+                    hosts.append(img)
+                say(f"case: levels {cons} {np.dtype(dtype).name} [{lo}, {hi}] range={r} nbins={nbins}")
+                devs = [to_dev(h) for h in hosts]
+                want = [oracle_mod.ecc(h, nbins, cons, value_range=r, threads=8) for h in hosts]
+                got = [ctx.compute(d, nbins, value_range=r) for d in devs]
+                batch = ctx.compute_batch(devs, nbins, value_ranges=[r] * len(devs))
+                torch.cuda.synchronize()
+                for h, w, g, b in zip(hosts, want, got, batch):
+                    assert np.array_equal(g.cpu().numpy(), w), (cons, lo, hi, r, nbins, h.shape)
+                    assert np.array_equal(b.cpu().numpy(), w), (cons, lo, hi, r, nbins, h.shape, "batch")
+        finally:
+            ctx.close()
