@@ -243,9 +243,13 @@ struct EccLaunch {
     uint32_t hist_copies;          // copies of the histogram (a power of two up to kMaxHistCopies)
     uint32_t lds_bytes;            // dynamic LDS of the launch
 };
-// Partial-row words (grid x window) up to which the histogram kernel merges its
-// own rows (fused_merge_scan) instead of launching the two merge kernels.
-constexpr int64_t kFusedMergeWords = int64_t(1) << 16;
+// Partial-row words (grid x window) up to which the histogram kernel's last
+// workgroup merges the rows (fused_merge) instead of a launch of k_merge.  One
+// workgroup takes about 0.3 us per 1024 words, the launch about 1 us more than none:
+// 300^2 uint8, 2 to 4 thousand words, 9.5 us a call fused and 10.6 with the launch;
+// 24x30x40 uint8, 4 to 8 thousand, 13.1 and 11.0; 300^2 float32, 8 to 16 thousand,
+// 13.0 and 10.5; 100^3 uint8, 32 to 64 thousand, 34.4 and 11.6.
+constexpr int64_t kFusedMergeWords = int64_t(1) << 12;
 
 // ---------------------------------------------------------------- batches
 
