@@ -892,15 +892,15 @@ constexpr int64_t kSegVoxels = int64_t(1) << 27;
 // Workgroups per CU of a batch launch with `work` vector instructions per CU.  More
 // workgroups even out the end of the launch (two fit a CU at a time, the others
 // follow), but each clears, flushes and has merged a histogram of its own, about
-// ten instructions per counter: so many that a workgroup still counts for one and a
-// half times that.  Measured: 512 uneven uint8 images, 256 bins: 572, 442, 441 and
-// 419 us with 1 to 4; 16 uint16 images (33 M voxels), 4096 bins: 94, 107, 128 and
-// 138 us.  At most 6 over the launches of all dtypes (ecc_reserve's segment bound).
+// ten instructions per counter.  With 1, 2, 3 and 4, in us: 71 float32 images of 4096
+// bins 134, 117, 140, 160; 38 uint16 images of 4096 bins 59, 69, 74, 75; 67 uint8
+// images of 256 bins 74, 70, 78, 77; 512 of them are fastest with 4.  At most 6 over
+// the launches of all dtypes (ecc_reserve's segment bound).
 int batch_wgs(double work, int32_t window, int ndtypes)
 {
     const double counters = (double)window * (double)ecc::hist_copies(window);
     for (int wgs : {4, 3, 2})
-        if (wgs * ndtypes <= 6 && work / wgs >= 15.0 * counters) return wgs;
+        if (wgs * ndtypes <= 6 && work / wgs >= (wgs == 2 ? 8.0 : 30.0) * counters) return wgs;
     return 1;
 }
 
@@ -954,9 +954,20 @@ void build_batch_tables(int cu_count, int construction, const std::vector<Job>& 
     std::vector<int64_t> bricks(nrec, 0), max_take(nrec, 1);
     std::vector<double> brick_cost(nrec, 0.0);
     T.owner_bricks.assign((size_t)count, 0);
+    double voxels = 0;
+    for (int i : vols) {
+        const ecc::Geom& g = T.images[(size_t)i].g;
+        if (T.images[(size_t)i].ndim == 3) voxels += (double)g.n0 * (double)g.n1 * (double)g.n2;
+    }
+    // Planes of a 3D wave task: about twice what a wave gets, so that it starts one or
+    // two tasks while the waves of a workgroup stay side by side in the volume.
+    // (16 serving images of 4096 bins, 11 planes per wave: 86 us so, 100 with tasks of
+    // all planes, whose waves read far apart; 512 uint8 images 338 either way.)
+    const int64_t planes = (int64_t)std::min(
+        1e9, std::max(16.0, voxels / ((double)ecc::kLaneCols * ecc::kStripRows * ecc::kMaxWaves * cu_count)));
     for (int i : vols) {
         ecc::BatchImage& im = T.images[(size_t)i];
-        const ecc::BatchWork w = ecc::batch_work(im, construction, shape.depth3, shape.depth2);
+        const ecc::BatchWork w = ecc::batch_work(im, construction, shape.depth3, shape.depth2, planes);
         T.work[(size_t)i] = w;
         bricks[(size_t)i] = w.bricks;
         T.owner_bricks[(size_t)im.owner] += w.bricks;
@@ -1045,11 +1056,11 @@ void build_batch_tables(int cu_count, int construction, const std::vector<Job>& 
     lay.total = lay.partials + align_up((size_t)nseg * (size_t)T.window * sizeof(int32_t));
 }
 
-// The wave tasks of a volume before its brick b: tasks * b / bricks, rounded down
-// (at most 2^32 tasks and 2^40 bricks).
+// The steps of a volume's wave tasks before its brick b: steps * b / bricks, rounded
+// down.
 int64_t share(const ecc::BatchWork& w, int64_t b)
 {
-    return (int64_t)((unsigned __int128)w.tasks * (uint64_t)b / (uint64_t)w.bricks);
+    return (int64_t)((unsigned __int128)w.steps * (uint64_t)b / (uint64_t)w.bricks);
 }
 
 // Copies the tables into host memory laid out as lay (bytes [0, tables_end)).
@@ -1057,7 +1068,7 @@ void pack_batch_tables(const BatchTables& T, char* h)
 {
     const BatchLayout& lay = T.lay;
     memcpy(h + lay.images, T.images.data(), T.images.size() * sizeof(ecc::BatchImage));
-    // the run [b0, b1) of a volume's bricks stands for this share of its wave tasks
+    // the run [b0, b1) of a volume's bricks stands for this share of its wave tasks' steps
     ecc::BatchSeg* segs = (ecc::BatchSeg*)(h + lay.segs);
     for (size_t k = 0; k < T.segs.size(); ++k) {
         const ecc::BatchSeg& g = T.segs[k];

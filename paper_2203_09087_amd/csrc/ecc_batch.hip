@@ -69,7 +69,7 @@ __global__ __launch_bounds__(kThreads) void k_minmax_batch(const BatchImage* ima
 
 }  // namespace
 
-BatchWork batch_work(BatchImage& im, int construction, int depth3, int depth2)
+BatchWork batch_work(BatchImage& im, int construction, int depth3, int depth2, int64_t planes)
 {
     const int64_t xpos = axis_positions(im.g.n2, construction);
     const int64_t cols = (xpos + kLaneCols - 1) / kLaneCols;
@@ -89,24 +89,29 @@ BatchWork batch_work(BatchImage& im, int construction, int depth3, int depth2)
     const int64_t chunk = kLaneCols * (int64_t)wpb;
     BatchWork b;
     if (im.ndim == 3) {
-        im.depth = depth3;
         im.units = units_3d(im.g, construction);
-        const int64_t nzb = (im.g.n0 + im.depth - 1) / im.depth;
+        const int64_t nzb = (im.g.n0 + depth3 - 1) / depth3;
         b.bricks = layout_3d(im.g, construction, wpb).per_z * nzb;
-        b.brick_voxels = chunk * kRows3 * im.depth;
-        b.tasks = (int64_t)im.units.tasks * nzb;
+        b.brick_voxels = chunk * kRows3 * depth3;
+        // the wave tasks' plane blocks share the planes evenly
+        const int64_t nb = (im.g.n0 + planes - 1) / planes;
+        im.depth = (im.g.n0 + nb - 1) / nb;
+        b.steps = (int64_t)im.units.tasks * nb * im.depth;
         // a plane step is about 240 instructions (a pair volume bins twice as
         // much), a task starts with about three steps' worth
-        b.cost = (double)b.tasks * ((double)std::min<int64_t>(im.depth, im.g.n0) + 3.0) * (im.data2 ? 300.0 : 240.0);
+        b.cost = (double)im.units.tasks * ((double)im.g.n0 + 3.0 * (double)nb) * (im.data2 ? 300.0 : 240.0);
     } else {
         // whole chunks of rows per brick (the 2D march steps groups of rows)
-        im.depth = ((int64_t)(depth2 < 1 ? 1 : depth2) + kChunk2 - 1) / kChunk2 * kChunk2;
+        const int64_t rows = ((int64_t)(depth2 < 1 ? 1 : depth2) + kChunk2 - 1) / kChunk2 * kChunk2;
+        const int64_t nyb = (im.g.n1 + rows - 1) / rows;
+        b.bricks = (xpos + chunk - 1) / chunk * nyb;
+        b.brick_voxels = chunk * rows;
+        // the wave tasks' blocks share the image's rows evenly
+        im.depth = ((im.g.n1 + nyb - 1) / nyb + kChunk2 - 1) / kChunk2 * kChunk2;
         im.units = units_2d(im.g, construction, im.depth);
-        b.bricks = (xpos + chunk - 1) / chunk * ((im.g.n1 + im.depth - 1) / im.depth);
-        b.brick_voxels = chunk * im.depth;
-        b.tasks = (int64_t)im.units.tasks;
+        b.steps = (int64_t)im.units.tasks * (im.depth / kChunk2);
         // 25 instructions a row, and about 20 rows' worth to start a task
-        b.cost = (double)b.tasks * ((double)std::min<int64_t>(im.depth, im.g.n1) + 20.0) * 25.0;
+        b.cost = (double)im.units.tasks * ((double)std::min<int64_t>(im.depth, im.g.n1) + 20.0) * 25.0;
     }
     b.cost /= (double)b.bricks;
     return b;

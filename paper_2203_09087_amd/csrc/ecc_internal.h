@@ -276,7 +276,7 @@ static_assert(sizeof(BatchImage) <= 160, "ecc_reserve's table bound counts 160 b
 
 // A run of one volume's work handled by one workgroup; its histogram lands in
 // partial row `slot`.  In the host's schedule [b0, b1) are bricks (BatchWork), in
-// the tables of the kernel the wave tasks that they stand for.
+// the tables of the kernel the steps that they stand for.
 struct BatchSeg {
     int32_t image;
     int32_t slot;
@@ -322,15 +322,16 @@ hipError_t launch_merge_batch(const BatchLaunch& B, hipStream_t s);
 // x-chunk of 63 * wpb position columns x kRows3 rows x depth3 planes (layout_3d);
 // 2D, a chunk x depth2 rows (a multiple of kChunk2).  The kernel divides the
 // volume into wave tasks (Units) instead; a run of bricks stands for the same
-// share of the volume's wave tasks, in order.
+// share of the steps of the volume's wave tasks, in order (3D: planes; 2D: groups of
+// kChunk2 rows).
 struct BatchWork {
     int64_t bricks;
     int64_t brick_voxels;   // whole brick, including any part outside the image
-    int64_t tasks;          // wave tasks of the volume
+    int64_t steps;          // of all wave tasks of the volume
     double cost;            // time of a brick, in vector instructions of a wave
 };
-// Sets the image's depth and units.
-BatchWork batch_work(BatchImage& im, int construction, int depth3, int depth2);
+// Sets the image's depth (3D: at most `planes`) and units.
+BatchWork batch_work(BatchImage& im, int construction, int depth3, int depth2, int64_t planes);
 constexpr int kBrickWaves = 9;                 // waves that a brick's width is chosen for
 
 // Launchers (ecc_kernels.hip: histogram kernels; ecc_reduce.hip: min/max,

@@ -664,6 +664,25 @@ __device__ __forceinline__ Task2 block_task(const Geom& G, const Units& Y, int64
     return K;
 }
 
+// Rows [r0, r1) of wave task K's blocks of `depth` rows (multiples of kChunk2), as a
+// task of its own; inactive where the image ends before them.
+__device__ __forceinline__ Task2 block_part(Task2 K, const Geom& G, int64_t depth, uint32_t row_bytes, uint32_t r0,
+                                            uint32_t r1)
+{
+    K.y0 += (int64_t)r0;
+    if (K.y0 >= G.n1) K.active = false;
+    if (r0 > 0u) K.first = 0u;
+    if ((int64_t)r1 < depth) {   // the row after them lies in the same block
+        K.xl[0] = K.lanes.xa + (r1 - r0) * row_bytes;
+        K.xl[1] = K.lanes.xb + (r1 - r0) * row_bytes;
+        K.oob_last = K.lanes.oob;
+    } else {
+        K.xl[0] -= r0 * row_bytes;
+        K.xl[1] -= r0 * row_bytes;
+    }
+    return K;
+}
+
 // Runs wave task K of the 2D image at data.
 template <int DT, int CONS, bool WIN, int IDENT>
 __device__ __forceinline__ void run_march_2d_as(const void* data, const Geom& G, int64_t depth, const BinParams& P,

@@ -200,3 +200,38 @@ def test_integer_levels_as_bins(oracle_mod, dtype):
                     assert np.array_equal(b.cpu().numpy(), w), (cons, lo, hi, r, nbins, h.shape, "batch")
         finally:
             ctx.close()
+
+
+@pytest.mark.parametrize("cons", ["vertex", "top"])
+def test_batch_parts_of_wave_tasks(oracle_mod, cons):
+    """Batches whose waves take several steps each (planes, or groups of 16 rows) and
+    start and end inside a wave task: ragged 2D and 3D images, blocks with fewer rows
+    than the others, 4D pair volumes, each type, at 1 to 4 workgroups per CU."""
+    from paper_2203_09087_amd import ecc
+    rng = np.random.default_rng(4600)
+    shapes = [(int(a), int(b)) for a, b in zip(rng.integers(100, 1500, 12), rng.integers(20, 1500, 12))]
+    shapes += [(129, 2500), (1700, 65), (17, 9000)]
+    shapes += [tuple(int(n) for n in rng.integers(20, 120, 3)) for _ in range(8)] + [(260, 50, 60), (3, 30, 50, 64)]
+    ctx = ecc.Context(0, cons)
+    try:
+        for kind in ("u8", "u16", "u16wide", "f32"):
+            drawn = [draw_image(rng, s, kind) for s in shapes]
+            nbins, r = drawn[0][1], drawn[0][2]
+            hosts = [d[0] for d in drawn]
+            devs = [to_dev(h) for h in hosts]
+            want = [oracle_mod.ecc(h, nbins, cons, value_range=r, threads=8) for h in hosts]
+            for part in (slice(0, 15), slice(15, 24), slice(0, None)):
+                say(f"case: parts {cons} {kind} {part} nbins={nbins}")
+                plan = ctx.plan_batch(devs[part], nbins, [r] * len(devs[part]))
+                for tuned in (False, True):
+                    if tuned:
+                        plan.autotune(1)
+                    for o in plan.outs:
+                        o.fill_(-1)
+                    plan.launch()
+                    torch.cuda.synchronize()
+                    for h, g, w in zip(hosts[part], plan.outs, want[part]):
+                        assert np.array_equal(g.cpu().numpy(), w), (cons, kind, h.shape, tuned)
+                plan.close()
+    finally:
+        ctx.close()
