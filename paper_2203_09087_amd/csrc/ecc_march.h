@@ -549,9 +549,16 @@ __device__ __forceinline__ void march_2d(const void* base, uint32_t row_bytes, c
     constexpr uint32_t M = CONS == CONS_VERTEX ? 0xFFFF0000u : 0x0000FFFFu;
     const Lanes& N = K.lanes;
     const uint32_t S = halves(H.sm);
-    const __amdgpu_buffer_rsrc_t rs = rsrc_at(base);
+    __amdgpu_buffer_rsrc_t rs = rsrc_at(base);
     T raw[G][2];
     uint32_t soff = 0;   // byte offset of the next row to load
+    // EDGE: the loads start anew at row r (the last readable one past it), from a
+    // 64-bit address.  A block's rows may span more than 4 GiB (rows of up to 2^27
+    // bytes, blocks of any depth); from one start to the next are 8 or 9 rows.
+    auto start_at = [&](uint32_t r) {
+        rs = rsrc_at((const char*)base + (int64_t)(r < avail ? r : avail - 1u) * (int64_t)row_bytes);
+        soff = 0;
+    };
     // loads row r (relative to the block): EDGE stays on the last readable row;
     // otherwise the row after the block takes the lanes' own places
     auto load = [&](int k, uint32_t r, bool last) {
@@ -595,6 +602,7 @@ __device__ __forceinline__ void march_2d(const void* base, uint32_t row_bytes, c
     const uint32_t plain = EDGE ? (rows < avail ? rows : rows - 1u) / G * G : rows - G;
     uint32_t y = 0;
     for (; y < plain; y += G) {
+        if (EDGE) start_at(y + 1u + (uint32_t)G);
 #pragma unroll
         for (int k = 0; k < G; ++k) {
             // the row's registers take the next group's row as soon as its key is made
