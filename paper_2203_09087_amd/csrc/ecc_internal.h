@@ -245,11 +245,12 @@ struct EccLaunch {
     uint32_t lds_bytes;            // dynamic LDS of the launch
 };
 // Partial-row words (grid x window) up to which the histogram kernel's last
-// workgroup merges the rows (fused_merge) instead of a launch of k_merge.  One
-// workgroup takes about 0.3 us per 1024 words, the launch about 1 us more than none:
-// 300^2 uint8, 2 to 4 thousand words, 9.5 us a call fused and 10.6 with the launch;
-// 24x30x40 uint8, 4 to 8 thousand, 13.1 and 11.0; 300^2 float32, 8 to 16 thousand,
-// 13.0 and 10.5; 100^3 uint8, 32 to 64 thousand, 34.4 and 11.6.
+// workgroup merges the rows (fused_merge) instead of a launch of k_merge.  In us a
+// call, merged so and with the launch: 64^2 float32, 500 bins (up to 2048 words) 8.7
+// and 11.2; 300^2 uint8 (2 to 4 thousand) 8.9 and 11.5; 400^2 uint8 (4 to 6 thousand)
+// 9.6 and 11.6; 700^2 uint8 (8 to 16 thousand) 12.1 and 11.6; 60^3 uint8 13.8 and
+// 11.4; 100^3 uint8 (32 to 64 thousand) 24.5 and 11.6.  The line lies on the safe
+// side of the crossing, which is near 8 thousand.
 constexpr int64_t kFusedMergeWords = int64_t(1) << 12;
 
 // ---------------------------------------------------------------- batches
