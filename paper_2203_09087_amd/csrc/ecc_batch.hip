@@ -145,18 +145,28 @@ hipError_t launch_ecc_batch(const BatchLaunch& B, int construction, hipStream_t 
 
 hipError_t launch_merge_batch(const BatchLaunch& B, hipStream_t s)
 {
-    if (B.count <= 0) return hipSuccess;
-    MergeArgs A = {};
-    A.partials = B.partials;
-    A.slot_off = B.slot_off;
-    A.slots = B.slots;
-    A.images = B.images;
-    A.width = B.width;
-    A.bin_lo = B.bin_lo;
-    A.sign = 1;
-    // few rows per image (many images): fewer threads per bin
-    if (B.avg_rows <= 12) return launch_merge_k<4, 64>(A, B.count, s);
-    return B.width >= kWideMerge ? launch_merge_k<32, 32>(A, B.count, s) : launch_merge_k<64, 16>(A, B.count, s);
+    // A launch takes at most 65535 images: the device reports 65536 blocks at most on
+    // the grid's second axis.  (The images on the first axis, the bins on the second:
+    // 16 images of 4096 bins 94 instead of 86 us a call; more of them along the third
+    // axis, which adds a check to every block: 0.3 us on a single image.)
+    constexpr int kMaxImages = 65535;
+    for (int64_t i0 = 0; i0 < B.count; i0 += kMaxImages) {
+        MergeArgs A = {};
+        A.partials = B.partials;
+        A.slot_off = B.slot_off + i0;
+        A.slots = B.slots;
+        A.images = B.images + i0;
+        A.width = B.width;
+        A.bin_lo = B.bin_lo;
+        A.sign = 1;
+        const int n = (int)std::min<int64_t>(B.count - i0, kMaxImages);
+        // few rows per image (many images): fewer threads per bin
+        const hipError_t e = B.avg_rows <= 12          ? launch_merge_k<4, 64>(A, n, s)
+                             : B.width >= kWideMerge ? launch_merge_k<32, 32>(A, n, s)
+                                                     : launch_merge_k<64, 16>(A, n, s);
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 }  // namespace ecc
