@@ -303,7 +303,7 @@ struct Sizes {
     int64_t depth;
     int32_t window;
     uint32_t hist_stride, hist_copies, lds_bytes;   // LDS layout of the histogram kernel
-    size_t off_counters, off_mm, off_carry, off_partials, total;
+    size_t off_counters, off_mm, off_partials, total;
 };
 
 // Launch shape of the main kernel for one image:
@@ -435,8 +435,7 @@ Sizes plan_sizes(const ecc_ctx* ctx, const Job& j, int32_t nbins, const ecc_laun
     s.grid = (int)std::max<int64_t>(grid, 1);
     s.off_counters = 0;   // fixed place, shared with the batch layout (never overwritten)
     s.off_mm = kCounterBytes;
-    s.off_carry = s.off_mm + align_up((size_t)(kMinmaxBlocks + 1) * 2 * sizeof(uint32_t));
-    s.off_partials = s.off_carry + align_up((size_t)s.grid * sizeof(int32_t));
+    s.off_partials = s.off_mm + align_up((size_t)(kMinmaxBlocks + 1) * 2 * sizeof(uint32_t));
     s.total = s.off_partials + align_up((size_t)s.grid * (size_t)s.window * sizeof(int32_t));
     return s;
 }
@@ -565,11 +564,11 @@ ecc_status enqueue_hist(ecc_ctx* ctx, char* base, const Job& j, int32_t nbins, h
     L.npass = j.npass;
     L.pass_stride = j.pass_stride;
     L.partials = (int32_t*)(base + sz.off_partials);
+    L.row_stride = sz.window;
     L.flush_add = pass_add ? 1 : 0;
     L.flush_sign = sign;
     L.out = j.out;
     L.counter = counters;
-    L.carry = (int32_t*)(base + sz.off_carry);
     L.fused = 0;
     L.hist_stride = sz.hist_stride;
     L.hist_copies = sz.hist_copies;
@@ -603,6 +602,7 @@ ecc_status enqueue_hist(ecc_ctx* ctx, char* base, const Job& j, int32_t nbins, h
             return hip_fail(ctx, e, "ecc launch");
         ecc::MergeArgs A = {};
         A.partials = L.partials;
+        A.row_stride = L.row_stride;
         A.rows = L.grid * L.npass;
         A.out = j.out;
         A.width = L.width;
@@ -738,6 +738,7 @@ ecc_status enqueue_4d_part(ecc_ctx* ctx, char* base, const Sizes& sz, Job h, con
     if (one_merge) {
         ecc::MergeArgs A = {};
         A.partials = (int32_t*)(base + sz.off_partials);
+        A.row_stride = nbins;
         A.rows = (int)rows;
         A.out = h.out;
         A.width = nbins;
@@ -855,7 +856,7 @@ ecc_status ensure_staging(ecc_ctx* ctx, size_t bytes, ecc_ctx::Staging** out)
 // same in the pinned staging buffer and in device memory), followed by the
 // partial histogram rows on the device.
 struct BatchLayout {
-    size_t images, segs, wg_seg, slot_off, slots, mm, pieces, tables_end, carry, partials, total;
+    size_t images, segs, wg_seg, slot_off, slots, mm, pieces, tables_end, partials, total;
 };
 
 struct BatchGroup {
@@ -1053,8 +1054,7 @@ void build_batch_tables(int cu_count, int construction, const std::vector<Job>& 
     lay.mm = align_up(lay.slots + T.slots.size() * sizeof(int32_t));
     lay.pieces = align_up(lay.mm + T.mm.size() * sizeof(uint32_t));
     lay.tables_end = align_up(lay.pieces + T.pieces.size() * sizeof(ecc::BatchPiece));
-    lay.carry = lay.tables_end;
-    lay.partials = align_up(lay.carry + (size_t)nseg * sizeof(int32_t));
+    lay.partials = lay.tables_end;
     lay.total = lay.partials + align_up((size_t)nseg * (size_t)T.window * sizeof(int32_t));
 }
 
@@ -1099,7 +1099,7 @@ ecc_status launch_batch_kernels(ecc_ctx* ctx, const BatchTables& T, char* d, boo
     B.slots = (const int32_t*)(d + lay.slots);
     B.mm = (uint32_t*)(d + lay.mm);
     B.partials = (int32_t*)(d + lay.partials);
-    B.carry = (int32_t*)(d + lay.carry);
+    B.row_stride = T.window;
     B.avg_rows = (int32_t)(T.segs.size() / (size_t)T.count);
     B.nbins = T.nbins;
     B.windowed = T.window < T.nbins ? 1 : 0;

@@ -153,6 +153,7 @@ hipError_t launch_merge_batch(const BatchLaunch& B, hipStream_t s)
     for (int64_t i0 = 0; i0 < B.count; i0 += kMaxImages) {
         MergeArgs A = {};
         A.partials = B.partials;
+        A.row_stride = B.row_stride;
         A.slot_off = B.slot_off + i0;
         A.slots = B.slots;
         A.images = B.images + i0;

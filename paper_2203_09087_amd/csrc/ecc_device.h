@@ -303,12 +303,13 @@ __device__ __forceinline__ int32_t wave_scan32(int32_t v)
 
 // Prefix-sums the workgroup histogram (negated with sign -1) into its partial row
 // dst[0..width), or adds it to what dst holds (add).  With windows the row goes on
-// from the sum of the windows before (`first` window: 0), which `carry` keeps.  The
-// merge then only adds rows (ecc_merge.h).  An int32 holds every prefix: a
+// from the sum of the windows before: prev (null for the first window) is the last
+// word that the window before left in this row.  The merge then only adds rows
+// (ecc_merge.h).  An int32 holds every prefix: a
 // workgroup takes at most 2^27 voxels of at most 8 in absolute value.  Each wave
 // scans a run of 64-bin segments in place in LDS, then adds the runs before it.
 __device__ __forceinline__ void flush_hist(const HistRef& H, int32_t* dst, int width, bool add, int sign,
-                                           int32_t* carry, bool first)
+                                           const int32_t* prev = nullptr)
 {
     __shared__ int32_t run_total[kMaxWaves];
     __syncthreads();
@@ -323,13 +324,11 @@ __device__ __forceinline__ void flush_hist(const HistRef& H, int32_t* dst, int w
         run = __builtin_amdgcn_readlane(v, 63);
     }
     if (lane == 0) run_total[w] = run;
-    const int32_t from = carry && !first ? *carry : 0;
+    // (read before the barrier: the row is overwritten after it)
+    const int32_t from = prev ? (sign < 0 ? -*prev : *prev) : 0;
     __syncthreads();
-    int32_t before = from, total = from;
-    for (int k = 0; k < waves; ++k) {
-        before += k < w ? run_total[k] : 0;
-        total += run_total[k];
-    }
+    int32_t before = from;
+    for (int k = 0; k < waves; ++k) before += k < w ? run_total[k] : 0;
 #pragma unroll 4
     for (int s = s0; s < s1; ++s) {
         const int j = s * 64 + lane;
@@ -338,7 +337,6 @@ __device__ __forceinline__ void flush_hist(const HistRef& H, int32_t* dst, int w
             dst[j] = (add ? dst[j] : 0) + (sign < 0 ? -v : v);
         }
     }
-    if (carry && threadIdx.x == 0) *carry = total;
 }
 
 // Values the whole wave shares, read back from the first lane so that the

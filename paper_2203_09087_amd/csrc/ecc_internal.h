@@ -233,12 +233,12 @@ struct EccLaunch {
     // plus y * pass_stride bytes; its histograms go to partial rows y * grid ..
     int32_t npass;
     int64_t pass_stride;
-    int32_t* partials;             // [grid * npass][width] workgroup histograms, prefix-summed
+    int32_t* partials;             // [grid * npass][row_stride] workgroup histograms, prefix-summed
+    int32_t row_stride;            // bins of a whole window (the last window may be narrower: width)
     int32_t flush_add;             // add the workgroup histogram to its partial row (else write it)
     int32_t flush_sign;            // +1, or -1: the histogram enters its row negated
     int64_t* out;                  // the caller's output
     uint32_t* counter;             // the fused merge's
-    int32_t* carry;                // windows: each workgroup's sum over the windows before this one
     int32_t fused;                 // one window, few rows: the last workgroup merges and scans into out
     uint32_t hist_stride;          // LDS words between the histogram copies (lds_stride(width))
     uint32_t hist_copies;          // copies of the histogram (a power of two up to kMaxHistCopies)
@@ -301,8 +301,8 @@ struct BatchLaunch {
     const int32_t* slot_off;    // image i owns partial rows slots[slot_off[i] .. slot_off[i+1])
     const int32_t* slots;
     uint32_t* mm;               // [count][2] min/max keys of AUTO images
-    int32_t* partials;          // [nslots][width]
-    int32_t* carry;             // windows: each row's sum over the windows before this one
+    int32_t* partials;          // [nslots][row_stride]
+    int32_t row_stride;         // bins of a whole window
     int32_t avg_rows;           // partial rows per image, on average
     int32_t nbins, bin_lo, width, windowed;
     int32_t grid, waves;
@@ -364,7 +364,8 @@ hipError_t launch_batch_dt(const BatchLaunch& B, int construction, hipStream_t s
 // The merge of partial rows into out[bin_lo .. bin_lo + width) of one image or of
 // every image of a batch (ecc_merge.h).
 struct MergeArgs {
-    const int32_t* partials;       // rows of `width` bins, prefix-summed
+    const int32_t* partials;       // rows of `width` bins, row_stride words apart, prefix-summed
+    int32_t row_stride;
     int rows;                      // one image: rows 0 .. rows - 1
     const int32_t* slot_off;       // a batch: image i has rows slots[slot_off[i] .. slot_off[i + 1])
     const int32_t* slots;

@@ -35,8 +35,9 @@ __global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(
         run_march_3d<DT, CONS, kStripRows, WIN, PAIR>(L, P, H, K, z0, ze);
     }
     const size_t row = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
-    flush_hist(H, L.partials + row * (size_t)L.width, L.width, L.flush_add != 0, L.flush_sign, WIN ? L.carry + row : nullptr,
-               L.bin_lo == 0);
+    int32_t* dst = L.partials + row * (size_t)(WIN ? L.row_stride : L.width);
+    flush_hist(H, dst, L.width, L.flush_add != 0, L.flush_sign,
+               WIN && L.bin_lo > 0 ? dst + L.row_stride - 1 : nullptr);
     if (L.fused) fused_merge(hist, L.partials, L.width, L.out, L.counter);
 }
 
@@ -54,8 +55,9 @@ __global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(
     for (uint32_t task = blockIdx.x * waves + (uint32_t)wave_id(); task < L.units.tasks; task += gridDim.x * waves)
         run_march_2d<DT, CONS, WIN>(L.data, L.g, L.depth, P, W, H,
                                     block_task<DT, CONS>(L.g, L.units, L.depth, H.sm, task));
-    flush_hist(H, L.partials + (size_t)blockIdx.x * (size_t)L.width, L.width, L.flush_add != 0, L.flush_sign,
-               WIN ? L.carry + blockIdx.x : nullptr, L.bin_lo == 0);
+    int32_t* dst = L.partials + (size_t)blockIdx.x * (size_t)(WIN ? L.row_stride : L.width);
+    flush_hist(H, dst, L.width, L.flush_add != 0, L.flush_sign,
+               WIN && L.bin_lo > 0 ? dst + L.row_stride - 1 : nullptr);
     if (L.fused) fused_merge(hist, L.partials, L.width, L.out, L.counter);
 }
 
@@ -129,8 +131,9 @@ void k_ecc_batch(BatchLaunch B)
             a += s1 - s0;
         }
         const size_t slot = (size_t)uniform_u32((uint32_t)S.slot);
-        flush_hist(H, B.partials + slot * (size_t)B.width, B.width, false, (int)uniform_u32((uint32_t)I.sign),
-                   WIN ? B.carry + slot : nullptr, B.bin_lo == 0);
+        int32_t* dst = B.partials + slot * (size_t)(WIN ? B.row_stride : B.width);
+        flush_hist(H, dst, B.width, false, (int)uniform_u32((uint32_t)I.sign),
+                   WIN && B.bin_lo > 0 ? dst + B.row_stride - 1 : nullptr);
         __syncthreads();   // the histogram is read before the next segment clears it
     }
 }

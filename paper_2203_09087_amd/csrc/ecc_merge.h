@@ -39,7 +39,7 @@ __global__ __launch_bounds__(RG * BB) void k_merge(MergeArgs A)
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int k = min(r + u * RG, r1 - 1);
-            x[u] = col[(size_t)(A.slots ? A.slots[k] : k) * (size_t)A.width];
+            x[u] = col[(size_t)(A.slots ? A.slots[k] : k) * (size_t)A.row_stride];
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) sum += r + u * RG < r1 ? x[u] : 0;

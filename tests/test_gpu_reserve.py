@@ -1,0 +1,59 @@
+"""GPU: calls that fit the documented scratch bound of ecc_reserve neither allocate
+nor wait.  Growing the scratch waits for the whole device, so a call that grew it
+would return only after the products that another stream is busy with."""
+import sys
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def busy_stream():
+    """A stream with about 100 ms of work on it, and the event that ends it."""
+    a = torch.ones((8192, 8192), device="cuda", dtype=torch.bfloat16)
+    b = torch.empty_like(a)
+    torch.mm(a, a, out=b)
+    torch.cuda.synchronize()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        for _ in range(100):
+            torch.mm(a, a, out=b)
+        done = torch.cuda.Event()
+        done.record(side)
+    return done, (a, b, side)
+
+
+def does_not_wait(call):
+    done, keep = busy_stream()
+    assert not done.query()
+    out = call()
+    waited = done.query()
+    torch.cuda.synchronize()
+    del keep
+    assert not waited, "the call waited for the device"
+    return out
+
+
+def test_batch_of_three_types_and_few_bins():
+    """Few images of three data types: as many workgroup segments as the bound has
+    room for, each with the shortest row."""
+    from paper_2203_09087_amd import ecc
+    rng = np.random.default_rng(61)
+    vols = [torch.from_numpy(rng.integers(0, 100, size=(128, 128, 128)).astype(t)).cuda() for t in ("u1", "i2", "f4")]
+    ranges = [(0, 99)] * 3
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    scratch, tables = ecc.batch_reserve_bytes(3, 3 * 128 ** 3, 1, cus)
+    print(f"case: 3 volumes of 128^3, 1 bin, {scratch} bytes reserved", flush=True, file=sys.stderr)
+    first, ctx = ecc.Context(0, "vertex"), ecc.Context(0, "vertex")
+    try:
+        first.compute_batch(vols, 1, value_ranges=ranges)   # loads the kernels
+        ctx.reserve(scratch, tables)
+        outs = torch.zeros((3, 1), dtype=torch.int64, device="cuda")
+        does_not_wait(lambda: ctx.compute_batch(vols, 1, value_ranges=ranges, outs=list(outs)))
+        assert outs.cpu().tolist() == [[1], [1], [1]]
+    finally:
+        first.close()
+        ctx.close()
