@@ -368,9 +368,11 @@ void pick_shape(const ecc_ctx* ctx, const Job& j, const ecc_launch_shape* tuned,
         // bricks of a block of rows (2D, fractional: blocks share bricks) or planes
         const double per_block = flat ? tasks / w : std::ceil(tasks / w);
         const int rmax = resident(w);
-        // at most the rows that ecc_reserve's bound holds (6 per CU of kMaxLdsBins bins)
+        // at most the rows that ecc_reserve's bound holds (6 per CU of kMaxLdsBins bins);
+        // a set shape may ask for more of them, but not of wider ones
         int r0 = 1, r1 = std::max(1, std::min(rmax, 6 * ecc::kMaxLdsBins / std::max(s.window, ecc::kMaxLdsBins)));
-        if (tuned && tuned->wgs_per_cu > 0) r0 = r1 = std::min(tuned->wgs_per_cu, rmax);
+        if (tuned && tuned->wgs_per_cu > 0)
+            r0 = r1 = std::min(tuned->wgs_per_cu, s.window > ecc::kMaxLdsBins ? r1 : rmax);
         for (int r = r0; r <= r1; ++r) {
             const double gx = std::max(1.0, std::floor(cus * r / npass));   // workgroups per pass
             for (int k = 1; k <= 3; ++k) {

@@ -57,3 +57,29 @@ def test_batch_of_three_types_and_few_bins():
     finally:
         first.close()
         ctx.close()
+
+
+@pytest.mark.parametrize("wgs", [0, 1, 2, 16])
+def test_wide_histogram_at_a_set_number_of_workgroups(oracle_mod, wgs):
+    """16384 bins in one pass: 64 KB a workgroup row, two workgroups fit a CU, and the
+    bound has room for one row per CU of that width."""
+    from paper_2203_09087_amd import ecc
+    rng = np.random.default_rng(62)
+    host = rng.integers(0, 16384, size=(160, 160, 160)).astype(np.uint16)
+    vol = torch.from_numpy(host.view(np.int16)).cuda()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    scratch, tables = ecc.batch_reserve_bytes(1, host.size, 16384, cus)
+    print(f"case: 160^3 uint16, 16384 bins, {wgs} workgroups per CU, {scratch} bytes reserved", flush=True,
+          file=sys.stderr)
+    first, ctx = ecc.Context(0, "vertex"), ecc.Context(0, "vertex")
+    try:
+        first.compute(vol, 16384, value_range=(0, 16383))
+        ctx.reserve(scratch, tables)
+        ctx.set_launch_shape(vol, 16384, waves=4, depth=2, wgs_per_cu=wgs)   # 720 bricks
+        out = torch.zeros(16384, dtype=torch.int64, device="cuda")
+        does_not_wait(lambda: ctx.compute(vol, 16384, value_range=(0, 16383), out=out))
+        assert np.array_equal(out.cpu().numpy(),
+                              oracle_mod.ecc(host, 16384, "vertex", value_range=(0, 16383), threads=8))
+    finally:
+        first.close()
+        ctx.close()
