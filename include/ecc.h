@@ -314,9 +314,10 @@ ecc_status ecc_batch_plan_destroy(ecc_batch_plan* plan);
  * `cu_count` compute units.  The bricks of every image (the units its work is
  * counted in; a run of them stands for the same share of the image's wave tasks)
  * are cut into segments, one workgroup histogram each; a segment covers at most
- * 2^27 voxels, so its
- * int32 counters cannot overflow (a voxel position adds at most 8 in absolute
- * value; Sec. 4.3's shared-memory counters hold the sums).  Outputs (HOST
+ * 2^27 voxels, so the
+ * prefix sums of its int32 row cannot overflow (the cells at a position that lie in
+ * a sublevel set add up to between -2 and 1; Sec. 4.3's shared-memory counters hold
+ * the sums).  Outputs (HOST
  * pointers): *segments = the number of segments, *max_segment_voxels = the most
  * voxels one segment covers (whole bricks), and, if not null, image_bricks[i] =
  * the bricks of image i and covered_bricks[i] = the bricks of image i that

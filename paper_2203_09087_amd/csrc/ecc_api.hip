@@ -308,9 +308,8 @@ struct Sizes {
 
 // Launch shape of the main kernel for one image:
 //  - waves, depth and workgroups: pick_shape;
-//  - grid: at least enough that no workgroup histogram can reach 2^31 (every
-//    voxel position adds at most 8 in absolute value: four type counts of at
-//    most 1, and at a brick's last plane four more).
+//  - grid: at least one workgroup per 2^27 voxels, which keeps the rows below 2^31
+//    (flush_hist).
 using TuneKey = std::tuple<int, int, int, int, int64_t, int64_t, int64_t>;
 
 // Constants of pick_shape's model: planes' (rows') worth of work a brick starts
@@ -713,7 +712,7 @@ ecc_status enqueue_4d_part(ecc_ctx* ctx, char* base, const Sizes& sz, Job h, con
     // With one LDS window every launch adds into the same workgroup rows and one
     // merge follows, when the int32 rows cannot overflow: a row's workgroup sees
     // at most ceil(bricks / gx) bricks of waves x 2 x 63 slots x rows x depth
-    // voxels per launch, and a voxel adds at most 8 in absolute value.
+    // positions per launch, each changing a prefix sum by at most 2.
     const int64_t bricks = ecc::wg_bricks(3, ctx->construction, h.g, sz.waves, sz.depth);
     const int64_t brick_vox = 2 * ecc::kLaneCols * sz.waves * ecc::kStripRows * sz.depth;
     int64_t per_row = 0;
@@ -888,10 +887,7 @@ struct BatchTables {
 constexpr ecc_batch_shape kDefaultBatchShape = {8, 128, 0, 0, 0.0};   // wgs_per_cu 0: batch_wgs
 
 // Voxels one batch segment may cover (counted over whole bricks, so including
-// brick parts outside the image).  Its workgroup histogram and its partial row
-// are int32 and a voxel position adds at most 8 in absolute value (four type
-// counts of at most 1 in 3D, two in 2D, and as many again at a brick's last
-// plane or row), so 2^27 voxels keep every counter below 2^31.
+// brick parts outside the image): its partial row is int32 (flush_hist).
 constexpr int64_t kSegVoxels = int64_t(1) << 27;
 
 // Workgroups per CU of a batch launch with `work` vector instructions per CU.  More

@@ -305,8 +305,11 @@ __device__ __forceinline__ int32_t wave_scan32(int32_t v)
 // dst[0..width), or adds it to what dst holds (add).  With windows the row goes on
 // from the sum of the windows before: prev (null for the first window) is the last
 // word that the window before left in this row.  The merge then only adds rows
-// (ecc_merge.h).  An int32 holds every prefix: a
-// workgroup takes at most 2^27 voxels of at most 8 in absolute value.  Each wave
+// (ecc_merge.h).  An int32 holds every prefix: the cells at a position that lie in a
+// sublevel set add up to between -2 and 1, and a workgroup counts fewer than 2^30
+// positions (about 2^27 voxels; four times that where most of an image's wave tasks
+// are nearly empty).  Counters may pass 2^31 on the way, 32-bit sums are exact modulo
+// 2^32.  Each wave
 // scans a run of 64-bin segments in place in LDS, then adds the runs before it.
 __device__ __forceinline__ void flush_hist(const HistRef& H, int32_t* dst, int width, bool add, int sign,
                                            const int32_t* prev = nullptr)
