@@ -876,6 +876,7 @@ struct BatchTables {
     std::vector<ecc::BatchWork> work;    // of each volume
     std::vector<ecc::BatchSeg> segs;     // in bricks (the kernel's table: in wave tasks)
     std::vector<int32_t> wg_seg, slot_off, slots;
+    int32_t max_rows = 0;                // partial rows of the image with the most of them
     std::vector<uint32_t> mm;
     std::vector<ecc::BatchPiece> pieces;
     std::vector<BatchGroup> groups;
@@ -1029,6 +1030,7 @@ void build_batch_tables(int cu_count, int construction, const std::vector<Job>& 
     T.slot_off.assign((size_t)count + 1, 0);
     T.slots.assign((size_t)nseg, 0);
     for (const auto& sg : T.segs) T.slot_off[(size_t)T.images[(size_t)sg.image].owner + 1]++;
+    T.max_rows = *std::max_element(T.slot_off.begin(), T.slot_off.end());
     for (int i = 0; i < count; ++i) T.slot_off[(size_t)i + 1] += T.slot_off[(size_t)i];
     {
         std::vector<int32_t> fill(T.slot_off.begin(), T.slot_off.end() - 1);
@@ -1099,6 +1101,7 @@ ecc_status launch_batch_kernels(ecc_ctx* ctx, const BatchTables& T, char* d, boo
     B.partials = (int32_t*)(d + lay.partials);
     B.row_stride = T.window;
     B.avg_rows = (int32_t)(T.segs.size() / (size_t)T.count);
+    B.max_rows = T.max_rows;
     B.nbins = T.nbins;
     B.windowed = T.window < T.nbins ? 1 : 0;
     B.hist_stride = ecc::lds_stride(T.window);

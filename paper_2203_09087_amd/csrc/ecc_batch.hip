@@ -67,6 +67,47 @@ __global__ __launch_bounds__(kThreads) void k_minmax_batch(const BatchImage* ima
     }
 }
 
+// The merge of a batch of many images with few rows each: a thread adds N bins (one
+// per kThreads) of its image's rows, four rows at a time, without LDS.  k_merge's
+// blocks of 64 bins are launch-bound there: about 1.4 ns each (2000 images of one
+// row, 4096 bins: 128000 blocks, 174 us).
+template <int N>
+__global__ __launch_bounds__(kThreads) void k_merge_rows(MergeArgs A)
+{
+    constexpr int U = 4;
+    const int img = blockIdx.y;
+    const int j0 = (int)blockIdx.x * kThreads * N + (int)threadIdx.x;
+    const int r0 = A.slot_off[img], r1 = A.slot_off[img + 1];
+    int64_t sum[N] = {};
+    for (int r = r0; r < r1; r += U) {
+        // rows past the last re-read it and are dropped; so are bins past the window
+        int32_t x[U][N];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int32_t* row = A.partials + (size_t)A.slots[min(r + u, r1 - 1)] * (size_t)A.row_stride;
+#pragma unroll
+            for (int n = 0; n < N; ++n) x[u][n] = row[min(j0 + n * kThreads, A.width - 1)];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int n = 0; n < N; ++n) sum[n] += r + u < r1 ? x[u][n] : 0;
+    }
+    int64_t* out = A.images[img].out + A.bin_lo;
+#pragma unroll
+    for (int n = 0; n < N; ++n)
+        if (j0 + n * kThreads < A.width) out[j0 + n * kThreads] = sum[n];
+}
+
+template <int N>
+hipError_t launch_merge_rows(const MergeArgs& A, int images, hipStream_t s)
+{
+    constexpr int bins = kThreads * N;
+    hipLaunchKernelGGL((k_merge_rows<N>), dim3((unsigned)((A.width + bins - 1) / bins), (unsigned)images), dim3(kThreads),
+                       0, s, A);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 BatchWork batch_work(BatchImage& im, int construction, int depth3, int depth2, int64_t planes)
@@ -161,10 +202,19 @@ hipError_t launch_merge_batch(const BatchLaunch& B, hipStream_t s)
         A.bin_lo = B.bin_lo;
         A.sign = 1;
         const int n = (int)std::min<int64_t>(B.count - i0, kMaxImages);
-        // few rows per image (many images): fewer threads per bin
-        const hipError_t e = B.avg_rows <= 12          ? launch_merge_k<4, 64>(A, n, s)
-                             : B.width >= kWideMerge ? launch_merge_k<32, 32>(A, n, s)
-                                                     : launch_merge_k<64, 16>(A, n, s);
+        // Up to 32 rows for every image: a thread per bin (16 images of 1000^2, 4096 bins,
+        // about 17 rows each: 31 and 22 us a launch; 250 of 800^2 194 and 164), or per
+        // four bins where that leaves thousands of blocks (2000 of 16^2, 4096 bins: 83
+        // and 74).  It adds an image's rows four at a time in turn, so more of them
+        // take blocks of fewer bins (16 serving images, up to about 50 rows: 87.1 with
+        // it and 86.3 us; 3 of 64^3, about 170 rows: 23 and 18).
+        hipError_t e;
+        if (B.max_rows <= 32)
+            e = (int64_t)n * B.width > (int64_t(4096) * kThreads) ? launch_merge_rows<4>(A, n, s) : launch_merge_rows<1>(A, n, s);
+        else if (B.avg_rows <= 12)
+            e = launch_merge_k<4, 64>(A, n, s);
+        else
+            e = B.width >= kWideMerge ? launch_merge_k<32, 32>(A, n, s) : launch_merge_k<64, 16>(A, n, s);
         if (e != hipSuccess) return e;
     }
     return hipSuccess;

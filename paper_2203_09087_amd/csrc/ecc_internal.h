@@ -303,7 +303,7 @@ struct BatchLaunch {
     uint32_t* mm;               // [count][2] min/max keys of AUTO images
     int32_t* partials;          // [nslots][row_stride]
     int32_t row_stride;         // bins of a whole window
-    int32_t avg_rows;           // partial rows per image, on average
+    int32_t avg_rows, max_rows; // partial rows per image, on average and at most
     int32_t nbins, bin_lo, width, windowed;
     int32_t grid, waves;
     int32_t pairs;              // the launch counts pair volumes (4D images)
