@@ -891,6 +891,13 @@ constexpr ecc_batch_shape kDefaultBatchShape = {8, 128, 0, 0, 0.0};   // wgs_per
 // brick parts outside the image): its partial row is int32 (flush_hist).
 constexpr int64_t kSegVoxels = int64_t(1) << 27;
 
+// What a segment costs its workgroup beyond its marching, in vector instructions of a
+// wave: the chain of table reads, the first loads, the barriers, clearing and flushing,
+// about 5 us.  Without it a workgroup was given as many small images as have the
+// marching work of its share of a large one (1000 images of 16^2 and one of 3000^2,
+// uint8, 256 bins: 90 us and 40 with it; 512 uneven uint8 images 341 and 328).
+constexpr double kSegmentCost = 6000;
+
 // Workgroups per CU of a batch launch with `work` vector instructions per CU.  More
 // workgroups even out the end of the launch (two fit a CU at a time, the others
 // follow), but each clears, flushes and has merged a histogram of its own, about
@@ -973,7 +980,7 @@ void build_batch_tables(int cu_count, int construction, const std::vector<Job>& 
         T.work[(size_t)i] = w;
         bricks[(size_t)i] = w.bricks;
         T.owner_bricks[(size_t)im.owner] += w.bricks;
-        brick_cost[(size_t)i] = w.cost;
+        brick_cost[(size_t)i] = w.cost + kSegmentCost / (double)w.bricks;
         // a segment's histogram is an int32 row: at most kSegVoxels voxels each
         max_take[(size_t)i] = std::max<int64_t>(1, kSegVoxels / w.brick_voxels);
     }
@@ -983,17 +990,18 @@ void build_batch_tables(int cu_count, int construction, const std::vector<Job>& 
     // One launch per dtype present; the bricks of its volumes, in order, are cut
     // into one contiguous run per workgroup with about equal work.
     for (int dt = 0; dt < 3; ++dt) {
-        double total = 0;
+        double total = 0, work = 0;   // with and without the segments' own cost
         int64_t nbr = 0;
         bool pairs = false;
         for (int i : vols)
             if (T.images[(size_t)i].dtype == dt) {
                 total += bricks[(size_t)i] * brick_cost[(size_t)i];
+                work += bricks[(size_t)i] * T.work[(size_t)i].cost;
                 nbr += bricks[(size_t)i];
                 pairs = pairs || T.images[(size_t)i].data2 != nullptr;
             }
         if (nbr == 0) continue;
-        const int wgs = shape.wgs_per_cu > 0 ? shape.wgs_per_cu : batch_wgs(total / cu_count, T.window, ndtypes);
+        const int wgs = shape.wgs_per_cu > 0 ? shape.wgs_per_cu : batch_wgs(work / cu_count, T.window, ndtypes);
         const int G = (int)std::max<int64_t>(1, std::min<int64_t>(nbr, (int64_t)wgs * cu_count));
         // One workgroup per CU gets as many waves as two would have (16 uint16 images,
         // 4096 bins: 93 us with 8, 87 with 16).
@@ -1009,14 +1017,14 @@ void build_batch_tables(int cu_count, int construction, const std::vector<Job>& 
             while (b < bricks[(size_t)i]) {
                 // bricks of volume i that still fit in workgroup wg's share
                 const double room = per * (wg + 1) - acc;
-                int64_t take = (int64_t)std::ceil(room / brick_cost[(size_t)i] - 1e-9);
+                int64_t take = (int64_t)std::ceil(room / brick_cost[(size_t)i] - 1e-6);
                 if (wg == G - 1) take = bricks[(size_t)i] - b;
                 take = std::max<int64_t>(1, std::min<int64_t>(take, bricks[(size_t)i] - b));
                 take = std::min<int64_t>(take, max_take[(size_t)i]);
                 T.segs.push_back(ecc::BatchSeg{i, (int32_t)T.segs.size(), b, b + take});
                 acc += take * brick_cost[(size_t)i];
                 b += take;
-                if (acc >= per * (wg + 1) - 1e-9 && wg < G - 1) {
+                if (acc >= per * (wg + 1 - 1e-6) && wg < G - 1) {
                     ++wg;
                     T.wg_seg.push_back((int32_t)T.segs.size());
                 }
