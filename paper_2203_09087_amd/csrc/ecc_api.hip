@@ -292,7 +292,12 @@ ecc::BinParams host_params(const Job& j, int32_t nbins)
         p.ihi = ihi;
         const bool whole = ilo == 0u && ihi == (j.dtype == ECC_U8 ? 255u : 65535u);
         p.ident = (uint32_t)nbins == D ? (whole ? ecc::kIdentRaw : ecc::kIdentLevel) : 0;
-        p.rcp = std::nextafter(1.0 / (double)D, HUGE_VAL);
+        // one step above the quotient (positive and normal)
+        const double q = 1.0 / (double)D;
+        uint64_t bits;
+        memcpy(&bits, &q, sizeof bits);
+        bits += 1;
+        memcpy(&p.rcp, &bits, sizeof bits);
     }
     return p;
 }
@@ -980,7 +985,7 @@ void build_batch_tables(int cu_count, int construction, const std::vector<Job>& 
         T.work[(size_t)i] = w;
         bricks[(size_t)i] = w.bricks;
         T.owner_bricks[(size_t)im.owner] += w.bricks;
-        brick_cost[(size_t)i] = w.cost + kSegmentCost / (double)w.bricks;
+        brick_cost[(size_t)i] = (w.cost + kSegmentCost) / (double)w.bricks;
         // a segment's histogram is an int32 row: at most kSegVoxels voxels each
         max_take[(size_t)i] = std::max<int64_t>(1, kSegVoxels / w.brick_voxels);
     }
@@ -995,8 +1000,8 @@ void build_batch_tables(int cu_count, int construction, const std::vector<Job>& 
         bool pairs = false;
         for (int i : vols)
             if (T.images[(size_t)i].dtype == dt) {
-                total += bricks[(size_t)i] * brick_cost[(size_t)i];
-                work += bricks[(size_t)i] * T.work[(size_t)i].cost;
+                work += T.work[(size_t)i].cost;
+                total += T.work[(size_t)i].cost + kSegmentCost;
                 nbr += bricks[(size_t)i];
                 pairs = pairs || T.images[(size_t)i].data2 != nullptr;
             }
@@ -1067,9 +1072,11 @@ void build_batch_tables(int cu_count, int construction, const std::vector<Job>& 
 }
 
 // The steps of a volume's wave tasks before its brick b: steps * b / bricks, rounded
-// down.
+// down (most segments of many small images are whole images: no division).
 int64_t share(const ecc::BatchWork& w, int64_t b)
 {
+    if (b == 0) return 0;
+    if (b == w.bricks) return w.steps;
     return (int64_t)((unsigned __int128)w.steps * (uint64_t)b / (uint64_t)w.bricks);
 }
 

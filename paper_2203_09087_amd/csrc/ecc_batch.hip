@@ -148,13 +148,12 @@ BatchWork batch_work(BatchImage& im, int construction, int depth3, int depth2, i
         b.bricks = (xpos + chunk - 1) / chunk * nyb;
         b.brick_voxels = chunk * rows;
         // the wave tasks' blocks share the image's rows evenly
-        im.depth = ((im.g.n1 + nyb - 1) / nyb + kChunk2 - 1) / kChunk2 * kChunk2;
+        im.depth = ((nyb == 1 ? im.g.n1 : (im.g.n1 + nyb - 1) / nyb) + kChunk2 - 1) / kChunk2 * kChunk2;
         im.units = units_2d(im.g, construction, im.depth);
         b.steps = (int64_t)im.units.tasks * (im.depth / kChunk2);
         // 25 instructions a row, and about 20 rows' worth to start a task
         b.cost = (double)im.units.tasks * ((double)std::min<int64_t>(im.depth, im.g.n1) + 20.0) * 25.0;
     }
-    b.cost /= (double)b.bricks;
     return b;
 }
 

@@ -198,8 +198,12 @@ inline Units units_3d(const Geom& g, int construction)
 }
 inline Units units_2d(const Geom& g, int construction, int64_t depth)
 {
-    const int64_t nyb = (g.n1 + depth - 1) / depth;
     const int64_t slots = axis_positions(g.n2, construction) + 1, per = 2 * kLaneCols;
+    if (g.n1 < depth) {   // one block, by itself (what follows gives the same)
+        const uint32_t tasks = (uint32_t)((slots + per - 1) / per);
+        return Units{(uint32_t)slots, 0u, 0u, 0u, tasks, tasks};
+    }
+    const int64_t nyb = (g.n1 + depth - 1) / depth;
     // a lane's rows reach up to `span` blocks past the wave's first row
     const int64_t span = (slots + per) / slots + 2;
     const bool flat = depth % 8 == 0 && (double)span * (double)depth * (double)(g.n2 * 4) < 2147483648.0;
@@ -330,7 +334,7 @@ struct BatchWork {
     int64_t bricks;
     int64_t brick_voxels;   // whole brick, including any part outside the image
     int64_t steps;          // of all wave tasks of the volume
-    double cost;            // time of a brick, in vector instructions of a wave
+    double cost;            // time of the marching, in vector instructions of a wave
 };
 // Sets the image's depth (3D: at most `planes`) and units.
 BatchWork batch_work(BatchImage& im, int construction, int depth3, int depth2, int64_t planes);
