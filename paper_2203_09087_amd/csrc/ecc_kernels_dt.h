@@ -32,7 +32,7 @@ __global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(
         const uint32_t z0 = zb * (uint32_t)L.depth;
         const uint32_t ze = (int64_t)z0 + L.depth < L.z_own ? z0 + (uint32_t)L.depth : (uint32_t)L.z_own;
         const Task3 K = strip_task<DT, CONS, kStripRows>(L.g, L.units, H.sm, r * waves + (uint32_t)wave_id());
-        run_march_3d<DT, CONS, kStripRows, WIN, PAIR>(L, P, H, K, z0, ze);
+        run_march_3d<DT, CONS, kStripRows, WIN, PAIR, !PAIR>(L, P, H, K, z0, ze);
     }
     const size_t row = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
     int32_t* dst = L.partials + row * (size_t)(WIN ? L.row_stride : L.width);
