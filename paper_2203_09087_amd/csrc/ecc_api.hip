@@ -275,6 +275,21 @@ ecc_status validate(ecc_ctx* ctx, const ecc_image& im, int32_t nbins, const char
     return ECC_OK;
 }
 
+// The images of a batch.  The text that names an image is only made for a bad one
+// (made for every image it was half the call's time: 2000 images of 16^2 uint8 170 us
+// a call, 96 without).
+ecc_status validate_batch(ecc_ctx* ctx, const ecc_image* imgs, int32_t count, int32_t nbins, const char* name,
+                          std::vector<Job>& jobs)
+{
+    for (int32_t i = 0; i < count; ++i) {
+        if (validate(ctx, imgs[i], nbins, "", &jobs[(size_t)i], 4) == ECC_OK) continue;
+        char where[64];
+        snprintf(where, sizeof where, "%s: image %d", name, i);
+        return validate(ctx, imgs[i], nbins, where, &jobs[(size_t)i], 4);
+    }
+    return ECC_OK;
+}
+
 ecc::BinParams host_params(const Job& j, int32_t nbins)
 {
     ecc::BinParams p = {};
@@ -1510,12 +1525,8 @@ ecc_status ecc_compute_batch(ecc_ctx* ctx, const ecc_image* imgs, int32_t count,
     if (count == 0) return ECC_OK;
     if (!imgs) return fail(ctx, ECC_ERR_INVALID_ARG, "ecc_compute_batch: null descriptor array");
     std::vector<Job> jobs((size_t)count);
-    for (int32_t i = 0; i < count; ++i) {
-        char where[64];
-        snprintf(where, sizeof where, "ecc_compute_batch: image %d", i);
-        ecc_status st = validate(ctx, imgs[i], nbins, where, &jobs[i], 4);
-        if (st != ECC_OK) return st;
-    }
+    ecc_status st = validate_batch(ctx, imgs, count, nbins, "ecc_compute_batch", jobs);
+    if (st != ECC_OK) return st;
     DeviceGuard g(ctx->device);
     if (!g.ok) return fail(ctx, ECC_ERR_DEVICE, "hipSetDevice failed");
     return enqueue_batch(ctx, jobs, nbins, (hipStream_t)hip_stream);
@@ -1542,14 +1553,10 @@ ecc_status ecc_batch_schedule(const ecc_image* imgs, int32_t count, int32_t nbin
     }
     ecc_ctx probe;   // carries validation messages only; owns no device resource
     std::vector<Job> jobs((size_t)count);
-    for (int32_t i = 0; i < count; ++i) {
-        char where[64];
-        snprintf(where, sizeof where, "ecc_batch_schedule: image %d", i);
-        const ecc_status st = validate(&probe, imgs[i], nbins, where, &jobs[(size_t)i], 4);
-        if (st != ECC_OK) {
-            g_create_err = probe.err;
-            return st;
-        }
+    const ecc_status st = validate_batch(&probe, imgs, count, nbins, "ecc_batch_schedule", jobs);
+    if (st != ECC_OK) {
+        g_create_err = probe.err;
+        return st;
     }
     BatchTables T;
     build_batch_tables(cu_count, construction, jobs, nbins, T, sh);
@@ -1623,12 +1630,8 @@ ecc_status ecc_batch_plan_create(ecc_ctx* ctx, const ecc_image* imgs, int32_t co
     if (count < 1) return fail(ctx, ECC_ERR_INVALID_ARG, "ecc_batch_plan_create: count must be at least 1");
     if (!imgs) return fail(ctx, ECC_ERR_INVALID_ARG, "ecc_batch_plan_create: null descriptor array");
     std::vector<Job> jobs((size_t)count);
-    for (int32_t i = 0; i < count; ++i) {
-        char where[64];
-        snprintf(where, sizeof where, "ecc_batch_plan_create: image %d", i);
-        ecc_status st = validate(ctx, imgs[i], nbins, where, &jobs[i], 4);
-        if (st != ECC_OK) return st;
-    }
+    ecc_status st = validate_batch(ctx, imgs, count, nbins, "ecc_batch_plan_create", jobs);
+    if (st != ECC_OK) return st;
     DeviceGuard g(ctx->device);
     if (!g.ok) return fail(ctx, ECC_ERR_DEVICE, "hipSetDevice failed");
     ecc_batch_plan* p = new (std::nothrow) ecc_batch_plan;
@@ -1636,7 +1639,7 @@ ecc_status ecc_batch_plan_create(ecc_ctx* ctx, const ecc_image* imgs, int32_t co
     p->ctx = ctx;
     p->jobs = std::move(jobs);
     p->nbins = nbins;
-    const ecc_status st = plan_upload(p, kDefaultBatchShape);
+    st = plan_upload(p, kDefaultBatchShape);
     if (st != ECC_OK) {
         if (p->dbuf) (void)hipFree(p->dbuf);
         delete p;
