@@ -579,6 +579,8 @@ ecc_status enqueue_hist(ecc_ctx* ctx, char* base, const Job& j, int32_t nbins, h
     L.waves = sz.waves;
     L.depth = sz.depth;
     L.units = j.ndim == 2 ? ecc::units_2d(j.g, ctx->construction, sz.depth) : ecc::units_3d(j.g, ctx->construction);
+    L.per_z = (L.units.tasks + (uint32_t)sz.waves - 1u) / (uint32_t)sz.waves;
+    L.nbricks = L.per_z * (uint32_t)((z_own + sz.depth - 1) / sz.depth);
     L.z_own = z_own;
     L.z_base = z_base;
     L.n0_global = n0_global;

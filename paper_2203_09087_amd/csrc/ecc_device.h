@@ -237,14 +237,14 @@ __device__ __forceinline__ bool last_to_arrive(uint32_t* counter, uint32_t total
 // rows into the ECC, then re-arms the counter.  It saves the merge launch where the
 // rows are few enough for one workgroup.
 __device__ __forceinline__ void fused_merge(int32_t* hist, const int32_t* partials, int width, int64_t* out,
-                                            uint32_t* counter)
+                                            uint32_t* counter, uint32_t waves)
 {
     const int rows = (int)(gridDim.x * gridDim.y);
     if (!last_to_arrive(counter, (uint32_t)rows)) return;
     // the rows as one flat array, 16 loads in flight per thread, added with LDS
     // atomics into int64 counters (the histogram's space, free after the flush);
     // element i adds to bin i mod width (tracked incrementally)
-    const int bd = (int)blockDim.x, t = (int)threadIdx.x;
+    const int bd = (int)(waves * 64u), t = (int)threadIdx.x;
     uint64_t* acc = reinterpret_cast<uint64_t*>(hist);
     for (int j = t; j < width; j += bd) acc[j] = 0;
     __syncthreads();
@@ -271,11 +271,13 @@ __device__ __forceinline__ void fused_merge(int32_t* hist, const int32_t* partia
 
 // ------------------------------------------------------------ main kernels
 
-__device__ __forceinline__ void zero_hist(const HistRef& H, int width)
+// Clears every copy (the words between them too), 16 bytes a store: the array starts on
+// 16 bytes and the copies are a multiple of 8 words apart.  waves: of the workgroup.
+__device__ __forceinline__ void zero_hist(const HistRef& H, uint32_t waves)
 {
-    const int words = width + (int)H.first;
-    for (uint32_t c = 0; c < H.copies; ++c)
-        for (int j = threadIdx.x; j < words; j += blockDim.x) H.hist[c * H.stride + j] = 0;
+    uint4* h = reinterpret_cast<uint4*>(H.hist);
+    const uint32_t n = H.copies * H.stride / 4u;
+    for (uint32_t j = threadIdx.x; j < n; j += waves * 64u) h[j] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
 }
 
@@ -312,11 +314,11 @@ __device__ __forceinline__ int32_t wave_scan32(int32_t v)
 // 2^32.  Each wave
 // scans a run of 64-bin segments in place in LDS, then adds the runs before it.
 __device__ __forceinline__ void flush_hist(const HistRef& H, int32_t* dst, int width, bool add, int sign,
-                                           const int32_t* prev = nullptr)
+                                           uint32_t nwaves, const int32_t* prev = nullptr)
 {
     __shared__ int32_t run_total[kMaxWaves];
     __syncthreads();
-    const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6), waves = (int)(blockDim.x >> 6);
+    const int lane = (int)(threadIdx.x & 63), w = (int)(threadIdx.x >> 6), waves = (int)nwaves;
     const int segs = (width + 63) / 64, per = (segs + waves - 1) / waves;
     const int s0 = min(w * per, segs), s1 = min(s0 + per, segs);
     int32_t run = 0;
@@ -381,13 +383,13 @@ __device__ __forceinline__ BinParams uniform_params(BinParams p)
 // pass's key pairs itself (up to 8 KB from the L2: about 1 us at the start of the
 // launch, where a launch of its own that did it once took 2.6 to 4.8 us).
 template <int DT>
-__device__ __forceinline__ BinParams load_params(const EccLaunch& L)
+__device__ __forceinline__ BinParams load_params(const EccLaunch& L, uint32_t waves)
 {
     if (!L.mm) return uniform_params<DT>(L.params);
     __shared__ uint32_t wlo[kMaxWaves], whi[kMaxWaves];
     uint32_t lo = 0xFFFFFFFFu, hi = 0u;
     const uint2* pairs = (const uint2*)L.mm;
-    for (int i = (int)threadIdx.x; i < L.mm_count; i += (int)blockDim.x) {
+    for (int i = (int)threadIdx.x; i < L.mm_count; i += (int)(waves * 64u)) {
         const uint2 p = pairs[i];
         lo = min(lo, p.x);
         hi = max(hi, p.y);
@@ -402,7 +404,7 @@ __device__ __forceinline__ BinParams load_params(const EccLaunch& L)
         whi[threadIdx.x >> 6] = hi;
     }
     __syncthreads();
-    for (int k = 0; k < (int)(blockDim.x >> 6); ++k) {
+    for (int k = 0; k < (int)waves; ++k) {
         lo = min(lo, wlo[k]);
         hi = max(hi, whi[k]);
     }

@@ -219,6 +219,7 @@ struct EccLaunch {
     int ndim, dtype, construction;
     Geom g;
     Units units;                   // units_3d or units_2d of g
+    uint32_t per_z, nbricks;       // 3D: workgroup bricks per plane block, and in all
     const uint32_t* mm;            // non-null: AUTO range, the mm_count min/max key pairs of the image
     int32_t mm_count;
     BinParams params;              // used when mm is null (nbins always)
