@@ -1830,10 +1830,10 @@ ecc_status ecc_autotune(ecc_ctx* ctx, const ecc_image* img, int32_t nbins, int32
     }
     // the bins-per-pass split: half the window (two passes, half the LDS each)
     // at the default shape and with more workgroups per CU, which the smaller
-    // LDS allows
-    if (def.window >= 2048)
-        for (int wgs : {def_wgs, def_wgs + 2})
-            add(def.waves, def.depth, wgs, std::min<int32_t>(def.window / 2, ecc::kMaxLdsBins));
+    // LDS allows.  Not above kMaxLdsBins: a shape tuned there holds for every such
+    // number of bins, and a window that is two passes of one is many of another.
+    if (def.window >= 2048 && nbins <= ecc::kMaxLdsBins)
+        for (int wgs : {def_wgs, def_wgs + 2}) add(def.waves, def.depth, wgs, def.window / 2);
     // histogram copies for narrow windows (few bins leave LDS for more)
     if (def.window <= 1024)
         for (int copies : {2, 4, 8}) add(def.waves, def.depth, def_wgs, 0, copies);

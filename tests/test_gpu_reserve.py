@@ -83,3 +83,17 @@ def test_wide_histogram_at_a_set_number_of_workgroups(oracle_mod, wgs):
     finally:
         first.close()
         ctx.close()
+
+
+def test_a_tuned_shape_holds_no_window_above_4096_bins():
+    """A shape tuned above 4096 bins is used for every such number of bins, so it names
+    none of its own bins per pass (below, it may)."""
+    from paper_2203_09087_amd import ecc
+    vol = torch.randint(0, 16384, (6, 9, 20), device="cuda", dtype=torch.int16)
+    ctx = ecc.Context(0, "vertex")
+    try:
+        for nbins in (4097, 5000, 16384, 40000):
+            print(f"case: autotune at {nbins} bins", flush=True, file=sys.stderr)
+            assert ctx.autotune(vol, nbins, value_range=(0, 16383), reps=1)["window"] == 0
+    finally:
+        ctx.close()
