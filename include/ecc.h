@@ -172,7 +172,7 @@ ecc_status ecc_compute_ex(ecc_ctx* ctx, const ecc_image* img, int32_t nbins, voi
 ecc_status ecc_compute_noalloc(ecc_ctx* ctx, const ecc_image* img, int32_t nbins, void* hip_stream);
 
 /* ECC of `count` images in one persistent histogram launch per dtype present
- * (then one merge and one scan launch for all images).  imgs: HOST array of `count`
+ * (then one merge launch for up to 65535 images).  imgs: HOST array of `count`
  * descriptors; images may differ in ndim, dtype, size and range mode but share
  * nbins and the context's filtration; each writes its own `out`.  A 4D image
  * enters as its signed 3D passes (hyperplanes and adjacent max/min pairs, as in
@@ -215,9 +215,9 @@ ecc_status ecc_compute_streamed(ecc_ctx* ctx, const ecc_image* img, int32_t nbin
 ecc_status ecc_smooth13(ecc_ctx* ctx, const float* in, float* out, int64_t n1, int64_t n2, const float* taps,
                         void* hip_stream);
 
-/* Launch shape of the single-image kernel: waves per workgroup (2D: a workgroup
- * covers waves * 63 consecutive position columns; 3D: each wave takes 126
- * neighbouring columns of a strip of rows), rows (2D) or planes (3D) per
+/* Launch shape of the single-image kernel: waves per workgroup (each takes 126
+ * neighbouring position columns of a block of rows, 3D: of a strip of 6 rows, running
+ * on into the next block or strip at a row's end), rows (2D) or planes (3D) per
  * workgroup brick, resident workgroups per CU aimed for, `window`, the bins
  * one pass counts in LDS (Sec. 4.3's block-shared histogram; fewer than nbins
  * makes several passes over the image, each with less LDS; 0: all of nbins up to
@@ -334,7 +334,7 @@ ecc_status ecc_batch_schedule(const ecc_image* imgs, int32_t count, int32_t nbin
 /* Kernel timing, for measurement tools (the method itself does not need it).
  * With enable != 0, every later call on `ctx` gives each launch of the
  * histogram kernel (the voxel pass of Sec. 2.3 that reads the image; AUTO
- * min/max, merge and scan launches are not counted) a pair of HIP events that
+ * min/max and merge launches are not counted) a pair of HIP events that
  * take that kernel's own start and end (hipExtLaunchKernel).
  * enable == 0 stops recording and drops unread records.  Timing changes no result.
  * Errors: ECC_ERR_INVALID_ARG (ctx null), ECC_ERR_DEVICE. */

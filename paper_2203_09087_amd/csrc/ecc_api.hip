@@ -3,7 +3,7 @@
 // Validates every argument before anything is enqueued, resolves the binning
 // parameters (on the host for explicit ranges, on the device for AUTO ranges),
 // owns the context's scratch memory, and enqueues the kernel sequence
-//     [minmax -> params]  ->  hist (per LDS bin window)  ->  merge
+//     [minmax]  ->  hist (per LDS bin window)  ->  merge
 // on the caller's stream.
 #include <stdio.h>
 #include <string.h>
@@ -69,7 +69,6 @@ constexpr int kMinmaxBlocks = 1024;
 // The first bytes of the scratch hold the counters of the single-image merge,
 // which the kernels re-arm after every call; no other use may overwrite them.
 constexpr size_t kCounterBytes = 1024;
-static_assert(kCounterBytes >= ecc::kCounterWords * sizeof(uint32_t), "counter region too small");
 constexpr size_t kAlign = 256;
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
@@ -297,7 +296,7 @@ ecc::BinParams host_params(const Job& j, int32_t nbins)
     p.nbins = nbins;
     if (j.dtype == ECC_F32) {
         p.flat = (j.hi == j.lo) ? 1 : 0;
-        // a flat range bins through scale = +inf (see key_of in the kernels)
+        // a flat range bins through scale = +inf (bin_of in the kernels)
         p.scale = p.flat ? HUGE_VAL : (double)nbins / (j.hi - j.lo);
         p.base = p.flat ? std::nextafter(j.lo, HUGE_VAL) : j.lo;
     } else {
@@ -435,8 +434,9 @@ Sizes plan_sizes(const ecc_ctx* ctx, const Job& j, int32_t nbins, const ecc_laun
     const int cons = ctx->construction;
     // bins per LDS pass: all of them up to kWideLdsBins, or fewer when tuned so.  Up
     // to kMaxLdsBins for images so large that the rows they need at least would not
-    // fit the fixed scratch of ecc_compute_noalloc, and for 8-bit data (256 levels:
-    // more bins than that are only asked for in tests of the passes).
+    // fit the fixed scratch of ecc_compute_noalloc, and for 8-bit data: its 256 levels
+    // fill few of more bins than that, and callers of ecc_kernel_time count its launches
+    // by passes of 4096.
     const bool wide = j.dtype != ECC_U8 && j.nvox < (int64_t(1) << 34);
     s.window = std::min<int32_t>(nbins, wide ? ecc::kWideLdsBins : ecc::kMaxLdsBins);
     if (tuned && tuned->window > 0) s.window = std::min<int32_t>(s.window, tuned->window);

@@ -43,7 +43,6 @@ namespace dev {
 
 
 constexpr int kThreads = 256;
-constexpr int kWaves = kThreads / 64;
 
 // ------------------------------------------------------------------ binning
 //
@@ -349,7 +348,6 @@ __device__ __forceinline__ void flush_hist(const HistRef& H, int32_t* dst, int w
 // memory, and brick coordinates come out of integer divisions that the compiler
 // expands into vector arithmetic.  Without this, branches on them are lowered
 // as divergent and the row masks that depend on them leave scalar registers.
-__device__ __forceinline__ bool uniform_flag(int32_t f) { return __builtin_amdgcn_readfirstlane(f) != 0; }
 __device__ __forceinline__ uint32_t uniform_u32(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 __device__ __forceinline__ int64_t uniform_i64(int64_t v)
 {

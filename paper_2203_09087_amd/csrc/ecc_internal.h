@@ -106,7 +106,7 @@ inline __host__ __device__ int64_t axis_positions(int64_t n, int construction)
 constexpr int kRows3 = ECC_ROWS3;      // rows per 3D brick of a batch
 constexpr int kStripRows = ECC_STRIP_ROWS;   // rows per strip of a single 3D image
 constexpr int kChunk2 = ECC_CHUNK2;    // rows loaded together in the 2D kernel
-// Waves per workgroup of the main kernels (x-chunk = waves * 63 position columns).
+// Waves per workgroup of the main kernels.
 constexpr int kMaxSetWaves = 9;   // the most that a launch shape can ask for
 constexpr int kBatchWaves = 8;    // of a batch launch, or kMaxWaves (build_batch_tables)
 constexpr int kMaxWaves = 16;
@@ -226,7 +226,7 @@ struct EccLaunch {
     int32_t bin_lo, width;
     int32_t windowed;              // nbins > width: skip bins outside the window
     int32_t grid;                  // number of workgroups
-    int32_t waves;                 // waves per workgroup (x-chunk = 63 * waves position columns)
+    int32_t waves;                 // waves per workgroup, a wave task each
     int64_t depth;                 // planes (3D) or rows (2D) per workgroup brick
     // 3D slab of a larger volume (streaming): planes [0, z_own) of the g.n0 in
     // memory are counted (a plane beyond them is the collar the last one needs);
@@ -244,7 +244,7 @@ struct EccLaunch {
     int32_t flush_sign;            // +1, or -1: the histogram enters its row negated
     int64_t* out;                  // the caller's output
     uint32_t* counter;             // the fused merge's
-    int32_t fused;                 // one window, few rows: the last workgroup merges and scans into out
+    int32_t fused;                 // one window, few rows: the last workgroup merges into out
     uint32_t hist_stride;          // LDS words between the histogram copies (lds_stride(width))
     uint32_t hist_copies;          // copies of the histogram (a power of two up to kMaxHistCopies)
     uint32_t lds_bytes;            // dynamic LDS of the launch
@@ -341,8 +341,8 @@ struct BatchWork {
 BatchWork batch_work(BatchImage& im, int construction, int depth3, int depth2, int64_t planes);
 constexpr int kBrickWaves = 9;                 // waves that a brick's width is chosen for
 
-// Launchers (ecc_kernels.hip: histogram kernels; ecc_reduce.hip: min/max,
-// parameters, merge).  All enqueue on `s` and return the launch status.
+// Launchers (ecc_kernels.hip: histogram kernels; ecc_reduce.hip: min/max
+// and merge).  All enqueue on `s` and return the launch status.
 
 // 13 smoothing taps (ecc_smooth.hip): tap k weights the neighbour at offset k - 6.
 struct Taps13 {
@@ -381,7 +381,6 @@ struct MergeArgs {
     int32_t sign;                  // -1: subtract the sums
 };
 constexpr int32_t kWideMerge = 1536;   // bins from which a merge block takes 32 of them, else 16
-constexpr int kCounterWords = 256;
 hipError_t launch_merge(const MergeArgs& A, hipStream_t s);
 // Folds `blocks` min/max key pairs into the running pair acc (first: start it).
 hipError_t launch_mm_fold(const uint32_t* mm, int blocks, uint32_t* acc, bool first, hipStream_t s);

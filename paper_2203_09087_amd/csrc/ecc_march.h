@@ -21,8 +21,8 @@
 // its waves run nothing but plain 32-bit adds, ands and shifts), so the packed
 // forms halve the time of what they do.  A row of two positions takes 47 (float32,
 // 14 of them binning 7/6 rows), the LDS is busy 22% of the cycles.  512^3 float32,
-// 4096 bins: 0.139 to 0.115 ms (5.8 TB/s past the L2, 1.26 times the image, beside
-// 0.1 ms of vector issue); 256^3 uint8, 256 bins: 0.044 to 0.017 ms.
+// 4096 bins: 0.142 to 0.120 ms (5.5 TB/s past the L2, 1.24 times the image, beside
+// 0.1 ms of vector issue); 256^3 uint8, 256 bins: 0.033 to 0.021 ms.
 //
 // Fields.  A register of byte fields holds [A.a, A.b, B.a, B.b]: two quantities
 // A and B (bytes 0-1 and 2-3) of the lane's positions a and b.  A field is a
