@@ -374,8 +374,8 @@ void pick_shape(const ecc_ctx* ctx, const Job& j, const ecc_launch_shape* tuned,
         forced_d = flat ? (double)((std::min<int64_t>(tuned->depth, 4096) + ecc::kChunk2 - 1) / ecc::kChunk2 * ecc::kChunk2)
                         : (double)std::min<int64_t>(tuned->depth, 256);
     // histograms are cleared and flushed by more waves than a small image has work for
-    // (at least 4 from 256 bins on: 24^3 float32, 500 bins, 11.2 us with 1 wave and 10.5
-    // with 4; 30x25x30, 900 bins, 12.8 and 11.3)
+    // (at least 4 from 256 bins on: 20^3 float32, 300 bins, 9.7 us with 1 wave and 8.7 with
+    // 4; 30x25x30, 900 bins, 11.3 and 10.2; 8 from 4096 on)
     const double least = s.window >= ecc::kMaxLdsBins ? 8 : (s.window >= 256 ? 4 : 1);
     double best = HUGE_VAL;
     s.waves = 0;

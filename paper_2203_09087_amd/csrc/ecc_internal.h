@@ -251,12 +251,12 @@ struct EccLaunch {
 };
 // Partial-row words (grid x window) up to which the histogram kernel's last
 // workgroup merges the rows (fused_merge) instead of a launch of k_merge.  In us a
-// call, merged so and with the launch: 64^2 float32, 500 bins (up to 2048 words) 8.7
-// and 11.2; 300^2 uint8 (2 to 4 thousand) 8.9 and 11.5; 400^2 uint8 (4 to 6 thousand)
-// 9.6 and 11.6; 700^2 uint8 (8 to 16 thousand) 12.1 and 11.6; 60^3 uint8 13.8 and
-// 11.4; 100^3 uint8 (32 to 64 thousand) 24.5 and 11.6.  The line lies on the safe
-// side of the crossing, which is near 8 thousand.
-constexpr int64_t kFusedMergeWords = int64_t(1) << 12;
+// call, merged so and with the launch: 64^2 float32, 500 bins (up to 2048 words) 8.5
+// and 11.0; 300^2 uint8 (2 to 4 thousand) 8.3 and 10.7; 400^2 uint8 (4 to 6 thousand)
+// 8.4 and 10.6; 30x25x30 float32, 500 bins (6 to 8 thousand) 9.6 and 11.9; 700^2 uint8
+// (8 to 16 thousand) 11.0 and 10.6; 60^3 uint8 12.6 and 10.5; 150^2 float32, 4096 bins
+// 15.0 and 11.9; 100^3 uint8 (32 to 64 thousand) 23.3 and 10.9.
+constexpr int64_t kFusedMergeWords = int64_t(1) << 13;
 
 // ---------------------------------------------------------------- batches
 

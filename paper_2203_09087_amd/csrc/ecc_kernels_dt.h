@@ -70,8 +70,9 @@ __global__ __launch_bounds__(kMaxWaves * 64) __attribute__((amdgpu_waves_per_eu(
 // segment is a run of steps (planes, or groups of kChunk2 rows) of the volume's wave
 // tasks, numbered task by task; each wave takes an equal part of it.  With whole tasks
 // of 8 planes or 128 rows per wave the last round left waves idle and the start-up of
-// a task (2.5 planes) was a quarter of its work: 512 uint8 images took 376 us and now
-// 338, 71 float32 images of 4096 bins 146 and 123, 11 uint8 images 31 and 26.  PAIRS: the launch
+// a task (2.5 planes) was a quarter of its work: 512 uint8 images took 376 us and 338
+// with equal parts, 71 float32 images of 4096 bins 146 and 123, 11 uint8 images 31
+// and 26.  PAIRS: the launch
 // holds pair volumes (their tasks load two hyperplanes).  WAVES per workgroup, as a
 // constant (read from the launch it costs the 512-image batch 5%).
 template <int DT, int CONS, bool WIN, bool PAIRS, int WAVES>
