@@ -107,7 +107,7 @@ void k_ecc_batch(BatchLaunch B)
                          uniform_u32(I.units.pairs_full), uniform_u32(I.units.pairs_edge),
                          uniform_u32(I.units.tasks)};
         const int ndim = (int)uniform_u32((uint32_t)I.ndim);
-        zero_hist(H, WAVES);
+        zero_hist_words(H, B.width);
         // steps of a wave task: groups of rows (2D), planes (3D)
         const int64_t len = ndim == 2 ? L.depth / kChunk2 : L.depth;
         const int64_t b0 = uniform_i64(S.b0), steps = uniform_i64(S.b1) - b0;
@@ -138,7 +138,7 @@ void k_ecc_batch(BatchLaunch B)
         }
         const size_t slot = (size_t)uniform_u32((uint32_t)S.slot);
         int32_t* dst = B.partials + slot * (size_t)(WIN ? B.row_stride : B.width);
-        flush_hist(H, dst, B.width, false, (int)uniform_u32((uint32_t)I.sign), WAVES,
+        flush_hist(H, dst, B.width, false, (int)uniform_u32((uint32_t)I.sign), blockDim.x >> 6,
                    WIN && B.bin_lo > 0 ? dst + B.row_stride - 1 : nullptr);
         __syncthreads();   // the histogram is read before the next segment clears it
     }
