@@ -201,17 +201,17 @@ hipError_t launch_merge_batch(const BatchLaunch& B, hipStream_t s)
         A.bin_lo = B.bin_lo;
         A.sign = 1;
         const int n = (int)std::min<int64_t>(B.count - i0, kMaxImages);
-        // Up to 32 rows for every image: a thread per bin (16 images of 1000^2, 4096 bins,
-        // about 17 rows each: 31 and 22 us a launch; 250 of 800^2 194 and 164), or per
+        // Up to 16 rows for every image: a thread per bin (16 images of 1000^2, 4096 bins,
+        // 16 rows each: 31 and 22 us a launch; 250 of 800^2 194 and 164), or per
         // four bins where that leaves thousands of blocks (2000 of 16^2, 4096 bins: 83
         // and 74).  It adds an image's rows four at a time in turn, about 0.06 us a row,
-        // so more of them take blocks of fewer bins (16 serving images, up to about 50
-        // rows: 87.1 with it and 86.3 us; 3 of 64^3, about 170 rows: 23 and 18), unless
+        // so more of them take blocks of fewer bins (2 images of 500^2, 32 rows: 14.4 with
+        // it and 13.6 us; 3 of 64^3, about 170 rows: 23 and 18), unless
         // those are so many that their launch takes longer than the rows (1000 of 16^2
         // and one of 3000^2, 4096 bins: 64 thousand blocks, 132 and 60 us).
         const int64_t blocks = (int64_t)n * ((B.width + 63) / 64);
         hipError_t e;
-        if (B.max_rows <= 32 || 44 * (int64_t)B.max_rows <= blocks)
+        if (B.max_rows <= 16 || 44 * (int64_t)B.max_rows <= blocks)
             e = (int64_t)n * B.width > (int64_t(4096) * kThreads) ? launch_merge_rows<4>(A, n, s) : launch_merge_rows<1>(A, n, s);
         else if (B.avg_rows <= 12)
             e = launch_merge_k<4, 64>(A, n, s);

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 
 # (images, bins): blocks of 256 bins; of 1024 from 4096 blocks of 256 bins on; several
-# windows; up to 32 rows each, and more than 32 for one of them
+# windows; up to 16 rows each, and more than 16 for one of them
 BATCHES = [([(5, 7)] * 40 + [(40, 37, 29)], 1), ([(16, 16)] * 300, 257), ([(16, 16)] * 300 + [(60, 60, 60)], 4096),
            ([(3, 5)] * 1100, 1025), ([(20, 30)] * 30 + [(3, 8, 9, 10)], 5000), ([(1500, 1500)] + [(8, 8)] * 5, 300)]
 
