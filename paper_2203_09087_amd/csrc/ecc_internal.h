@@ -253,10 +253,11 @@ struct EccLaunch {
 // workgroup merges the rows (fused_merge) instead of a launch of k_merge.  In us a
 // call, merged so and with the launch: 64^2 float32, 500 bins (up to 2048 words) 8.5
 // and 11.0; 300^2 uint8 (2 to 4 thousand) 8.3 and 10.7; 400^2 uint8 (4 to 6 thousand)
-// 8.4 and 10.6; 30x25x30 float32, 500 bins (6 to 8 thousand) 9.6 and 11.9; 700^2 uint8
-// (8 to 16 thousand) 11.0 and 10.6; 60^3 uint8 12.6 and 10.5; 150^2 float32, 4096 bins
-// 15.0 and 11.9; 100^3 uint8 (32 to 64 thousand) 23.3 and 10.9.
-constexpr int64_t kFusedMergeWords = int64_t(1) << 13;
+// 8.4 and 10.6, but 500x200x33 uint16, 16 bins (512 rows, 8192 words) 18.1 and 15.1: its
+// LDS adds meet in few counters; 700^2 uint8 (8 to 16 thousand) 11.0 and 10.6; 60^3
+// uint8 12.6 and 10.5; 150^2 float32, 4096 bins 15.0 and 11.9; 100^3 uint8 (32 to 64
+// thousand) 23.3 and 10.9.
+constexpr int64_t kFusedMergeWords = int64_t(1) << 12;
 
 // ---------------------------------------------------------------- batches
 
