@@ -174,7 +174,7 @@ inline Layout3 layout_3d(const Geom& g, int construction, int waves)
 // 2D: the same with blocks of `depth` rows (a multiple of 8) in place of strips;
 // a last block of fewer rows is cut for itself.  Rows too long for 32-bit offsets
 // from one block into the next ones: every block for itself (and within it the
-// loads start anew every 8 rows, march_2d).
+// loads start anew where a row's offset grows past 32 bits, march_2d).
 struct Units {
     uint32_t slots;        // per strip (block)
     uint32_t sa, sb;       // strips (blocks) [sa, sb) are numbered through

@@ -560,12 +560,16 @@ __device__ __forceinline__ void march_2d(const void* base, uint32_t row_bytes, c
     __amdgpu_buffer_rsrc_t rs = rsrc_at(base);
     T raw[G][2];
     uint32_t soff = 0;   // byte offset of the next row to load
-    // EDGE: the loads start anew at row r (the last readable one past it), from a
-    // 64-bit address.  A block's rows may span more than 4 GiB (rows of up to 2^27
-    // bytes, blocks of any depth); from one start to the next are 8 or 9 rows.
-    auto start_at = [&](uint32_t r) {
-        rs = rsrc_at((const char*)base + (int64_t)(r < avail ? r : avail - 1u) * (int64_t)row_bytes);
-        soff = 0;
+    // EDGE: a block's rows may span more than 4 GiB (rows of up to 2^27 bytes, blocks of
+    // any depth), so the loads start anew, from the next row's 64-bit address, before a
+    // row's offset passes 2^30 by more than 8 rows.
+    const char* from = (const char*)base;
+    auto keep_offsets_small = [&]() {
+        if (soff > (1u << 30)) {
+            from += soff;
+            rs = rsrc_at(from);
+            soff = 0;
+        }
     };
     // loads row r (relative to the block): EDGE stays on the last readable row;
     // otherwise the row after the block takes the lanes' own places
@@ -610,7 +614,7 @@ __device__ __forceinline__ void march_2d(const void* base, uint32_t row_bytes, c
     const uint32_t plain = EDGE ? (rows < avail ? rows : rows - 1u) / G * G : rows - G;
     uint32_t y = 0;
     for (; y < plain; y += G) {
-        if (EDGE) start_at(y + 1u + (uint32_t)G);
+        if (EDGE) keep_offsets_small();
 #pragma unroll
         for (int k = 0; k < G; ++k) {
             // the row's registers take the next group's row as soon as its key is made

@@ -23,7 +23,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(os.path.dirname(HERE), "paper_2203_09087_amd", "csrc")
 UNIT, ROWS = 63, 6          # owned lanes of a half task; rows of a strip
 MAX_ROW_BYTES = 1 << 27     # longest row that is accepted
-LOADED_ROWS = 9             # rows of a 2D block from one 64-bit address, at most
+FRESH = 1 << 30             # row offset in a 2D block past which the loads start anew
 
 SHIM = r"""
 #include <string.h>
@@ -158,8 +158,8 @@ def test_byte_offsets_fit_32_bits(lib, top):
                     U = call(lib.units2, 4 * depth + 3, n2, top, depth)
                     if U[2] > 0:     # numbered through: offsets reach over all the blocks of a task
                         assert (n2 + q * depth * n2 + (depth + 1) * n2) * size < 2 ** 32, (n2, size, depth)
-                    else:            # every block for itself, from a new address every 8 rows
-                        assert (n2 + LOADED_ROWS * n2) * size < 2 ** 32
+                    else:            # every block for itself: 8 rows past FRESH at most
+                        assert FRESH + (n2 + 8 * n2) * size < 2 ** 32
 
 
 @pytest.mark.parametrize("top", [0, 1])
